@@ -49,9 +49,6 @@
  *       * with FMM_OPT_USE_GRAPH, capturing a 17th graph first releases the
  *         least recently used graph, after the host has waited for that
  *         graph's last launch (on whatever stream it ran);
- *       * the first call on a set that runs the round split (FMM_OPT_ROUND_SPLIT,
- *         or fmm_autotune timing it) allocates its round list and round
- *         sums, held with the set;
  *       * the first FMM_EXACT_SLICE call on a set, or one with more slices
  *         than before, allocates the slice planes (after waiting for the
  *         set's last launch when it replaces them);
@@ -124,7 +121,9 @@ typedef struct {
 
 /* Library options (fmm_set_option). */
 #define FMM_OPT_M2L_KERNEL  1  /* 0 auto (default), 1 reference VALU kernel, 2 MFMA kernel */
-#define FMM_OPT_USE_GRAPH   2  /* 1 (default): replay cached hipGraphs for M2L; 0: plain launches */
+#define FMM_OPT_USE_GRAPH   2  /* 1 (default): replay cached hipGraphs for the M2L forms that take more than
+                                  one launch (FMM_FP64 tile configurations 2 to 5, FMM_SPLIT_FP32); 0: plain
+                                  launches. FMM_FP64 and FMM_FP64_HARMONIC by default are one launch */
 #define FMM_OPT_TILE_CONFIG 3  /* -1 (default): autotuned/built-in choice; >= 0 forces a table entry */
 #define FMM_OPT_P2M_WINDOW  5  /* fmm_p2m: 0 (default) writes every cell of the frame; 1 reads and writes
                                   only the frame rows (y, z) in [2,22)^2 (all 24 cells of each), which
@@ -135,16 +134,13 @@ typedef struct {
                                   (p+1)^2 harmonic columns, dM expanded from the folded components;
                                   equal to the dense adjoint up to rounding; MFMA kernel only) */
 #define FMM_OPT_SLICES      7  /* FMM_EXACT_SLICE: slices per operand S, 6, 7 (default) or 8 */
-#define FMM_OPT_ROUND_SPLIT 6  /* fmm_m2l (and the M2L of fmm_p2m_m2l when it runs as two
-                                  launches) on batches of at most 256 sub-grids, with a configuration
-                                  with LDS-staged tables: 0 one workgroup per sub-grid; 1 one
-                                  workgroup per (sub-grid, round of two moment components), each
-                                  round's sums added in round order by a second kernel; -1 (default)
-                                  the choice fmm_autotune made for the descriptor set and precision
-                                  (one workgroup per sub-grid until it has run). For batches that
-                                  cannot fill the GPU, or whose longest sub-grid (p = 4) would set
-                                  the time; equal up to rounding; 140 KB of device memory per
-                                  (sub-grid, round) is held per descriptor set. */
+#define FMM_OPT_ROUND_SPLIT 6  /* FMM_FP64 and FMM_FP64_HARMONIC M2L (tile configurations 0, 1, 7, 9, 10):
+                                  0 one workgroup per sub-grid; 1 batches of at most 256 sub-grids in
+                                  parts of a sub-grid's targets, spread over the workgroups; -1 (default)
+                                  whole sub-grids or parts, whichever is expected to be faster for the
+                                  batch. For batches that cannot fill the GPU, whose longest sub-grid
+                                  (p = 4) would set the time, or whose last wave of sub-grids is short.
+                                  The results are the same bits. */
 
 /* Create a context on HIP device `device`, or a host-only context with
  * device = -1 (argument checking and host queries only; compute calls then
@@ -219,11 +215,11 @@ fmm_status fmm_m2l_noalloc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
  * moments itself, during the M2L of the sub-grid before it, so the
  * HBM-bound moment work of some workgroups overlaps the matrix work of the
  * others. The single launch is used for batches of more sub-grids than the
- * GPU has compute units, with ppc = 8, 16-byte aligned pos and mass, even
- * part_off and a configuration with LDS-staged tables (every
- * FMM_FP64_HARMONIC configuration; FMM_FP64 configurations 0 and 1);
- * otherwise, and with FMM_OPT_M2L_KERNEL = 1, the call runs the two steps
- * one after the other, with the same results. */
+ * GPU has compute units for which it is expected to be faster than P2M and the
+ * M2L's own choice of parts, with ppc = 8, 16-byte aligned pos and mass, even
+ * part_off and the default FMM_FP64 or FMM_FP64_HARMONIC tile configuration
+ * (0, 1, 7, 9 or 10); otherwise, and with FMM_OPT_M2L_KERNEL = 1, the call runs
+ * the two steps one after the other, with the same results. */
 fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
                        const double* pos, const double* mass, int32_t ppc,
                        double* M, double* L, fmm_precision prec, void* stream);
@@ -335,14 +331,10 @@ fmm_status fmm_tree_solve(fmm_ctx* ctx, const fmm_tree* tree, const double* pos,
  * device memory `out` ([892][C][C], offsets in fmm_stencil order). */
 fmm_status fmm_stencil_tables(fmm_ctx* ctx, int32_t p, double* out, void* stream);
 
-/* Autotuner: time every candidate M2L configuration (waves per workgroup,
- * operand prefetch) on these descriptors and buffers (M read, L
- * overwritten) and keep the fastest for later calls with the same
- * descriptor set and precision; `chosen` (may be NULL) receives its index.
- * On batches of at most 256 sub-grids whose chosen configuration stages its
- * tables in LDS it also times the round split (FMM_OPT_ROUND_SPLIT) with that
- * configuration, allocating its list as the option's first call does, and
- * keeps it for later calls if it is faster and the option is -1.
+/* Autotuner: time every candidate M2L configuration (the streamed kernel, and
+ * for FMM_FP64 those with per-wave table loads) on these descriptors and
+ * buffers (M read, L overwritten) and keep the fastest for later calls with the
+ * same descriptor set and precision; `chosen` (may be NULL) receives its index.
  * Synchronises the stream. FMM_OPT_TILE_CONFIG >= 0 overrides the choice. */
 fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
                         const double* M, double* L, fmm_precision prec,

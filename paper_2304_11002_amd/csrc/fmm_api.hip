@@ -21,7 +21,8 @@ using namespace fmm;
 // device's address of it (fmm_ctx::noalloc_dev) and that address is used.
 constexpr size_t kNoAllocDescBytes = sizeof(fmm_subgrid) * FMM_NOALLOC_MAX_SUBGRIDS;
 constexpr size_t kNoAllocWorkOff = (kNoAllocDescBytes + 255) / 256 * 256;
-constexpr size_t kNoAllocCounterOff = (kNoAllocWorkOff + sizeof(WorkItem) * FMM_NOALLOC_MAX_SUBGRIDS + 255) / 256 * 256;
+constexpr size_t kNoAllocItems = (size_t)max_parts(FMM_NOALLOC_MAX_SUBGRIDS);   // parts of the sub-grids
+constexpr size_t kNoAllocCounterOff = (kNoAllocWorkOff + sizeof(WorkItem) * kNoAllocItems + 255) / 256 * 256;
 constexpr size_t kNoAllocBytes = kNoAllocCounterOff + 256;
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
@@ -104,16 +105,14 @@ struct DescEntry {
   int count[kMaxP + 1] = {};
   WorkList work;                  // matrix-core kernels, dense-form costs (C^2 per pair)
   WorkList work_h;                // the same items ordered by harmonic-form costs ((p+1)^4)
-  // FMM_OPT_ROUND_SPLIT, per form (dense, harmonic): (sub-grid, round) list, the
-  // first slot of each sub-grid, and the rounds' sums; one allocation each
-  void* split_dev[2] = {};
-  void* split_pinned[2] = {};     // host staging of the (sub-grid, round) list
-  WorkList split[2];
-  int* split_base[2] = {};
-  double* split_part[2] = {};
+  // streamed forward, per form (dense, harmonic): whole sub-grids, and their parts
+  // (where planned or small enough to be asked for), with a counter that its
+  // launches leave at zero
+  WorkList whole[2];
+  WorkList parts[2];
+  StreamPlan plan[2];
   bool part_even = true;          // every part_off even: particle blocks 16-byte aligned
   int tuned[4] = {-1, -1, -1, -1};   // autotuned configuration per precision
-  bool split_tuned[4] = {false, false, false, false};   // the autotuner chose the round split
   // FMM_EXACT_SLICE: the sub-grids' slice planes and exponents (one allocation)
   void* slice_dev = nullptr;
   size_t slice_bytes = 0;
@@ -149,7 +148,7 @@ struct fmm_ctx {
   int tile_config = -1;
   int adjoint_form = 0;     // FMM_OPT_ADJOINT_FORM
   int p2m_window = 0;       // FMM_OPT_P2M_WINDOW
-  int round_split = -1;     // FMM_OPT_ROUND_SPLIT: -1 the autotuner's choice, 0 never, 1 always
+  int round_split = -1;     // FMM_OPT_ROUND_SPLIT: -1 as planned, 0 whole sub-grids, 1 parts (small batches)
   int slices = 7;           // FMM_OPT_SLICES
   // fmm_m2l_noalloc: this device's address of the static array, a pinned host
   // copy of its descriptor and work-list part, and the event after its upload
@@ -267,10 +266,6 @@ void free_entry(DescEntry* e) {
   if (e->last_launch) (void)hipEventSynchronize(e->last_launch);
   if (e->ready) (void)hipEventSynchronize(e->ready);
   if (e->dev) (void)hipFree(e->dev);
-  for (int f = 0; f < 2; ++f) {
-    if (e->split_dev[f]) (void)hipFree(e->split_dev[f]);
-    if (e->split_pinned[f]) (void)hipHostFree(e->split_pinned[f]);
-  }
   if (e->pinned) (void)hipHostFree(e->pinned);
   if (e->slice_dev) (void)hipFree(e->slice_dev);
   if (e->ready) (void)hipEventDestroy(e->ready);
@@ -336,8 +331,19 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     ids[desc[b].p].push_back((int)b);
     if (desc[b].part_off & 1) e->part_even = false;
   }
-  std::vector<WorkItem> items = build_work_list(desc, nsub, false);
-  std::vector<WorkItem> items_h = build_work_list(desc, nsub, true);
+  std::vector<WorkItem> items[2], parts[2];   // dense, harmonic
+  StreamPlan plan[2];
+  for (int f = 0; f < 2; ++f) {
+    items[f].resize((size_t)nsub);
+    sort_by_cost(desc, nsub, f == 1, items[f].data());
+    plan[f] = plan_stream(items[f].data(), nsub, ctx->mfma.num_cu);
+    if (plan[f].parts || nsub <= kMaxSplitSubgrids) {
+      parts[f] = items[f];
+      parts[f].resize((size_t)max_parts(nsub));
+      parts[f].resize((size_t)split_items(parts[f].data(), nsub, ctx->mfma.num_cu));
+    }
+    whole_items(items[f].data(), nsub);
+  }
   size_t off_desc = 0;
   size_t off = align_up(nbytes, 256);
   size_t off_ids[kMaxP + 1] = {};
@@ -345,14 +351,17 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     off_ids[p] = off;
     off = align_up(off + sizeof(int) * ids[p].size(), 256);
   }
-  size_t off_work = off;
-  off = align_up(off + sizeof(WorkItem) * items.size(), 256);
-  size_t off_work_h = off;
-  off = align_up(off + sizeof(WorkItem) * items_h.size(), 256);
-  size_t off_counter = off;
-  off = align_up(off + 256, 256);
-  size_t off_counter_h = off;
-  off = align_up(off + 256, 256);
+  size_t off_work[2], off_parts[2], off_counter[2], off_zero[2];
+  for (int f = 0; f < 2; ++f) {
+    off_work[f] = off;
+    off = align_up(off + sizeof(WorkItem) * items[f].size(), 256);
+    off_parts[f] = off;
+    off = align_up(off + sizeof(WorkItem) * parts[f].size(), 256);
+    off_counter[f] = off;
+    off = align_up(off + 256, 256);
+    off_zero[f] = off;
+    off = align_up(off + 256, 256);
+  }
   e->bytes = off;
   HIP_TRY(ctx, hipMalloc(&e->dev, e->bytes));
   HIP_TRY(ctx, hipHostMalloc(&e->pinned, e->bytes, hipHostMallocDefault));
@@ -360,24 +369,29 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
   std::memset(hp, 0, e->bytes);
   std::memcpy(hp + off_desc, desc, nbytes);
   for (int p = 2; p <= kMaxP; ++p) std::memcpy(hp + off_ids[p], ids[p].data(), sizeof(int) * ids[p].size());
-  std::memcpy(hp + off_work, items.data(), sizeof(WorkItem) * items.size());
-  std::memcpy(hp + off_work_h, items_h.data(), sizeof(WorkItem) * items_h.size());
+  for (int f = 0; f < 2; ++f) {
+    std::memcpy(hp + off_work[f], items[f].data(), sizeof(WorkItem) * items[f].size());
+    std::memcpy(hp + off_parts[f], parts[f].data(), sizeof(WorkItem) * parts[f].size());
+  }
   char* dp = static_cast<char*>(e->dev);
   e->d_desc = reinterpret_cast<DevDesc*>(dp + off_desc);
   for (int p = 2; p <= kMaxP; ++p) {
     e->d_ids[p] = reinterpret_cast<int*>(dp + off_ids[p]);
     e->count[p] = (int)ids[p].size();
   }
-  e->work.items = reinterpret_cast<const WorkItem*>(dp + off_work);
-  e->work.count = (int)items.size();
-  e->work.counter = reinterpret_cast<unsigned*>(dp + off_counter);
-  e->work.cost = 0;
-  for (const auto& it : items) e->work.cost += it.cost;
-  e->work_h.items = reinterpret_cast<const WorkItem*>(dp + off_work_h);
-  e->work_h.count = (int)items_h.size();
-  e->work_h.counter = reinterpret_cast<unsigned*>(dp + off_counter_h);
-  e->work_h.cost = 0;
-  for (const auto& it : items_h) e->work_h.cost += it.cost;
+  for (int f = 0; f < 2; ++f) {
+    WorkList& w = f ? e->work_h : e->work;
+    w.items = reinterpret_cast<const WorkItem*>(dp + off_work[f]);
+    w.count = (int)items[f].size();
+    w.counter = reinterpret_cast<unsigned*>(dp + off_counter[f]);
+    e->whole[f] = w;
+    e->whole[f].counter = reinterpret_cast<unsigned*>(dp + off_zero[f]);
+    e->parts[f].items = reinterpret_cast<const WorkItem*>(dp + off_parts[f]);
+    e->parts[f].count = (int)parts[f].size();
+    e->parts[f].counter = e->whole[f].counter;
+    e->parts[f].parts = true;
+    e->plan[f] = plan[f];
+  }
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->ready, hipEventDisableTiming));
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->last_launch, hipEventDisableTiming));
   HIP_TRY(ctx, hipMemcpyAsync(e->dev, e->pinned, e->bytes, hipMemcpyHostToDevice, stream));
@@ -475,7 +489,7 @@ fmm_status fmm_create(fmm_ctx** out, int32_t device) {
   CREATE_TRY(hipGetSymbolAddress(reinterpret_cast<void**>(&c->noalloc_dev), HIP_SYMBOL(scratch)));
   CREATE_TRY(hipHostMalloc(reinterpret_cast<void**>(&c->noalloc_host), kNoAllocCounterOff, hipHostMallocDefault));
   CREATE_TRY(hipEventCreateWithFlags(&c->noalloc_uploaded, hipEventDisableTiming));
-  fill_work_list(nullptr, 0, false, nullptr);   // the work-list builder's tables, set up once
+  sort_by_cost(nullptr, 0, false, nullptr);   // the work-list builder's tables, set up once
   CREATE_TRY(hipStreamSynchronize(c->internal));
 #undef CREATE_TRY
   *out = ctx.release();
@@ -754,16 +768,13 @@ static fmm_status run_ref(fmm_ctx* ctx, DescEntry* e, bool backward, const doubl
   return FMM_OK;
 }
 
-// Launch the persistent matrix-core kernel, through a cached graph if enabled.
-// pos, mass, Mw non-null: the fused P2M + M2L launch (launch_m2l_mfma's fused
-// form; Mw is M, writable).
+// Launch a persistent matrix-core kernel over whole sub-grids, through a cached
+// graph if enabled.
 static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* L,
-                           fmm_precision prec, int cfg, hipStream_t s,
-                           const double* pos = nullptr, const double* mass = nullptr,
-                           double* Mw = nullptr) {
+                           fmm_precision prec, int cfg, hipStream_t s) {
   const WorkList& wl = work_for(e, prec == FMM_FP64_HARMONIC);
   if (!ctx->use_graph) {
-    HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, e->d_desc, M, L, prec, cfg, s, pos, mass, Mw));
+    HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, e->d_desc, M, L, prec, cfg, s));
     return FMM_OK;
   }
   uint64_t key = fnv1a(&e->id, sizeof e->id);
@@ -771,8 +782,6 @@ static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* 
   key = fnv1a(&L, sizeof L, key);
   key = fnv1a(&prec, sizeof prec, key);
   key = fnv1a(&cfg, sizeof cfg, key);
-  key = fnv1a(&pos, sizeof pos, key);
-  key = fnv1a(&mass, sizeof mass, key);
   auto it = ctx->graphs.find(key);
   if (it == ctx->graphs.end()) {
     if (ctx->graphs.size() >= kMaxGraphs) {
@@ -786,7 +795,7 @@ static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* 
     GraphEntry g;
     g.owner = e->id;
     HIP_TRY(ctx, hipStreamBeginCapture(ctx->internal, hipStreamCaptureModeThreadLocal));
-    hipError_t le = launch_m2l_mfma(ctx->mfma, wl, e->d_desc, M, L, prec, cfg, ctx->internal, pos, mass, Mw);
+    hipError_t le = launch_m2l_mfma(ctx->mfma, wl, e->d_desc, M, L, prec, cfg, ctx->internal);
     hipError_t ce = hipStreamEndCapture(ctx->internal, &g.graph);
     if (le != hipSuccess || ce != hipSuccess) {
       if (g.graph) (void)hipGraphDestroy(g.graph);
@@ -804,56 +813,6 @@ static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* 
   it->second.last_use = ++ctx->clock;
   HIP_TRY(ctx, hipGraphLaunch(it->second.exec, s));
   HIP_TRY(ctx, hipEventRecord(it->second.done, s));
-  return FMM_OK;
-}
-
-// FMM_OPT_ROUND_SPLIT: the (sub-grid, round) list of the entry for this form,
-// built on first use, then the two launches
-static fmm_status run_split(fmm_ctx* ctx, DescEntry* e, const double* M, double* L, fmm_precision prec,
-                            int cfg, hipStream_t s) {
-  const int f = prec == FMM_FP64_HARMONIC ? 1 : 0;
-  const int64_t nsub = (int64_t)e->host.size();
-  if (!e->split_dev[f]) {
-    std::vector<WorkItem> items;
-    std::vector<int> base((size_t)nsub);
-    for (int64_t b = 0; b < nsub; ++b) {
-      base[(size_t)b] = (int)items.size();
-      for (int r = 0; r < m2l_rounds(e->host[(size_t)b].p, f == 1); ++r) items.push_back(WorkItem{(int32_t)b, r});
-    }
-    const size_t off_base = align_up(sizeof(WorkItem) * items.size(), 256);
-    const size_t off_counter = align_up(off_base + sizeof(int) * base.size(), 256);
-    const size_t off_part = align_up(off_counter + 256, 256);
-    const size_t bytes = off_part + sizeof(double) * items.size() * 35 * kNTarget;
-    // the list goes through pinned host memory, copied on the caller's stream
-    // (both allocations are held with the descriptor set)
-    void* dev = nullptr;
-    void* pin = nullptr;
-    HIP_TRY(ctx, hipMalloc(&dev, bytes));
-    hipError_t ae = hipHostMalloc(&pin, off_counter, hipHostMallocDefault);
-    if (ae != hipSuccess) {
-      (void)hipFree(dev);
-      return hip_err(ctx, ae, "hipHostMalloc (round split list)");
-    }
-    char* hp = static_cast<char*>(pin);
-    std::memcpy(hp, items.data(), sizeof(WorkItem) * items.size());
-    std::memcpy(hp + off_base, base.data(), sizeof(int) * base.size());
-    char* dp = static_cast<char*>(dev);
-    hipError_t ce = hipMemcpyAsync(dp, hp, off_counter, hipMemcpyHostToDevice, s);
-    if (ce != hipSuccess) {
-      (void)hipFree(dev);
-      (void)hipHostFree(pin);
-      return hip_err(ctx, ce, "hipMemcpyAsync (round split list)");
-    }
-    e->split_dev[f] = dev;
-    e->split_pinned[f] = pin;
-    e->split[f].items = reinterpret_cast<const WorkItem*>(dp);
-    e->split[f].count = (int)items.size();
-    e->split[f].counter = reinterpret_cast<unsigned*>(dp + off_counter);
-    e->split_base[f] = reinterpret_cast<int*>(dp + off_base);
-    e->split_part[f] = reinterpret_cast<double*>(dp + off_part);
-  }
-  HIP_TRY(ctx, launch_m2l_round_split(ctx->mfma, e->split[f], e->d_desc, nsub, e->split_base[f], M, L,
-                                      e->split_part[f], prec, cfg, s));
   return FMM_OK;
 }
 
@@ -880,15 +839,27 @@ static fmm_status run_slice(fmm_ctx* ctx, DescEntry* e, const double* M, double*
   return FMM_OK;
 }
 
-// The M2L of one call: reference kernel, exact slices, round split or the
-// persistent matrix-core kernel.
+// FMM_OPT_ROUND_SPLIT: whole sub-grids, parts of them (small batches), or as planned
+static bool takes_parts(const fmm_ctx* ctx, int64_t nsub, const StreamPlan& plan) {
+  if (ctx->round_split == 0) return false;
+  return plan.parts || (ctx->round_split == 1 && nsub <= kMaxSplitSubgrids);
+}
+
+static const WorkList& stream_list(const fmm_ctx* ctx, const DescEntry* e, bool harmonic) {
+  return takes_parts(ctx, (int64_t)e->host.size(), e->plan[harmonic]) ? e->parts[harmonic] : e->whole[harmonic];
+}
+
+// The M2L of one call: reference kernel, exact slices, the streamed forward, or
+// another matrix-core kernel over whole sub-grids.
 static fmm_status run_m2l(fmm_ctx* ctx, DescEntry* e, const double* M, double* L, fmm_precision prec,
                           int cfg, hipStream_t s) {
   if (ctx->m2l_kernel == 1) return run_ref(ctx, e, false, M, L, s);
   if (prec == FMM_EXACT_SLICE) return run_slice(ctx, e, M, L, s);
-  const bool split = ctx->round_split > 0 || (ctx->round_split < 0 && e->split_tuned[prec]);
-  if (split && (int64_t)e->host.size() <= kMaxSplitSubgrids && mfma_config_fusable(cfg))
-    return run_split(ctx, e, M, L, prec, cfg, s);
+  if (mfma_config_streams(cfg)) {
+    const bool harm = prec == FMM_FP64_HARMONIC;
+    HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s));
+    return FMM_OK;
+  }
   return run_mfma(ctx, e, M, L, prec, cfg, s);
 }
 
@@ -944,16 +915,26 @@ fmm_status fmm_m2l_noalloc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, 
   HIP_TRY(ctx, hipEventSynchronize(ctx->noalloc_uploaded));
   unsigned char* hp = ctx->noalloc_host;
   std::memcpy(hp, desc, sizeof(fmm_subgrid) * (size_t)nsub);
-  fill_work_list(desc, nsub, prec == FMM_FP64_HARMONIC, reinterpret_cast<WorkItem*>(hp + kNoAllocWorkOff));
-  const size_t used = kNoAllocWorkOff + sizeof(WorkItem) * (size_t)nsub;
+  WorkItem* items = reinterpret_cast<WorkItem*>(hp + kNoAllocWorkOff);
+  const bool harm = prec == FMM_FP64_HARMONIC;
+  const int cfg = pick_config(ctx, nullptr, prec);
+  const bool streams = mfma_config_streams(cfg);
+  int64_t count = nsub;
+  WorkList wl;
+  sort_by_cost(desc, nsub, harm, items);
+  wl.parts = streams && takes_parts(ctx, nsub, plan_stream(items, nsub, ctx->mfma.num_cu));
+  if (wl.parts) count = split_items(items, nsub, ctx->mfma.num_cu);
+  else whole_items(items, nsub);
+  const size_t used = kNoAllocWorkOff + sizeof(WorkItem) * (size_t)count;
   HIP_TRY(ctx, hipMemcpyAsync(ctx->noalloc_dev, hp, used, hipMemcpyHostToDevice, s));
   HIP_TRY(ctx, hipEventRecord(ctx->noalloc_uploaded, s));
-  WorkList wl;
   wl.items = reinterpret_cast<const WorkItem*>(ctx->noalloc_dev + kNoAllocWorkOff);
-  wl.count = (int)nsub;
-  wl.counter = reinterpret_cast<unsigned*>(ctx->noalloc_dev + kNoAllocCounterOff);   // reset by the launch
-  HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, reinterpret_cast<const DevDesc*>(ctx->noalloc_dev), M, L, prec,
-                               pick_config(ctx, nullptr, prec), s));
+  wl.count = (int)count;
+  // (the streamed forward's counter is zero between its calls, the other is reset by the launch)
+  wl.counter = reinterpret_cast<unsigned*>(ctx->noalloc_dev + kNoAllocCounterOff) + (streams ? 0 : 1);
+  const DevDesc* d_desc = reinterpret_cast<const DevDesc*>(ctx->noalloc_dev);
+  if (streams) HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, wl, d_desc, M, L, harm, s));
+  else HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, d_desc, M, L, prec, cfg, s));
   return FMM_OK;
 }
 
@@ -981,11 +962,11 @@ fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, cons
   CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
   const int cfg = pick_config(ctx, e, prec);
   const bool aligned = ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(mass)) & 15u) == 0;
-  // one launch pays off once workgroups take several sub-grids (with at most one
-  // each, every moment phase runs at the start, on one workgroup per sub-grid)
-  if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && mfma_config_fusable(cfg) &&
-      nsub > ctx->mfma.num_cu) {
-    CHECK_OK(run_mfma(ctx, e, M, L, prec, cfg, s, pos, mass, M));
+  // (moments in the M2L's launch where the plan expects that to be faster)
+  const bool harm = prec == FMM_FP64_HARMONIC;
+  if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && mfma_config_streams(cfg) &&
+      e->plan[harm].fuse) {
+    HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, e->whole[harm], e->d_desc, M, L, harm, s, pos, mass, M));
   } else {
     HIP_TRY(ctx, launch_p2m(e->d_desc, nsub, e->d_ids, e->count, pos, mass, ppc, M, e->part_even, true, s));
     CHECK_OK(run_m2l(ctx, e, M, L, prec, cfg, s));
@@ -1090,13 +1071,18 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
   int best = -1;
   float best_ms = 0.f;
   for (int cfg = 0; cfg < mfma_num_configs(); ++cfg) {
-    if (!mfma_config_supports(cfg, prec)) continue;
-    // one warm-up launch, then the best of three
-    HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, work_for(e, prec == FMM_FP64_HARMONIC), e->d_desc, M, L, prec, cfg, s));
+    if (!mfma_config_supports(cfg, prec) || !mfma_config_distinct(cfg)) continue;
+    // one warm-up launch, then the best of three, as fmm_m2l runs the configuration
+    auto launch = [&]() {
+      const bool harm = prec == FMM_FP64_HARMONIC;
+      return mfma_config_streams(cfg) ? launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s)
+                                      : launch_m2l_mfma(ctx->mfma, work_for(e, harm), e->d_desc, M, L, prec, cfg, s);
+    };
+    HIP_TRY(ctx, launch());
     float cfg_ms = 1e30f;
     for (int r = 0; r < 3; ++r) {
       HIP_TRY(ctx, hipEventRecord(t0, s));
-      HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, work_for(e, prec == FMM_FP64_HARMONIC), e->d_desc, M, L, prec, cfg, s));
+      HIP_TRY(ctx, launch());
       HIP_TRY(ctx, hipEventRecord(t1, s));
       HIP_TRY(ctx, hipEventSynchronize(t1));
       float ms = 0.f;
@@ -1107,22 +1093,6 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
       best = cfg;
       best_ms = cfg_ms;
     }
-  }
-  // small batches: the round split with the chosen configuration, timed the same way
-  e->split_tuned[prec] = false;
-  if (nsub <= kMaxSplitSubgrids && mfma_config_fusable(best) && ctx->m2l_kernel != 1) {
-    CHECK_OK(run_split(ctx, e, M, L, prec, best, s));
-    float split_ms = 1e30f;
-    for (int r = 0; r < 3; ++r) {
-      HIP_TRY(ctx, hipEventRecord(t0, s));
-      CHECK_OK(run_split(ctx, e, M, L, prec, best, s));
-      HIP_TRY(ctx, hipEventRecord(t1, s));
-      HIP_TRY(ctx, hipEventSynchronize(t1));
-      float ms = 0.f;
-      HIP_TRY(ctx, hipEventElapsedTime(&ms, t0, t1));
-      split_ms = std::min(split_ms, ms);
-    }
-    e->split_tuned[prec] = split_ms < best_ms;
   }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);

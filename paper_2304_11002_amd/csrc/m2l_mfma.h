@@ -7,27 +7,45 @@
 
 namespace fmm {
 
-// One work item: a sub-grid (forward and adjoint kernels both own whole
-// sub-grids, so every output element has exactly one writer).
+// One work item: a sub-grid, or (forward) a part of its targets. Every output
+// element has exactly one writer.
 struct WorkItem {
   int32_t sub;    // descriptor index
-  int32_t cost;   // relative cost used for the longest-first order
+  int32_t part;   // level | index << 4: part `index` of the kLevelParts[level] the sub-grid is cut into
 };
 
 struct WorkList {
   const WorkItem* items = nullptr;   // device, longest first
   int count = 0;
-  unsigned* counter = nullptr;       // device work counter, reset by every launch
-  int64_t cost = 0;
+  unsigned* counter = nullptr;       // device work counter, reset by every launch that uses it
+  bool parts = false;                // the items are parts of sub-grids (streamed forward)
 };
 
-// Host: items for the descriptors, longest first. The cost of an item is its
-// products: C^2 x present pairs for the dense form, (p+1)^4 x present pairs for
-// the harmonic form (harmonic = true), whose p = 4 : p = 3 ratio is 2.44, not 3.06.
-std::vector<WorkItem> build_work_list(const fmm_subgrid* desc, int64_t nsub, bool harmonic = false);
-// The same list written into out[0 .. nsub) and ordered in place (no allocation):
-// longest first, equal costs by descriptor index.
-void fill_work_list(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkItem* out);
+// Host: the sub-grids in out[0 .. nsub), longest first (equal costs by
+// descriptor index), each item's cost in `part`. The cost is its products:
+// C^2 x present pairs for the dense form, (p+1)^4 x present pairs for the
+// harmonic form, whose p = 4 : p = 3 ratio is 2.44, not 3.06.
+void sort_by_cost(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkItem* out);
+// Sorted items (costs in `part`) as whole sub-grids, in place.
+void whole_items(WorkItem* items, int64_t n);
+// How the streamed forward runs sorted items (costs in `part`): as parts or as
+// whole sub-grids, and whether a step computes the moments in the M2L's launch
+// (whole sub-grids) rather than in one of their own.
+struct StreamPlan {
+  bool parts = false, fuse = false;
+};
+StreamPlan plan_stream(const WorkItem* items, int64_t n, int num_cu);
+// Sorted items cut into parts, in place (room for max_parts(n)); returns their
+// number. A sub-grid goes in 4 parts, and in 8 or 32 while a part costs more
+// than the work left from it on, per workgroup slot: a batch that cannot fill
+// the GPU is spread over it, and a large one ends on small parts instead of a
+// last wave that most compute units sit out.
+constexpr int kMaxPartLevel = 2;
+constexpr int kLevelParts[kMaxPartLevel + 1] = {4, 8, 32};
+constexpr int64_t kMaxExtraItems = 8192;
+constexpr int64_t kMaxSplitSubgrids = 256;   // batches that FMM_OPT_ROUND_SPLIT = 1 applies to
+constexpr int64_t max_parts(int64_t n) { return n * kLevelParts[0] + kMaxExtraItems; }
+int64_t split_items(WorkItem* items, int64_t n, int num_cu);
 
 constexpr int kQuads = kNStencil / 4;   // offsets are consumed four at a time
 static_assert(kNStencil % 4 == 0, "offset quads");
@@ -36,6 +54,7 @@ static_assert(kNStencil % 4 == 0, "offset quads");
 // are staged two per round; each is a combination of at most kHMaxSup moment
 // components of its own order, with integer coefficients.
 constexpr int kHMaxSup = 6;
+constexpr int harmonic_sup(int p) { return p == 4 ? 5 : 3; }   // per order (checked when the plan is built)
 struct HRound {
   int32_t nsup;            // moment components read in this round
   int32_t ord0, ord1;      // orders of the two folded components (ord1 < 0: only one)
@@ -88,6 +107,11 @@ struct MfmaTables {
   const int* stencil = nullptr;   // [892][3] offsets (owned by the context)
   int* lds_off = nullptr;     // [892] dx + 20 dy + 400 dz
   uint32_t* touch = nullptr;  // [8][quads] blocks touched by an 8x8 target plane per quad
+  // streamed forward: [32][quads] blocks touched by a 16-cell target tile per quad, the rows
+  // of its windows and the quads' LDS offsets in them
+  uint32_t* ttouch = nullptr;
+  int* rowtab = nullptr;
+  short4* woff = nullptr;
   // harmonic form, per order p: tables [rounds][quad][n'-group][kk*4 + j][folded comp of pair]
   // (T_d restricted to kz <= 1 rows and columns), the rounds' fold plans and the
   // expansion of L
@@ -149,28 +173,23 @@ int mfma_num_configs();
 bool mfma_config_supports(int cfg, fmm_precision prec);
 int mfma_default_config(fmm_precision prec);
 
-// pos, mass, Mw (all or none; Mw == M): the fused form, for configurations
-// where mfma_config_fusable(cfg). The kernel first computes each sub-grid's
-// moments (frame rows holding the reachable window, 8 particles per cell,
-// 16-byte aligned particle blocks) into M through Mw, as launch_p2m with
-// window = true writes them, and then its M2L.
-bool mfma_config_fusable(int cfg);
+// the streamed forward, which takes parts of sub-grids and can compute moments (FMM_FP64, FMM_FP64_HARMONIC)
+bool mfma_config_streams(int cfg);
+// false: the same kernel as another configuration
+bool mfma_config_distinct(int cfg);
+// The other FMM_FP64 and the split-precision configurations, over whole sub-grids.
 hipError_t launch_m2l_mfma(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc,
-                           const double* M, double* L, fmm_precision prec, int cfg,
-                           hipStream_t s, const double* pos = nullptr,
-                           const double* mass = nullptr, double* Mw = nullptr);
-// Round split (small batches): w lists (sub-grid, round) pairs, sub-grid-major,
-// WorkItem::cost holding the round; d_base[b] is the slot (list index) of
-// sub-grid b's first round; part holds kMaxSplitSlots slots of 35 x 512
-// doubles. The rounds' raw sums go to their slots, then each sub-grid's are
-// added in round order into L. Configurations with LDS-staged tables only.
-constexpr int kMaxSplitSubgrids = 256;
-constexpr int kMaxSplitSlots = kMaxSplitSubgrids * 18;   // 18 rounds: dense p = 4
-constexpr size_t kSplitPartBytes = (size_t)kMaxSplitSlots * 35 * 512 * sizeof(double);
-int m2l_rounds(int p, bool harmonic);
-hipError_t launch_m2l_round_split(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc,
-                                  int64_t nsub, const int* d_base, const double* M, double* L,
-                                  double* part, fmm_precision prec, int cfg, hipStream_t s);
+                           const double* M, double* L, fmm_precision prec, int cfg, hipStream_t s);
+// The streamed forward, dense or harmonic form, over a list of parts
+// (split_items). Its counter must be zero, and the kernel leaves it so.
+// pos, mass, Mw (all or none; Mw == M): the fused form over a list of whole
+// sub-grids. The kernel first computes each sub-grid's moments (frame rows
+// holding the reachable window, 8 particles per cell, 16-byte aligned particle
+// blocks) into M through Mw, as launch_p2m with window = true writes them, and
+// then its M2L.
+hipError_t launch_m2l_stream(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc, const double* M,
+                             double* L, bool harmonic, hipStream_t s, const double* pos = nullptr,
+                             const double* mass = nullptr, double* Mw = nullptr);
 // harmonic: the harmonic form of the adjoint (equal to the dense one up to rounding)
 // pos, dmass (both or neither): the kernel also computes the mass gradients of
 // each sub-grid's dM (as launch_p2m_backward, 8 particles per cell, 16-byte

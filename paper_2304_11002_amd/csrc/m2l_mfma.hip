@@ -36,8 +36,44 @@ namespace {
 
 constexpr int kWinCells = kWin * kWin * kWin;   // 8000
 
+// Rows of the forward's compact window (see the streamed forward below): plane w
+// of the window of nz target planes holds the rows within window_reach of the block.
+__host__ __device__ constexpr int shell_reach(int dz) {
+  int r = 0;
+  while ((r + 1) * (r + 1) + dz * dz <= 36) ++r;
+  return r;
+}
+__host__ __device__ constexpr int window_reach(int nz, int w) {
+  int r = 0;
+  for (int t = 0; t < nz; ++t) {
+    const int dz = w - 6 - t;
+    if (dz >= -6 && dz <= 6 && shell_reach(dz) > r) r = shell_reach(dz);
+  }
+  return r;
+}
+// rows of a window whose targets span `span` rows per plane (8, or 4 for one tile)
+__host__ __device__ constexpr int window_rows(int nz, int span) {
+  int n = 0;
+  for (int w = 0; w < nz + 12; ++w) n += span + 2 * window_reach(nz, w);
+  return n;
+}
+constexpr int kWinRows8 = window_rows(8, 8), kWinRows2 = window_rows(2, 8), kWinRows1 = window_rows(1, 8),
+              kWinRowsTile = window_rows(1, 4);
+static_assert(kWinRows8 == 344 && kWinRows2 == 224 && kWinRows1 == 204 && kWinRowsTile == 152, "window rows");
+// LDS cell of window coordinate (0, 0) of plane w: the plane's first stored row is 6 - reach
+__host__ __device__ constexpr int window_base(int nz, int w) {
+  int n = 0;
+  for (int v = 0; v < w; ++v) n += 8 + 2 * window_reach(nz, v);
+  return kWin * (n - 6 + window_reach(nz, w));
+}
+
 __device__ __forceinline__ double mfma4(double a, double b, double c) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4d mfma16(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 __global__ void reset_counter_kernel(unsigned* counter) { *counter = 0u; }
@@ -219,55 +255,185 @@ __global__ void __launch_bounds__(WAVES * 64) m2l_fwd_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// forward, table operands staged in LDS
+// forward, table operands streamed from L2
 // ---------------------------------------------------------------------------
 //
-// Same products and order as fwd_subgrid. Instead of every wave loading its
-// table operands from L2 (16 distinct values per 64-lane load, replicated over
-// the four MFMA blocks, which keeps the texture-address path ~70% busy), the
-// workgroup copies the tables of a chunk of offset quads into the LDS left over
-// by the window (double-buffered, one barrier per chunk) and each wave reads
-// them with broadcast ds_read_b128 (both components of a column group at once).
-// Table layout for this form: [round][quad][group][kk*4 + j][component].
+// A workgroup takes a whole sub-grid's targets or a part of them, with the window
+// of two components (a round) that they reach in LDS. Each target's sums run over
+// the rounds, quads and components in one order whatever the part, so the results
+// are the same bits.
+//
+//   level   targets   of one sub-grid   threads   a wave's share
+//   kWhole  8 planes         1            512     4 tiles, all columns
+//     0     2 planes         4            256     2 tiles, all columns
+//     1     1 plane          8            256     1 tile, all columns
+//     2     1 tile          32            256     1 tile, every fourth group of 4 columns
+//
+// Parts spread a few sub-grids over the GPU (one sub-grid's M2L 920 -> 80 us, 43
+// mixed ones 2590 -> 575) and even out the end of a middling batch (300 sub-grids
+// 2000 -> 1230 us, where whole ones take two waves); two workgroups share a
+// compute unit, but their staging still costs (a window of 14 planes for 2 target
+// planes, and one workgroup's loads in flight hold up the other's table
+// operands), so large batches go in whole sub-grids (4096 at p = 3, harmonic:
+// 14.26 ms, 67 TFLOP/s executed, in parts 14.5, and 15.2 with the four-block
+// instruction and tables staged through LDS). plan_stream and split_items choose.
+//
+// Columns. Sixteen output columns at a time go through v_mfma_f64_16x16x4
+// ([16 cells x 4 offsets] x [4 offsets x 16 columns]), which sums the offsets in
+// the order the four-block instruction does (both are chains of fused
+// multiply-adds over k, so their results are the same bits), takes the same A
+// operand, needs a quarter of the B operand reads (no value is replicated over
+// blocks) and runs at full rate without independent accumulators: 69 and 77
+// TFLOP/s with one accumulator and one or two waves per SIMD, where the
+// four-block one reaches 28 and 56. Columns past the last sixteen go four at a
+// time through the four-block instruction, so nothing more is padded than there.
+//   D of 16x16x4: lane l, element v -> cell 4 v + l/16 of the tile, column l%16
+// At level 2, which has waves to spare, the shorter latency of the four-block
+// instruction (18 ns against 30) counts.
+//
+// Operands. A wave reads its tiles' window cells AD quads ahead of their
+// products. Table operands come from L2 straight into registers, U quads ahead,
+// so the quad loop has no barrier and no wave waits for another one.
+//
+// Window. At distance dz of a target plane only the cells within
+// reach(dz) = floor(sqrt(36 - dz^2)) of the block in x and y are used, so the
+// window of a part holds, per plane, the rows within that reach in y (all 20
+// cells of each): 224 rows for two target planes (71,680 bytes, two of which fit
+// a compute unit) and 204 for one, instead of 280 and 260. A whole sub-grid's
+// keeps full planes, with 344 of their 400 rows staged.
+//
+// Tried: the next round's window loaded into registers during the products, or
+// its cache lines touched: both slower, as vector loads return in order and the
+// table operands behind them wait for the window's latency. Operand sets 2 and 3
+// quads ahead at level 0, and table operands 4 or 16 quads ahead: within 2%.
+constexpr int kPartThreads = 256;
+constexpr int kWholeThreads = 512;
 
-constexpr int kBlChunkMax = 12 * 5 * 32;             // doubles per chunk buffer
-// HARM: the harmonic form, (p+1)^2 folded components instead of C
-// QDIV: chunks of 1/QDIV of the default length (an autotuner candidate)
-template <int P, bool HARM = false, int QDIV = 1>
-struct BlShape {
+template <int P, bool HARM>
+struct FwdCols {
   static constexpr int CR = HARM ? (P + 1) * (P + 1) : ncomp(P);   // reduced components
-  static constexpr int NG = (CR + 3) / 4;
-  // quads per staged chunk (even: a full chunk ends on the second operand set)
-  static constexpr int QC0 = HARM ? (kBlChunkMax / (NG * 32)) & ~1 : (P == 4 ? 6 : 12);
-  static constexpr int QC = (QC0 / QDIV) & ~1;
-  static constexpr int CHUNK = QC * NG * 32;         // doubles per chunk buffer
-  static_assert(QC >= 2, "chunk length");
+  static constexpr int NG = (CR + 3) / 4;                          // columns in groups of four
+  static constexpr int N16 = CR / 16, N4 = NG - 4 * N16;
 };
-static_assert(BlShape<2>::CHUNK <= kBlChunkMax && BlShape<3>::CHUNK <= kBlChunkMax &&
-              BlShape<4>::CHUNK <= kBlChunkMax && BlShape<2, true>::CHUNK <= kBlChunkMax &&
-              BlShape<3, true>::CHUNK <= kBlChunkMax && BlShape<4, true>::CHUNK <= kBlChunkMax,
-              "chunk buffer");
-constexpr int kBlThreads = 512;
+constexpr int kWhole = -1;   // the level of a whole sub-grid
+template <int LEVEL>
+struct PartShape {
+  static constexpr int NT = LEVEL == kWhole ? kWholeThreads : kPartThreads, WAVES = NT / 64;
+  static constexpr int NZ = LEVEL == kWhole ? 8 : LEVEL == 0 ? 2 : 1;   // target planes of the window
+  static constexpr int TPW = LEVEL == kWhole ? 4 : LEVEL == 0 ? 2 : 1;  // tiles per wave
+  static constexpr int CS = LEVEL == 2 ? WAVES : 1;         // waves sharing a tile's columns
+  static constexpr int TILES = LEVEL == 2 ? 1 : 4 * NZ;
+  // LDS rows of the window, and the rows staged
+  static constexpr int ROWS = NZ == 8 ? kWin * kWin : NZ == 2 ? kWinRows2 : kWinRows1;
+  static constexpr int STAGED = LEVEL == kWhole ? kWinRows8 : LEVEL == 2 ? kWinRowsTile : ROWS;
+  static constexpr int FIRST = LEVEL == kWhole ? kWinRows2 + kWinRows1 + 2 * kWinRowsTile   // in the row table
+                               : LEVEL == 0 ? 0 : LEVEL == 1 ? kWinRows2 : kWinRows2 + kWinRows1;
+  static constexpr int AD = LEVEL <= 0 ? 1 : 3;
+};
+// A wave's columns: N16 sixteens, then N4 groups of four, every S4-th.
+template <int N16_, int N4_, int S4_>
+struct Cols {
+  static constexpr int N16 = N16_, N4 = N4_, S4 = S4_;
+};
+constexpr int kOffPad = 20;   // s_off entries past the last quad: offsets are read ahead
+// room past the tables for the quads read ahead in the last round (at most 16 of
+// 9 column groups; never multiplied)
+constexpr size_t kTablePad = 16 * 9 * 32;
 
-// PIPE: the inner loop reads only LDS (offsets staged once per workgroup, skip
-// decisions as per-wave bitmasks), so the next quad's operand reads can be issued
-// before this quad's products and waited for with partial counters.
-// FULL: every neighbour block is present, so no quad is skipped and the quad
-// loop carries no skip branches.
-// HARM: the harmonic form. Each round stages two folded moment components
-// (combinations of moment components of one order, per the round's plan), the
-// products run over the (p+1)^2 harmonic columns, and L is expanded to all C
-// components at the end through LDS.
-// Hook: at the top of round r, when the window buffer and the table buffers are
-// free (every wave is past the previous round's last barrier), hook.run() is
-// called if hook.wants(r, ROUNDS) (uniform over the workgroup); it may use
-// those buffers and must leave no LDS access in flight. Around it the sums so
-// far are parked in the sub-grid's own L slots (written only at the end), so
-// run() has the registers.
-struct NoHook {
+// The cells of a part's window that one thread stages, fixed over the rounds:
+// frame cell | LDS cell << 16. An absent cell loads the (always present) centre
+// cell and stores zero. rowtab: the window's rows, y | plane << 8 | LDS row << 16.
+template <int COUNT, int NT>
+struct WindowCells {
+  int at[COUNT];
+  uint32_t on;
+  __device__ __forceinline__ void set(const DevDesc& d, const int* __restrict__ rowtab, int rows, int z0) {
+    constexpr int kCentre = kBlock * (1 + kFrame + kFrame * kFrame);
+    on = 0;
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) {
+      const int c = (int)threadIdx.x + i * NT;
+      const int x = c % kWin, v = rowtab[min(c / kWin, rows - 1)];
+      const int jx = x + kWin0, jy = (v & 255) + kWin0, jz = ((v >> 8) & 255) + kWin0 + z0;
+      const bool in = block_present(d.mask, jx, jy, jz);
+      at[i] = (in ? jx + kFrame * jy + kFrame * kFrame * jz : kCentre) | ((v >> 16) * kWin + x) << 16;
+      on |= (uint32_t)in << i;
+    }
+  }
+  __device__ __forceinline__ int cell(int i) const { return at[i] & 0xffff; }
+  __device__ __forceinline__ int lds(int i) const { return at[i] >> 16; }
+};
+static_assert(kWin * kWin * kWin < 1 << 15 && kNCell < 1 << 16, "packed cells");
+
+// Round r's two components of the part's window cells, scaled, into LDS; in the
+// harmonic form each of the two is a combination of the round's moment
+// components. All loads of a pass are in flight together. Barriers: one before
+// the first store; the caller's follows.
+template <int P, bool HARM, int ROWS, int COUNT, int NT>
+__device__ __forceinline__ void stage_window(const WindowCells<COUNT, NT>& wc, int l2, const double* __restrict__ src,
+                                             const HRound* __restrict__ hround, int r, double2* win) {
+  constexpr int C = ncomp(P);
+  constexpr int SUP = HARM ? harmonic_sup(P) : 2;        // components read per round, at most
+  constexpr int kPasses = SUP * COUNT > 60 ? 2 : 1;      // (registers)
+  constexpr int kPer = (COUNT + kPasses - 1) / kPasses;
+#pragma unroll
+  for (int pass = 0; pass < kPasses; ++pass) {
+    double x[SUP][kPer];
+    double2 v[kPer];
+    double s0, s1;
+#pragma unroll
+    for (int u = 0; u < SUP; ++u) {
+      int comp;
+      if constexpr (HARM) comp = hround[r].comp[min(u, hround[r].nsup - 1)];
+      else comp = min(2 * r + u, C - 1);
+      const double* su = src + (size_t)comp * kNCell;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i)
+        if (pass * kPer + i < COUNT) x[u][i] = su[wc.cell(pass * kPer + i)];
+    }
+    if constexpr (HARM) {
+      const HRound& rd = hround[r];
+      s0 = ldexp(1.0, l2 * rd.ord0);
+      s1 = rd.ord1 >= 0 ? ldexp(1.0, l2 * rd.ord1) : 0.0;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) v[i] = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int u = 0; u < SUP; ++u) {
+        if (u < rd.nsup) {
+          const double f0 = rd.c0[u], f1 = rd.c1[u];
+#pragma unroll
+          for (int i = 0; i < kPer; ++i) {
+            if (pass * kPer + i >= COUNT) continue;
+            v[i].x = __builtin_fma(f0, x[u][i], v[i].x);
+            v[i].y = __builtin_fma(f1, x[u][i], v[i].y);
+          }
+        }
+      }
+    } else {
+      s0 = ldexp(1.0, l2 * order_of(2 * r));
+      s1 = 2 * r + 1 < C ? ldexp(1.0, l2 * order_of(2 * r + 1)) : 0.0;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i)
+        if (pass * kPer + i < COUNT) v[i] = make_double2(x[0][i], x[1][i]);
+    }
+    if (pass == 0) __syncthreads();   // the previous round's window reads are done
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int k = pass * kPer + i;
+      if (k < COUNT && (int)threadIdx.x + k * NT < ROWS * kWin)
+        win[wc.lds(k)] = (wc.on >> k) & 1u ? make_double2(v[i].x * s0, v[i].y * s1) : make_double2(0.0, 0.0);
+    }
+  }
+}
+
+// Hook (whole sub-grids): at the top of round r, hook.run() is called if
+// hook.wants(r, ROUNDS) (uniform over the workgroup); it starts with a barrier,
+// may use the window buffer and must leave no LDS access in flight. Around it
+// the sums so far are parked in the sub-grid's own L slots (written only at the
+// end), so run() has the registers.
+struct NoMoments {
   __device__ bool wants(int, int) const { return false; }
   __device__ void run() const {}
-  __device__ void run(double*) const {}
 };
 // the moments of the next item, at the top of round (workgroup index mod rounds)
 template <class F>
@@ -280,364 +446,295 @@ struct MomentHook {
   __device__ void run() const { moments(next); }
 };
 
-// Rounds of one call: all of them, with L written; or one round, with the raw
-// sums of its products (unscaled, before any expansion) written to `part`
-// [column][target] for a later sum over rounds.
-struct AllRounds {
-  static constexpr bool kPartial = false;
-  __device__ int begin() const { return 0; }
-  __device__ int end(int rounds) const { return rounds; }
-  __device__ double* partial() const { return nullptr; }
-};
-struct OneRound {
-  static constexpr bool kPartial = true;
-  int r;
-  double* part;
-  __device__ int begin() const { return r; }
-  __device__ int end(int) const { return r + 1; }
-  __device__ double* partial() const { return part; }
-};
-
-template <int P, bool PIPE, bool FULL = false, bool HARM = false, class Hook = NoHook, class Range = AllRounds,
-          int QDIV = 1>
-__device__ __forceinline__ void fwd_bl_subgrid(const DevDesc& d, const double* __restrict__ M,
-                                               double* __restrict__ L,
-                                               const double* __restrict__ Bl,
-                                               const int* __restrict__ lds_off,
-                                               const uint32_t* __restrict__ touch, double2* smem,
-                                               double* sB, const int4* s_off,
-                                               const HRound* __restrict__ hround = nullptr,
-                                               const HExp* __restrict__ hexp = nullptr,
-                                               Hook hook = Hook(), Range range = Range()) {
-  constexpr int C = ncomp(P);
-  constexpr int CR = BlShape<P, HARM, QDIV>::CR;
-  constexpr int NG = BlShape<P, HARM, QDIV>::NG;
-  constexpr int QC = BlShape<P, HARM, QDIV>::QC;
-  constexpr int CH2 = BlShape<P, HARM, QDIV>::CHUNK / 2;    // double2 per chunk
+// FULL: every neighbour block is present, so no quad is skipped.
+// s_off: the quads' LDS offsets; of a part, for either plane of level 0, then for
+// the one plane of the other levels.
+template <int P, bool HARM, bool FULL, int LEVEL, class Hook = NoMoments>
+__device__ __forceinline__ void fwd_part(const DevDesc& d, const double* __restrict__ M, double* __restrict__ L,
+                                         const double* __restrict__ Bl, const uint32_t* __restrict__ ttouch,
+                                         const int* __restrict__ rowtab, double2* win, const short4 (*s_off)[kQuads + kOffPad],
+                                         const HRound* __restrict__ hround, const HExp* __restrict__ hexp, int part,
+                                         Hook hook = Hook()) {
+  using S = PartShape<LEVEL>;
+  using F = FwdCols<P, HARM>;
+  constexpr int C = ncomp(P), CR = F::CR, NG = F::NG;
   constexpr int ROUNDS = (CR + 1) / 2;
-  constexpr int TPW = 4, NT = kBlThreads;
-  constexpr int NCHUNK = (kQuads + QC - 1) / QC;
-  static_assert((CH2 + NT - 1) / NT <= 2, "at most two staged table values per thread");
+  constexpr int TPW = S::TPW, CS = S::CS, AD = S::AD;
+  constexpr int AR = AD == 1 ? 2 : 4;                  // window operand sets
+  // quads of table operands in flight: 64 registers of them in a part, up to 48
+  // beside the tiles of a whole sub-grid, whose quads take longer
+  constexpr int kUnits = CS == 1 ? F::N16 + F::N4 : (NG + CS - 1) / CS;
+  constexpr int U = LEVEL == kWhole ? (kUnits > 3 ? 2 : 4) : kUnits == 1 ? 16 : kUnits == 2 ? 8 : 4;
+  static_assert(U % AR == 0 && U + AD <= kOffPad && U * NG * 32 <= (int)kTablePad, "read ahead");
+  // this wave's columns: all, or groups of four wave, wave + 4, ... (Most of them, or one fewer)
+  using Most = std::conditional_t<CS == 1, Cols<F::N16, F::N4, 1>, Cols<0, (NG + CS - 1) / CS, CS>>;
+  using Less = Cols<0, Most::N4 - (CS > 1), CS>;
+  constexpr int M16 = Most::N16, M4 = Most::N4;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // target plane
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kk = lane >> 4, ci = lane & 15;
+  const int f4 = CS == 1 ? 4 * F::N16 : wave;          // this wave's first group of four
+  // first tile of the wave (4 plane + 2 y + x in the 2 x 2 tiles of a plane)
+  const int tile0 = part * S::TILES + (CS == 1 ? wave * TPW : 0);
+  const int plane = tile0 >> 2, z0 = (part * S::TILES) >> 2;
+  auto tile_x = [&](int t) { return (TPW == 1 ? tile0 & 1 : t & 1) * 4; };
+  const int ty = ((tile0 >> 1) & 1) * 4;
+  auto tile_y = [&](int t) { return TPW == 4 ? (t >> 1) * 4 : ty; };
   int abase[TPW];
 #pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int x = (t & 1) * 4 + (ci & 3), y = (t >> 1) * 4 + (ci >> 2);
-    abase[t] = (x + 6) + kWin * (y + 6) + kWin * kWin * (wave + 6);
-  }
-  double acc[TPW][NG];
-#pragma unroll
   for (int t = 0; t < TPW; ++t)
+    abase[t] = (tile_x(t) + (ci & 3) + 6) + kWin * (tile_y(t) + (ci >> 2) + 6) +
+               (LEVEL == kWhole ? kWin * kWin * (plane + 6) : 0);
+  v4d acc16[TPW][M16 > 0 ? M16 : 1];
+  double acc4[TPW][M4 > 0 ? M4 : 1];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) acc[t][g] = 0.0;
-
-  const int l2 = d.log2_inv_h;
-  const double* src = M + d.m_off;
-  const int4* off4 = reinterpret_cast<const int4*>(lds_off);
-  const uint32_t* tw = touch + wave * kQuads;
-  double2* sB2 = reinterpret_cast<double2*>(sB);
-  const int boff = kk * 4 + (lane & 3);                // this lane's slot in a column group
-  uint32_t cl0 = 0;                                    // live quads of chunk 0
-  if constexpr (PIPE) {
-    const bool on = lane < QC && (tw[min(lane, QC - 1)] & d.mask) != 0;
-    cl0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(__ballot(on) & 0xffffffffu));
+  for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+    for (int g = 0; g < M16; ++g) acc16[t][g] = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int g = 0; g < M4; ++g) acc4[t][g] = 0.0;
   }
-  for (int r = range.begin(); r < range.end(ROUNDS); ++r) {
-    if (hook.wants(r, ROUNDS)) {
-      double* park = L + d.l_off;
-      const int pxi = lane >> 4, pyi = (lane & 15) >> 2, pj = lane & 3;
+  auto columns = [&](auto f) __attribute__((always_inline)) {
+    if (CS == 1 || wave < NG - (M4 - 1) * CS) f(Most{});
+    else if constexpr (CS > 1 && Less::N4 > 0) f(Less{});
+  };
+  // sum = f(column, target of the sub-grid, sum) over this wave's sums
+  auto each_sum = [&](auto f) __attribute__((always_inline)) {
+    const int xi = lane >> 4, yi = (lane & 15) >> 2, j = lane & 3;
+    columns([&](auto cols) __attribute__((always_inline)) {
+      using K = decltype(cols);
 #pragma unroll
       for (int t = 0; t < TPW; ++t) {
-        const int tcell = ((t & 1) * 4 + pxi) + kBlock * ((t >> 1) * 4 + pyi) + kBlock * kBlock * wave;
+        const int t0 = tile_x(t) + xi + kBlock * tile_y(t) + kBlock * kBlock * plane;
 #pragma unroll
-        for (int g = 0; g < NG; ++g)
-          if (4 * g + pj < CR) park[(size_t)(4 * g + pj) * kNTarget + tcell] = acc[t][g];
+        for (int g = 0; g < K::N16; ++g)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc16[t][g][v] = f(16 * g + ci, t0 + kBlock * v, acc16[t][g][v]);
+#pragma unroll
+        for (int g = 0; g < K::N4; ++g) acc4[t][g] = f(4 * (f4 + g * K::S4) + j, t0 + kBlock * yi, acc4[t][g]);
       }
+    });
+  };
+  const int l2 = d.log2_inv_h;
+  const double* src = M + d.m_off;
+  const short* so = reinterpret_cast<const short*>(s_off[LEVEL == kWhole ? 0 : LEVEL == 0 ? plane - z0 : 2]) + kk;
+  // per tile: the quads with a present source, one bit each; lane 4 t + i holds word i of tile t
+  uint64_t live = 0;
+  if constexpr (!FULL) {
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int q = 64 * i + lane;
+        const uint64_t w = __ballot(q < kQuads && (ttouch[(tile0 + t) * kQuads + min(q, kQuads - 1)] & d.mask) != 0);
+        live = lane == 4 * t + i ? w : live;
+      }
+  }
+  WindowCells<(S::STAGED * kWin + S::NT - 1) / S::NT, S::NT> wc;
+  wc.set(d, rowtab + S::FIRST + (LEVEL == 2 && ty ? kWinRowsTile : 0), S::STAGED, z0);
+  // tables through a buffer resource: a per-quad scalar offset and fixed lane
+  // offsets (quads read ahead in the last round fall in the tables' padding)
+  const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<double*>(Bl), (short)0, ROUNDS * kQuads * NG * 256 + (int)kTablePad * 8, 0x00020000);
+  const int vb16 = ((ci >> 2) * 16 + kk * 4 + (lane & 3)) * 16;      // column ci of a sixteen
+  const int vb4 = (f4 * 16 + kk * 4 + (lane & 3)) * 16;
+  for (int r = 0; r < ROUNDS; ++r) {
+    if (hook.wants(r, ROUNDS)) {
+      double* park = L + d.l_off;
+      each_sum([&](int n, int target, double a) __attribute__((always_inline)) {
+        if (n < CR) park[(size_t)n * kNTarget + target] = a;
+        return a;
+      });
       asm volatile("" ::: "memory");   // the sums are reloaded, not kept in registers
       hook.run();
       asm volatile("" ::: "memory");
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-        const int tcell = ((t & 1) * 4 + pxi) + kBlock * ((t >> 1) * 4 + pyi) + kBlock * kBlock * wave;
-#pragma unroll
-        for (int g = 0; g < NG; ++g)
-          acc[t][g] = 4 * g + pj < CR ? park[(size_t)(4 * g + pj) * kNTarget + tcell] : 0.0;
-      }
+      each_sum([&](int n, int target, double) __attribute__((always_inline)) {
+        return n < CR ? park[(size_t)n * kNTarget + target] : 0.0;
+      });
     }
-    double s0, s1;
-    const double *src0 = nullptr, *src1 = nullptr;
-    if constexpr (HARM) {
-      s0 = ldexp(1.0, l2 * hround[r].ord0);
-      s1 = hround[r].ord1 >= 0 ? ldexp(1.0, l2 * hround[r].ord1) : 0.0;
-    } else {
-      const int k0 = 2 * r, k1 = 2 * r + 1;
-      s0 = ldexp(1.0, l2 * order_of(k0));
-      s1 = k1 < C ? ldexp(1.0, l2 * order_of(k1)) : 0.0;
-      src0 = src + (size_t)k0 * kNCell;
-      src1 = src + (size_t)(k1 < C ? k1 : k0) * kNCell;
-    }
-    // tables of chunk 0 (contiguous in this layout)
-    const double2* gB = reinterpret_cast<const double2*>(Bl + (size_t)r * kQuads * NG * 32);
-    // (clamped indices: every element is loaded, so the staging stays in registers;
-    // slots past the chunk's quads are never read)
-    double2 bst0 = gB[min(tid, CH2 - 1)], bst1 = gB[min(tid + NT, CH2 - 1)];
-    // window: two halves of loads-then-stores keep the staging registers small
-    constexpr int kStage = (kWinCells + NT - 1) / NT;
-    constexpr int kHalf = (kStage + 1) / 2;
-    // with a hook, the staging indices are recomputed each round from an opaque
-    // copy of tid instead of being kept live across the rounds (and the hook)
-    int stid = tid;
-    if constexpr (!std::is_same_v<Hook, NoHook>) asm volatile("" : "+v"(stid));
-#pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      double2 v[kHalf];
-      if constexpr (HARM) {
-        // folded components: sum over the round's moment components, in plan order
-        int cell[kHalf];
-        bool on[kHalf];
-#pragma unroll
-        for (int i = 0; i < kHalf; ++i) {
-          const int c = stid + (hb * kHalf + i) * NT;
-          v[i] = make_double2(0.0, 0.0);
-          const int wx = c % kWin, wy = (c / kWin) % kWin, wz = c / (kWin * kWin);
-          const int jx = wx + kWin0, jy = wy + kWin0, jz = wz + kWin0;
-          cell[i] = jx + kFrame * jy + kFrame * kFrame * jz;
-          on[i] = hb * kHalf + i < kStage && c < kWinCells && block_present(d.mask, jx, jy, jz);
-        }
-        const int nsup = hround[r].nsup;
-        for (int u = 0; u < nsup; ++u) {
-          const double* su = src + (size_t)hround[r].comp[u] * kNCell;
-          const double f0 = hround[r].c0[u], f1 = hround[r].c1[u];
-          double x[kHalf];
-#pragma unroll
-          for (int i = 0; i < kHalf; ++i) x[i] = on[i] ? su[cell[i]] : 0.0;
-#pragma unroll
-          for (int i = 0; i < kHalf; ++i) {
-            v[i].x = __builtin_fma(f0, x[i], v[i].x);
-            v[i].y = __builtin_fma(f1, x[i], v[i].y);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < kHalf; ++i) {
-          const int c = stid + (hb * kHalf + i) * NT;
-          v[i] = make_double2(0.0, 0.0);
-          if (hb * kHalf + i < kStage && c < kWinCells) {
-            const int wx = c % kWin, wy = (c / kWin) % kWin, wz = c / (kWin * kWin);
-            const int jx = wx + kWin0, jy = wy + kWin0, jz = wz + kWin0;
-            const int cell = jx + kFrame * jy + kFrame * kFrame * jz;
-            if (block_present(d.mask, jx, jy, jz)) {
-              v[i].x = src0[cell];
-              v[i].y = src1[cell];
-            }
-          }
-        }
-      }
-      if (hb == 0) __syncthreads();   // previous round's reads of smem and sB are done
-#pragma unroll
-      for (int i = 0; i < kHalf; ++i) {
-        const int c = stid + (hb * kHalf + i) * NT;
-        if (hb * kHalf + i < kStage && c < kWinCells) smem[c] = make_double2(v[i].x * s0, v[i].y * s1);
-      }
-    }
-    sB2[tid] = bst0;
-    if (tid + NT < CH2) sB2[tid + NT] = bst1;
+    stage_window<P, HARM, S::STAGED>(wc, l2, src, hround, r, win);
     __syncthreads();
-    // bit i of cl: quad q0 + i has a present source for this wave's plane (the
-    // next chunk's touch words are loaded with its tables and reduced at its end)
-    uint32_t cl = cl0;
-    [[maybe_unused]] double2 a0[TPW], b0[NG], a1[TPW], b1[NG];   // operand sets (PIPE)
-    [[maybe_unused]] int offn = 0;
-    [[maybe_unused]] const int* so = reinterpret_cast<const int*>(s_off) + kk;
-    static_assert(QC % 2 == 0, "a full chunk ends on the second operand set");
-    for (int ch = 0; ch < NCHUNK; ++ch) {
-      const int q0 = ch * QC;
-      const int nq = min(QC, kQuads - q0);
-      // next chunk's tables: global loads now, LDS stores after this chunk
-      const bool more = ch + 1 < NCHUNK;
-      const int nq2 = more ? min(QC, kQuads - q0 - QC) : 1;
-      uint32_t tn = 0;
-      if (more) {
-        if constexpr (PIPE) tn = tw[q0 + QC + min(lane, nq2 - 1)];
-        const int n2 = nq2 * NG * 16;
-        const double2* gn = gB + (size_t)(q0 + QC) * NG * 16;
-        bst0 = gn[min(tid, n2 - 1)];
-        bst1 = gn[min(tid + NT, n2 - 1)];
+    columns([&](auto cols) __attribute__((always_inline)) {
+      using K = decltype(cols);
+      constexpr int KN16 = K::N16 > 0 ? K::N16 : 1, KN4 = K::N4 > 0 ? K::N4 : 1;
+      int sq = r * kQuads * NG * 256;                  // table offset of the quad group
+      const short* sp = so;                            // and its LDS offsets
+      double2 b16[U][KN16], b4[U][KN4], a[AR][TPW];
+      int o[U];
+#define PT_LOADB(SET, Q)                                                                           \
+  {                                                                                                \
+    _Pragma("unroll") for (int g = 0; g < K::N16; ++g) b16[SET][g] = __builtin_bit_cast(double2,   \
+        __builtin_amdgcn_raw_buffer_load_b128(brs, vb16 + 4 * g * 256, sq + (Q) * NG * 256, 0));   \
+    _Pragma("unroll") for (int g = 0; g < K::N4; ++g) b4[SET][g] = __builtin_bit_cast(double2,     \
+        __builtin_amdgcn_raw_buffer_load_b128(brs, vb4 + g * K::S4 * 256, sq + (Q) * NG * 256, 0)); \
+  }
+#define PT_LOADA(SET, OSET) \
+  _Pragma("unroll") for (int t = 0; t < TPW; ++t) a[SET][t] = win[abase[t] + o[OSET]];
+#define PT_MMA1(u, t, X)                                                                           \
+  {                                                                                                \
+    _Pragma("unroll") for (int g = 0; g < K::N16; ++g) acc16[t][g] = mfma16(a[(u) % AR][t].X, b16[u][g].X, acc16[t][g]); \
+    _Pragma("unroll") for (int g = 0; g < K::N4; ++g) acc4[t][g] = mfma4(a[(u) % AR][t].X, b4[u][g].X, acc4[t][g]); \
+  }
+// one quad: window operands AD quads ahead, then the offset that operand set
+// needs next; the products (each tile on its own where blocks are absent); the
+// table operands of quad u + U. The fences keep the reads in issue order and out
+// of the conditional blocks: then every wait covers the oldest reads only.
+#define PT_STEP(u, MORE)                                                                           \
+  {                                                                                                \
+    __builtin_amdgcn_sched_barrier(0);                                                             \
+    PT_LOADA(((u) + AD) % AR, ((u) + AD) % U);                                                     \
+    o[((u) + AD) % U] = sp[((u) + AD + U) * 4];                                                    \
+    if constexpr (FULL) {                                                                          \
+      _Pragma("unroll") for (int t = 0; t < TPW; ++t) PT_MMA1(u, t, x);                            \
+      _Pragma("unroll") for (int t = 0; t < TPW; ++t) PT_MMA1(u, t, y);                            \
+    } else {                                                                                       \
+      asm volatile("" ::: "memory");                                                               \
+      _Pragma("unroll") for (int t = 0; t < TPW; ++t) if ((uint32_t)lw[t][0] >> (u) & 1u) {        \
+        PT_MMA1(u, t, x);                                                                          \
+        PT_MMA1(u, t, y);                                                                          \
+      }                                                                                            \
+      asm volatile("" ::: "memory");                                                               \
+    }                                                                                              \
+    if (MORE) PT_LOADB(u, u + U);                                                                  \
+    __builtin_amdgcn_sched_barrier(0);                                                             \
+  }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        PT_LOADB(u, u);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      const double2* bb = sB2 + (ch & 1) * CH2 + boff;
-      if constexpr (PIPE) {
-        // Two operand sets: the reads of quad qi + 1 are issued before the products
-        // of quad qi, and the offset of qi + 2 one step further ahead. The reads
-        // are unconditional, with table indices clamped into the chunk, so every
-        // path into a product sees the same outstanding reads; operands read past
-        // the chunk's last quad are never multiplied. Window offsets are not
-        // clamped to the chunk, so a full chunk's last step leaves the window
-        // operands of the next chunk's first quad in (a0, offn): after the
-        // barrier only its table operands are read.
-#define BL_LOADA(DA, OFF)                                                      \
-  {                                                                            \
-    const int doff_ = (OFF);                                                   \
-    _Pragma("unroll") for (int t = 0; t < TPW; ++t) DA[t] = smem[abase[t] + doff_]; \
-  }
-#define BL_LOADB(DB, QI)                                                       \
-  { _Pragma("unroll") for (int g = 0; g < NG; ++g) DB[g] = bb[((QI) * NG + g) * 16]; }
-#define BL_LOAD(DA, DB, QI, OFF) \
-  BL_LOADA(DA, OFF);             \
-  BL_LOADB(DB, QI);
-#define BL_MMA(SA, SB)                                                              \
-  _Pragma("unroll") for (int t = 0; t < TPW; ++t) {                                 \
-    _Pragma("unroll") for (int g = 0; g < NG; ++g) acc[t][g] = mfma4(SA[t].x, SB[g].x, acc[t][g]); \
-    _Pragma("unroll") for (int g = 0; g < NG; ++g) acc[t][g] = mfma4(SA[t].y, SB[g].y, acc[t][g]); \
-  }
-// the reads for the next quad are spread through the first half of this quad's
-// products, so no wave has a long stretch without matrix instructions (the two
-// waves of a SIMD run in step between barriers and would otherwise leave the unit
-// idle together), and the last read has half the products to complete
-#define BL_INTERLEAVE()                                                             \
-  {                                                                                 \
-    constexpr int NLD = TPW + NG + 1, NMF = 2 * TPW * NG, PER = NMF / NLD > 2 ? 2 : 1; \
-    _Pragma("unroll") for (int i_ = 0; i_ < NLD; ++i_) {                            \
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                            \
-      __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);                          \
-    }                                                                               \
-    __builtin_amdgcn_sched_group_barrier(0x008, NMF - PER * NLD, 0);                \
-  }
-// product of quad QI from (SA, SB) while the reads of quad QN go into (DA, DB) and
-// the offset of quad OQ into offn
-#define BL_STEP(SA, SB, QI, DA, DB, QN, OQ)                                         \
-  if (FULL || ((cl >> (QI)) & 1u)) {                                                \
-    BL_LOAD(DA, DB, QN, offn);                                                      \
-    offn = so[(OQ) * 4];                                                            \
-    BL_MMA(SA, SB);                                                                 \
-    BL_INTERLEAVE();                                                                \
-  } else {                                                                          \
-    __builtin_amdgcn_sched_barrier(0); /* keeps the reads in each branch's block */ \
-    BL_LOAD(DA, DB, QN, offn);                                                      \
-    offn = so[(OQ) * 4];                                                            \
-  }
-        if (ch == 0) {
-          BL_LOADA(a0, so[q0 * 4]);
-          offn = so[min(q0 + 1, kQuads - 1) * 4];
-        }
-        BL_LOADB(b0, 0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) o[u] = sp[u * 4];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < AD; ++u) {
+        PT_LOADA(u, u);
+        o[u] = sp[(u + U) * 4];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      uint64_t lw[TPW][4];                             // live quads from the loop's first quad on
+      if constexpr (!FULL) {
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            lw[t][i] = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)live, 4 * t + i) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(live >> 32), 4 * t + i) << 32;
+      }
 #pragma unroll 1
-        for (int qi = 0; qi < nq; qi += 2) {
-          BL_STEP(a0, b0, qi, a1, b1, min(qi + 1, nq - 1), min(q0 + qi + 2, kQuads - 1));
-          if (qi + 1 >= nq) break;
-          BL_STEP(a1, b1, qi + 1, a0, b0, min(qi + 2, nq - 1), min(q0 + qi + 3, kQuads - 1));
-          if (qi == 4 && more) {
-            // next chunk's tables, stored mid-chunk (the buffer was freed by the
-            // previous chunk's barrier) so the barrier does not wait on them
-            double2* dst = sB2 + ((ch + 1) & 1) * CH2;
-            dst[tid] = bst0;
-            if (tid + NT < CH2) dst[tid + NT] = bst1;
-          }
-        }
-#undef BL_LOADA
-#undef BL_LOADB
-#undef BL_LOAD
-#undef BL_MMA
-#undef BL_INTERLEAVE
-#undef BL_STEP
-      } else {
-        uint32_t tm_next = tw[q0];
-        int4 o_next = off4[q0];
-        for (int qi = 0; qi < nq; ++qi) {
-          const uint32_t tm = tm_next;
-          const int4 o = o_next;
-          if (qi + 1 < nq) {
-            tm_next = tw[q0 + qi + 1];
-            o_next = off4[q0 + qi + 1];
-          }
-          if ((tm & d.mask) == 0) continue;   // every source of this quad is absent for this wave
-          int doff = o.x;
-          doff = kk == 1 ? o.y : doff;
-          doff = kk == 2 ? o.z : doff;
-          doff = kk == 3 ? o.w : doff;
-          double2 a[TPW];
+      for (int q = 0; q < kQuads / U * U; q += U) {
 #pragma unroll
-          for (int t = 0; t < TPW; ++t) a[t] = smem[abase[t] + doff];
-          double2 b[NG];
-#pragma unroll
-          for (int g = 0; g < NG; ++g) b[g] = bb[(qi * NG + g) * 16];
+        for (int u = 0; u < U; ++u) PT_STEP(u, true);
+        if constexpr (!FULL) {
 #pragma unroll
           for (int t = 0; t < TPW; ++t) {
 #pragma unroll
-            for (int g = 0; g < NG; ++g) acc[t][g] = mfma4(a[t].x, b[g].x, acc[t][g]);
-#pragma unroll
-            for (int g = 0; g < NG; ++g) acc[t][g] = mfma4(a[t].y, b[g].y, acc[t][g]);
+            for (int i = 0; i < 3; ++i) lw[t][i] = lw[t][i] >> U | lw[t][i + 1] << (64 - U);
+            lw[t][3] >>= U;
           }
         }
+        sq += U * NG * 256;
+        sp += U * 4;
       }
-      if (more) {
-        if constexpr (!PIPE || QC < 6) {
-          double2* dst = sB2 + ((ch + 1) & 1) * CH2;
-          dst[tid] = bst0;
-          if (tid + NT < CH2) dst[tid + NT] = bst1;
-        }
-        if constexpr (PIPE) {
-          const bool on = lane < nq2 && (tn & d.mask) != 0;
-          cl = (uint32_t)__builtin_amdgcn_readfirstlane((int)(__ballot(on) & 0xffffffffu));
-        }
-      }
-      __syncthreads();   // next chunk's tables visible; this chunk's buffer free
-    }
-  }
-
-  const int xi = lane >> 4, yi = (lane & 15) >> 2, j = lane & 3;
-  if constexpr (Range::kPartial) {
-    double* part = range.partial();
 #pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      const int tcell = ((t & 1) * 4 + xi) + kBlock * ((t >> 1) * 4 + yi) + kBlock * kBlock * wave;
-#pragma unroll
-      for (int g = 0; g < NG; ++g)
-        if (4 * g + j < CR) part[(size_t)(4 * g + j) * kNTarget + tcell] = acc[t][g];
-    }
-    return;
+      for (int u = 0; u < kQuads % U; ++u) PT_STEP(u, false);
+#undef PT_LOADB
+#undef PT_LOADA
+#undef PT_MMA1
+#undef PT_STEP
+    });
   }
   double* out = L + d.l_off;
-  if constexpr (HARM) {
-    // harmonic columns to LDS ([n'][target], over the window, which every wave
-    // has finished reading), then each thread expands one target to all C
+  if constexpr (!HARM) {
+    each_sum([&](int n, int target, double a) __attribute__((always_inline)) {
+      if (n < C) out[(size_t)n * kNTarget + target] = ldexp(a, l2 * (1 + order_of(n)));
+      return a;
+    });
+  } else {
+    // harmonic columns to LDS ([column][target of the part], over the window, which
+    // every wave has finished reading), then every target is expanded to all C
+    constexpr int NTG = 16 * S::TILES;
+    double* lh = reinterpret_cast<double*>(win);
+    static_assert(CR * NTG <= 2 * kWin * S::ROWS, "harmonic columns fit the window buffer");
+    // position of a target in the part: level 2 holds one tile, the others whole planes
+    auto local = [&](int target) { return LEVEL == 2 ? (target & 3) + 4 * ((target >> 3) & 3) : target - 64 * z0; };
     __syncthreads();
-    double* lh = reinterpret_cast<double*>(smem);
-    static_assert(CR * kNTarget <= 2 * kWinCells, "harmonic columns fit the window buffer");
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      const int x = (t & 1) * 4 + xi, y = (t >> 1) * 4 + yi;
-      const int tcell = x + kBlock * y + kBlock * kBlock * wave;
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const int n = 4 * g + j;
-        if (n < CR) lh[n * kNTarget + tcell] = acc[t][g];
-      }
-    }
+    each_sum([&](int n, int target, double a) __attribute__((always_inline)) {
+      if (n < CR) lh[n * NTG + local(target)] = a;
+      return a;
+    });
     __syncthreads();
-    static_assert(kBlThreads == kNTarget, "one target per thread");
-#pragma unroll
-    for (int n = 0; n < C; ++n) {
+    const int tg = tid % NTG;
+    const int target = 64 * z0 + (LEVEL == 2 ? tile_x(0) + (tg & 3) + kBlock * (ty + (tg >> 2)) : tg);
+    for (int n = tid / NTG; n < C; n += S::NT / NTG) {
       const HExp& e = hexp[n];
       double v = 0.0;
-      for (int u = 0; u < e.nterm; ++u) v = __builtin_fma(e.coef[u], lh[e.col[u] * kNTarget + tid], v);
-      out[(size_t)n * kNTarget + tid] = ldexp(v, l2 * (1 + order_of(n)));
-    }
-    return;
-  }
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int x = (t & 1) * 4 + xi, y = (t >> 1) * 4 + yi;
-    const int tcell = x + kBlock * y + kBlock * kBlock * wave;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const int n = 4 * g + j;
-      if (n < C) out[(size_t)n * kNTarget + tcell] = ldexp(acc[t][g], l2 * (1 + order_of(n)));
+      for (int u = 0; u < e.nterm; ++u) v = __builtin_fma(e.coef[u], lh[e.col[u] * NTG + tg], v);
+      out[(size_t)n * kNTarget + target] = ldexp(v, l2 * (1 + order_of(n)));
     }
   }
 }
 
+// The quads' LDS offsets to LDS: tables [first, first + N) of woff.
+template <int N, int NT>
+__device__ __forceinline__ void load_offsets(short4 (*s_off)[kQuads + kOffPad], const short4* __restrict__ woff, int first) {
+  for (int i = threadIdx.x; i < N * (kQuads + kOffPad); i += NT) {
+    const int t = i / (kQuads + kOffPad), q = i % (kQuads + kOffPad);
+    s_off[t][q] = q < kQuads ? woff[(first + t) * kQuads + q] : make_short4(0, 0, 0, 0);
+  }
+}
+
+// Parts of sub-grids, two workgroups per compute unit. With a counter the
+// workgroups take items from it; without, workgroup i runs item i.
+template <bool HARM>
+__global__ void __launch_bounds__(kPartThreads, 2) m2l_fwd_part_kernel(
+    const WorkItem* __restrict__ items, int count, unsigned* __restrict__ counter,
+    const DevDesc* __restrict__ desc, const double* __restrict__ M, double* __restrict__ L,
+    const double* __restrict__ B2, const double* __restrict__ B3, const double* __restrict__ B4,
+    const short4* __restrict__ woff, const uint32_t* __restrict__ ttouch, const int* __restrict__ rowtab,
+    const HRound* __restrict__ hr2, const HRound* __restrict__ hr3, const HRound* __restrict__ hr4,
+    const HExp* __restrict__ he2, const HExp* __restrict__ he3, const HExp* __restrict__ he4) {
+  __shared__ double2 win[kWin * kWinRows2];
+  __shared__ short4 s_off[3][kQuads + kOffPad];
+  __shared__ int s_item;
+  load_offsets<3, kPartThreads>(s_off, woff, 0);
+  for (;;) {
+    if (counter && threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
+    __syncthreads();
+    const int item = counter ? s_item : (int)blockIdx.x;
+    if (item >= count) {
+      // every workgroup draws one number past the items: the last one drawn clears
+      // the counter for the next launch
+      if (counter && threadIdx.x == 0 && item == count + (int)gridDim.x - 1) *counter = 0u;
+      break;
+    }
+    const WorkItem w = items[item];
+    const DevDesc d = desc[w.sub];
+    auto run = [&](auto order, const double* B, const HRound* hr, const HExp* he) __attribute__((always_inline)) {
+      constexpr int P = decltype(order)::value;
+      const int level = w.part & 15, idx = w.part >> 4;
+      auto part = [&](auto lv) __attribute__((always_inline)) {
+        constexpr int LV = decltype(lv)::value;
+        if (d.mask == kFullMask) fwd_part<P, HARM, true, LV>(d, M, L, B, ttouch, rowtab, win, s_off, hr, he, idx);
+        else fwd_part<P, HARM, false, LV>(d, M, L, B, ttouch, rowtab, win, s_off, hr, he, idx);
+      };
+      if (level == 0) part(std::integral_constant<int, 0>{});
+      else if (level == 1) part(std::integral_constant<int, 1>{});
+      else part(std::integral_constant<int, 2>{});
+    };
+    switch (d.p) {
+      case 2: run(std::integral_constant<int, 2>{}, B2, hr2, he2); break;
+      case 3: run(std::integral_constant<int, 3>{}, B3, hr3, he3); break;
+      case 4: run(std::integral_constant<int, 4>{}, B4, hr4, he4); break;
+      default: break;
+    }
+    if (!counter) break;
+    __syncthreads();   // every thread has read s_item; the item's LDS use is done
+  }
+}
+
+// Whole sub-grids, one workgroup per compute unit, items from the counter.
+//
 // FUSE: the kernel computes each sub-grid's moments itself (the frame rows
 // holding the reachable window, 8 particles per cell, written to M as the P2M
 // kernel writes them) before that sub-grid's M2L reads them. A workgroup takes
@@ -647,31 +744,26 @@ __device__ __forceinline__ void fwd_bl_subgrid(const DevDesc& d, const double* _
 // phase while the others keep the matrix cores busy. Only the first item's
 // moments are computed before any M2L. The moments are written and read by the
 // same workgroup, with barriers between.
-template <bool PIPE, bool HARM = false, bool FUSE = false, int QDIV = 1>
-__global__ void __launch_bounds__(kBlThreads) m2l_fwd_bl_kernel(
+template <bool HARM, bool FUSE>
+__global__ void __launch_bounds__(kWholeThreads) m2l_fwd_whole_kernel(
     const WorkItem* __restrict__ items, int count, unsigned* __restrict__ counter,
     const DevDesc* __restrict__ desc, const double* M, double* __restrict__ L,
     const double* __restrict__ B2, const double* __restrict__ B3, const double* __restrict__ B4,
-    const int* __restrict__ lds_off, const uint32_t* __restrict__ touch,
+    const short4* __restrict__ woff, const uint32_t* __restrict__ ttouch, const int* __restrict__ rowtab,
     const HRound* __restrict__ hr2, const HRound* __restrict__ hr3, const HRound* __restrict__ hr4,
     const HExp* __restrict__ he2, const HExp* __restrict__ he3, const HExp* __restrict__ he4,
-    const double* __restrict__ pos = nullptr, const double* __restrict__ mass = nullptr,
-    double* Mw = nullptr) {
+    const double* __restrict__ pos, const double* __restrict__ mass, double* Mw) {
   // (FUSE: Mw is M, writable; the moment phase writes through it)
-  __shared__ double2 smem[kWinCells];
-  __shared__ double sB[2 * kBlChunkMax];
-  __shared__ int4 s_off[kQuads];
+  __shared__ double2 win[kWinCells];
+  __shared__ short4 s_off[1][kQuads + kOffPad];
   __shared__ int s_item;
-  static_assert(kP2MRowsLds <= 2 * kWinCells && kBlThreads == kP2MRowsThreads,
+  static_assert(kP2MRowsLds <= 2 * kWinCells && kWholeThreads == kP2MRowsThreads,
                 "the moment phase fits the window buffer and the workgroup");
-  if (PIPE) {
-    const int4* off4 = reinterpret_cast<const int4*>(lds_off);
-    for (int i = threadIdx.x; i < kQuads; i += blockDim.x) s_off[i] = off4[i];
-  }
+  load_offsets<1, kWholeThreads>(s_off, woff, 3);
   // moments of item `it` into M (the window buffer is free whenever this runs)
   auto moments = [&](int it) __attribute__((always_inline)) {
     const DevDesc dn = desc[items[it].sub];
-    double* lds = reinterpret_cast<double*>(smem);
+    double* lds = reinterpret_cast<double*>(win);
     switch (dn.p) {
       case 2: p2m_window_rows<2>(dn, pos, mass, Mw, lds); break;
       case 3: p2m_window_rows<3>(dn, pos, mass, Mw, lds); break;
@@ -691,45 +783,28 @@ __global__ void __launch_bounds__(kBlThreads) m2l_fwd_bl_kernel(
     if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
     __syncthreads();
     // FUSE: s_item is the next item, whose moments are computed during this one
-    const int item = FUSE ? cur : s_item;
     const int next = s_item;
-    if (item >= count) break;
+    const int item = FUSE ? cur : next;
+    if (item >= count) {
+      // the last number any workgroup draws (one past the items each, two in the
+      // fused form) clears the counter for the next launch
+      if (threadIdx.x == 0 && next == count + (FUSE ? 2 : 1) * (int)gridDim.x - 1) *counter = 0u;
+      break;
+    }
     const DevDesc d = desc[items[item].sub];
-    const bool full = d.mask == kFullMask;
-    const auto hook = [&]() {
-      if constexpr (FUSE) return MomentHook<decltype(moments)>{next, count, moments};
-      else return NoHook{};
-    }();
+    auto run = [&](auto order, const double* B, const HRound* hr, const HExp* he) __attribute__((always_inline)) {
+      constexpr int P = decltype(order)::value;
+      const auto hook = [&]() {
+        if constexpr (FUSE) return MomentHook<decltype(moments)>{next, count, moments};
+        else return NoMoments{};
+      }();
+      if (d.mask == kFullMask) fwd_part<P, HARM, true, kWhole>(d, M, L, B, ttouch, rowtab, win, s_off, hr, he, 0, hook);
+      else fwd_part<P, HARM, false, kWhole>(d, M, L, B, ttouch, rowtab, win, s_off, hr, he, 0, hook);
+    };
     switch (d.p) {
-      case 2:
-        if (PIPE && full)
-          fwd_bl_subgrid<2, PIPE, true, HARM, std::remove_cv_t<decltype(hook)>, AllRounds, QDIV>(d, M, L, B2, lds_off, touch, smem, sB,
-                                                                              s_off, hr2, he2, hook);
-        else
-          fwd_bl_subgrid<2, PIPE, false, HARM, std::remove_cv_t<decltype(hook)>, AllRounds, QDIV>(d, M, L, B2, lds_off, touch, smem, sB,
-                                                                              s_off, hr2, he2, hook);
-        break;
-      case 3:
-        if (PIPE && full)
-          fwd_bl_subgrid<3, PIPE, true, HARM, std::remove_cv_t<decltype(hook)>, AllRounds, QDIV>(d, M, L, B3, lds_off, touch, smem, sB,
-                                                                              s_off, hr3, he3, hook);
-        else
-          fwd_bl_subgrid<3, PIPE, false, HARM, std::remove_cv_t<decltype(hook)>, AllRounds, QDIV>(d, M, L, B3, lds_off, touch, smem, sB,
-                                                                              s_off, hr3, he3, hook);
-        break;
-      case 4:
-        // the dense p = 4 operand sets (9 column groups) do not fit the registers
-        // of the pipelined loop; the harmonic ones (7) do
-        if (HARM && PIPE && full)
-          fwd_bl_subgrid<4, PIPE, true, HARM, std::remove_cv_t<decltype(hook)>, AllRounds, QDIV>(d, M, L, B4, lds_off, touch, smem, sB,
-                                                                               s_off, hr4, he4, hook);
-        else if (HARM && PIPE)
-          fwd_bl_subgrid<4, PIPE, false, HARM, std::remove_cv_t<decltype(hook)>, AllRounds, QDIV>(d, M, L, B4, lds_off, touch, smem, sB,
-                                                                                s_off, hr4, he4, hook);
-        else
-          fwd_bl_subgrid<4, false, false, HARM, std::remove_cv_t<decltype(hook)>, AllRounds, QDIV>(d, M, L, B4, lds_off, touch, smem, sB,
-                                                                                s_off, hr4, he4, hook);
-        break;
+      case 2: run(std::integral_constant<int, 2>{}, B2, hr2, he2); break;
+      case 3: run(std::integral_constant<int, 3>{}, B3, hr3, he3); break;
+      case 4: run(std::integral_constant<int, 4>{}, B4, hr4, he4); break;
       default: break;
     }
     __syncthreads();   // every thread has read s_item; the item's LDS use is done
@@ -1024,13 +1099,19 @@ constexpr int kAccStride = kWinCells + 17;
 constexpr int kMaxPairs = 512;
 constexpr int kBwdGroups = 8;       // offset groups, between barriers (see build_pairs)
 
+// Hook: at the top of round r, after the round's first barrier and with the
+// accumulators all zero, hook.run(lds) is called if hook.wants(r, ROUNDS)
+// (uniform over the workgroup); it may use the accumulators as scratch, and they
+// are cleared again after it. The A operands are rebuilt from dL after it.
+struct NoHook {
+  __device__ bool wants(int, int) const { return false; }
+  __device__ void run(double*) const {}
+};
+
 // FULL: every neighbour block is present, so no pair is skipped and the pair
 // loop carries no branches.
 // HARM: the harmonic form; dL is folded to the (p+1)^2 harmonic columns, the
 // rounds accumulate folded output components and the write-out expands them.
-// Hook: as for the forward kernel; here it runs after the barrier at the top of
-// round r, with the accumulators all zero, may use them as scratch, and they
-// are cleared again after it. The A operands are rebuilt from dL after it.
 template <int P, bool FULL, bool HARM = false, class Hook = NoHook>
 __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __restrict__ dL,
                                             double* dM, const double* __restrict__ Bp,
@@ -1337,120 +1418,6 @@ __global__ void __launch_bounds__(kBwdThreads) m2l_bwd_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Round split, for batches too small to fill the GPU: work items are (sub-grid,
-// round) pairs (WorkItem::cost holds the round), each writing its round's raw
-// sums to its own slot of `part`; m2l_round_sum_kernel then adds a sub-grid's
-// rounds in round order and scales (and, in the harmonic form, expands) them
-// into L. Same products as the whole-sub-grid kernel, summed in another order.
-// ---------------------------------------------------------------------------
-constexpr int kPartStride = 35 * kNTarget;    // doubles per slot: C (p = 4) x 512
-
-template <bool PIPE, bool HARM>
-__global__ void __launch_bounds__(kBlThreads) m2l_fwd_round_kernel(
-    const WorkItem* __restrict__ items, int count, unsigned* __restrict__ counter,
-    const DevDesc* __restrict__ desc, const double* __restrict__ M, double* __restrict__ part,
-    const double* __restrict__ B2, const double* __restrict__ B3, const double* __restrict__ B4,
-    const int* __restrict__ lds_off, const uint32_t* __restrict__ touch,
-    const HRound* __restrict__ hr2, const HRound* __restrict__ hr3, const HRound* __restrict__ hr4) {
-  __shared__ double2 smem[kWinCells];
-  __shared__ double sB[2 * kBlChunkMax];
-  __shared__ int4 s_off[kQuads];
-  __shared__ int s_item;
-  if (PIPE) {
-    const int4* off4 = reinterpret_cast<const int4*>(lds_off);
-    for (int i = threadIdx.x; i < kQuads; i += blockDim.x) s_off[i] = off4[i];
-  }
-  const HExp* ne = nullptr;
-  for (;;) {
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
-    __syncthreads();
-    const int item = s_item;
-    if (item >= count) break;
-    const DevDesc d = desc[items[item].sub];
-    const bool full = d.mask == kFullMask;
-    const OneRound rg{items[item].cost, part + (size_t)item * kPartStride};
-    const NoHook nh;
-    switch (d.p) {
-      case 2:
-        if (PIPE && full)
-          fwd_bl_subgrid<2, PIPE, true, HARM>(d, M, nullptr, B2, lds_off, touch, smem, sB, s_off, hr2, ne, nh, rg);
-        else
-          fwd_bl_subgrid<2, PIPE, false, HARM>(d, M, nullptr, B2, lds_off, touch, smem, sB, s_off, hr2, ne, nh, rg);
-        break;
-      case 3:
-        if (PIPE && full)
-          fwd_bl_subgrid<3, PIPE, true, HARM>(d, M, nullptr, B3, lds_off, touch, smem, sB, s_off, hr3, ne, nh, rg);
-        else
-          fwd_bl_subgrid<3, PIPE, false, HARM>(d, M, nullptr, B3, lds_off, touch, smem, sB, s_off, hr3, ne, nh, rg);
-        break;
-      case 4:
-        if (HARM && PIPE && full)
-          fwd_bl_subgrid<4, PIPE, true, HARM>(d, M, nullptr, B4, lds_off, touch, smem, sB, s_off, hr4, ne, nh, rg);
-        else if (HARM && PIPE)
-          fwd_bl_subgrid<4, PIPE, false, HARM>(d, M, nullptr, B4, lds_off, touch, smem, sB, s_off, hr4, ne, nh, rg);
-        else
-          fwd_bl_subgrid<4, false, false, HARM>(d, M, nullptr, B4, lds_off, touch, smem, sB, s_off, hr4, ne, nh, rg);
-        break;
-      default: break;
-    }
-    __syncthreads();
-  }
-}
-
-template <int P, bool HARM>
-__device__ __forceinline__ void round_sum(const DevDesc& d, const double* __restrict__ part, int base,
-                                          double* __restrict__ L, const HExp* __restrict__ hexp) {
-  constexpr int C = ncomp(P);
-  constexpr int CR = HARM ? (P + 1) * (P + 1) : C;
-  constexpr int ROUNDS = (CR + 1) / 2;
-  const int tid = threadIdx.x;
-  const int l2 = d.log2_inv_h;
-  double h[CR];
-#pragma unroll
-  for (int c = 0; c < CR; ++c) h[c] = 0.0;
-  for (int r = 0; r < ROUNDS; ++r) {
-    const double* src = part + (size_t)(base + r) * kPartStride + tid;
-#pragma unroll
-    for (int c = 0; c < CR; ++c) h[c] += src[(size_t)c * kNTarget];
-  }
-  double* out = L + d.l_off + tid;
-#pragma unroll
-  for (int n = 0; n < C; ++n) {
-    double v;
-    if constexpr (HARM) {
-      const HExp& e = hexp[n];
-      v = 0.0;
-      for (int u = 0; u < e.nterm; ++u) {
-        double hc = 0.0;
-#pragma unroll
-        for (int c = 0; c < CR; ++c) hc = c == e.col[u] ? h[c] : hc;
-        v = __builtin_fma(e.coef[u], hc, v);
-      }
-    } else {
-      v = h[n];
-    }
-    out[(size_t)n * kNTarget] = ldexp(v, l2 * (1 + order_of(n)));
-  }
-}
-
-// one workgroup per sub-grid, one thread per target cell; base[b]: the slot of
-// sub-grid b's first round (its rounds are consecutive slots)
-template <bool HARM>
-__global__ void __launch_bounds__(kNTarget) m2l_round_sum_kernel(
-    const DevDesc* __restrict__ desc, const int* __restrict__ base, const double* __restrict__ part,
-    double* __restrict__ L, const HExp* __restrict__ he2, const HExp* __restrict__ he3,
-    const HExp* __restrict__ he4) {
-  const int b = blockIdx.x;
-  const DevDesc d = desc[b];
-  switch (d.p) {
-    case 2: round_sum<2, HARM>(d, part, base[b], L, he2); break;
-    case 3: round_sum<3, HARM>(d, part, base[b], L, he3); break;
-    case 4: round_sum<4, HARM>(d, part, base[b], L, he4); break;
-    default: break;
-  }
-}
-
-// ---------------------------------------------------------------------------
 // table packing
 // ---------------------------------------------------------------------------
 
@@ -1656,27 +1623,25 @@ std::vector<int> host_stencil() {
   return s;
 }
 
-// Configurations: forward waves per workgroup (tiles per wave = 32 / waves).
+// Forward configurations.
 struct Config {
-  int ldstab;       // table operands staged through LDS (8 waves): 1, or 2 with the
-                    // next quad's operand reads issued ahead; 0: loaded per wave
-  int waves;        // waves per workgroup (16-cell tiles per wave = 32 / waves)
-  bool prefetch;    // table operands of the next offset quad loaded one quad ahead
-                    // (not at p = 4 with 8 waves: the registers would spill)
   fmm_precision prec;
-  int qdiv = 1;     // LDS-staged tables: chunks of 1/qdiv of the default length
+  bool stream;          // m2l_fwd_stream_kernel; otherwise (FMM_FP64) m2l_fwd_kernel with
+  int waves = 8;        //   this many waves per workgroup (16-cell tiles per wave = 32 / waves)
+  bool prefetch = false;   // and the table operands of the next offset quad loaded one quad ahead
+                           // (not at p = 4 with 8 waves: the registers would spill)
+  int same_as = -1;     // runs the same kernel as this entry (not timed by the autotuner)
 };
-constexpr Config kConfigs[] = {{2, 8, false, FMM_FP64}, {1, 8, false, FMM_FP64},
-                               {0, 8, true, FMM_FP64},  {0, 8, false, FMM_FP64},
-                               {0, 4, false, FMM_FP64}, {0, 4, true, FMM_FP64},
-                               {0, 8, false, FMM_SPLIT_FP32}, {2, 8, false, FMM_FP64_HARMONIC},
-                               {0, 4, false, FMM_EXACT_SLICE},
-                               {1, 8, false, FMM_FP64_HARMONIC}, {2, 8, false, FMM_FP64_HARMONIC, 2}};
+constexpr Config kConfigs[] = {{FMM_FP64, true}, {FMM_FP64, true, 8, false, 0},
+                               {FMM_FP64, false, 8, true},  {FMM_FP64, false, 8, false},
+                               {FMM_FP64, false, 4, false}, {FMM_FP64, false, 4, true},
+                               {FMM_SPLIT_FP32, false}, {FMM_FP64_HARMONIC, true}, {FMM_EXACT_SLICE, false},
+                               {FMM_FP64_HARMONIC, true, 8, false, 7}, {FMM_FP64_HARMONIC, true, 8, false, 7}};
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 
 }  // namespace
 
-void fill_work_list(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkItem* out) {
+void sort_by_cost(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkItem* out) {
   static const std::vector<int> st = host_stencil();
   for (int64_t b = 0; b < nsub; ++b) {
     const int p = desc[b].p;
@@ -1684,17 +1649,84 @@ void fill_work_list(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkIt
                                       : (int64_t)ncomp(p) * ncomp(p);
     const int64_t pairs = block_pair_count(desc[b].mask, st);
     out[b].sub = (int32_t)b;
-    out[b].cost = (int32_t)(per_pair * pairs / 4096);
+    out[b].part = (int32_t)(per_pair * pairs / 4096);   // below 2^18
   }
   std::sort(out, out + nsub, [](const WorkItem& a, const WorkItem& b) {
-    return a.cost != b.cost ? a.cost > b.cost : a.sub < b.sub;
+    return a.part != b.part ? a.part > b.part : a.sub < b.sub;
   });
 }
 
-std::vector<WorkItem> build_work_list(const fmm_subgrid* desc, int64_t nsub, bool harmonic) {
-  std::vector<WorkItem> items((size_t)nsub);
-  fill_work_list(desc, nsub, harmonic, items.data());
-  return items;
+void whole_items(WorkItem* items, int64_t n) {
+  for (int64_t i = 0; i < n; ++i) items[i].part = 0;
+}
+
+// Time (in cost units) of the items, longest first, on num_cu compute units that
+// each take the next one when free, with `each` added to every item.
+static int64_t makespan(const WorkItem* items, int64_t n, int num_cu, int64_t total, int64_t each) {
+  constexpr int kMaxUnits = 1024;
+  if (n <= num_cu) return items[0].part + each;
+  if (items[0].part == items[n - 1].part) return ((n + num_cu - 1) / num_cu) * (items[0].part + each);
+  // unlike sub-grids end on short ones: past a few per unit the ends even out
+  if (n > 4 * (int64_t)num_cu || num_cu > kMaxUnits) return (total + n * each) / num_cu;
+  int64_t free_at[kMaxUnits] = {};   // a min-heap
+  for (int64_t i = 0; i < n; ++i) {
+    std::pop_heap(free_at, free_at + num_cu, std::greater<int64_t>());
+    free_at[num_cu - 1] += items[i].part + each;
+    std::push_heap(free_at, free_at + num_cu, std::greater<int64_t>());
+  }
+  return *std::max_element(free_at, free_at + num_cu);
+}
+
+// In cost units (p = 3, all blocks present: 28,544 harmonic, 44,600 dense; a
+// workgroup takes 0.031 us per unit, so 890 and 1350 us): a batch in parts takes
+// 1.03 of its work spread evenly plus about a fifth of its longest sub-grid (512
+// alike: 2050 us against 1850 whole; 300: 1230 against 1960; 700 mixed: 3300
+// against 3640); moments cost 100 us inside a whole sub-grid's launch and 0.77 us
+// of the whole GPU per sub-grid in a launch of their own.
+StreamPlan plan_stream(const WorkItem* items, int64_t n, int num_cu) {
+  constexpr int64_t kMomentsInside = 3300, kMomentsApart = 6300;
+  if (n == 0) return StreamPlan{};
+  int64_t total = 0;
+  for (int64_t i = 0; i < n; ++i) total += items[i].part;
+  const int64_t whole = makespan(items, n, num_cu, total, 0);
+  const int64_t parts = (total * 103 / num_cu + 20 * (int64_t)items[0].part) / 100;
+  StreamPlan p;
+  p.parts = parts < whole;
+  p.fuse = n > num_cu && makespan(items, n, num_cu, total, kMomentsInside) <
+                             std::min(parts, whole) + n * kMomentsApart / num_cu;
+  return p;
+}
+
+// Where the levels' lines lie (costs c in sub-grids, harmonic p = 3, 256 compute
+// units, us): a sub-grid goes in eighths while a quarter of it on a compute unit
+// of its own takes longer than the whole batch on a full GPU. 32 alike: 288 in
+// quarters, 188 in eighths; 43 alike 293 and 302; 100 alike 514 and 559. A batch
+// of unlike sub-grids, whose longest would set the time, gains further up: 64
+// mixed orders 956 and 701, 128 1102 and 958, 200 1390 and 1349. Tiles, which
+// stage more window and use the matrix cores less well, only where eighths cannot
+// reach every compute unit: 8 alike 266 in quarters, 158 in eighths, 118 in tiles;
+// 24 alike 279, 180, 269.
+int64_t split_items(WorkItem* items, int64_t n, int num_cu) {
+  int64_t total = 0, extra = 0;
+  for (int64_t i = 0; i < n; ++i) total += items[i].part;
+  const bool unlike = n > 0 && 2 * n * items[0].part > 3 * total;   // the longest is over 1.5 times the mean
+  for (int64_t i = 0; i < n; ++i) {
+    const int64_t c = (int64_t)items[i].part * num_cu;
+    int level = 0;
+    if ((unlike ? c * 2 : c * 6 / 10) > 4 * total) level = 1;
+    if (c * 6 / 10 > 8 * total) level = 2;
+    if (extra + kLevelParts[level] - kLevelParts[0] > kMaxExtraItems) level = 0;
+    extra += kLevelParts[level] - kLevelParts[0];
+    items[i].part = level;
+  }
+  // in place, from the back: an item's parts land at or after it
+  const int64_t parts = n * kLevelParts[0] + extra;
+  int64_t to = parts;
+  for (int64_t i = n - 1; i >= 0; --i) {
+    const WorkItem w = items[i];
+    for (int k = kLevelParts[w.part] - 1; k >= 0; --k) items[--to] = WorkItem{w.sub, w.part | k << 4};
+  }
+  return parts;
 }
 
 namespace {
@@ -1707,6 +1739,49 @@ uint32_t plane_blocks(const std::vector<int>& st, int z, int o) {
     for (int by = (8 + dy) / 8; by <= (15 + dy) / 8; ++by) m |= 1u << (bx + 3 * by + 9 * bz);
   return m;
 }
+// blocks touched by target tile `tile` (4 plane + 2 y + x in the plane's 2 x 2 tiles) shifted by offset o
+uint32_t tile_blocks(const std::vector<int>& st, int tile, int o) {
+  const int x0 = 8 + 4 * (tile & 1) + st[3 * o], y0 = 8 + 4 * ((tile >> 1) & 1) + st[3 * o + 1];
+  const int bz = (8 + (tile >> 2) + st[3 * o + 2]) / 8;
+  uint32_t m = 0;
+  for (int bx = x0 / 8; bx <= (x0 + 3) / 8; ++bx)
+    for (int by = y0 / 8; by <= (y0 + 3) / 8; ++by) m |= 1u << (bx + 3 * by + 9 * bz);
+  return m;
+}
+
+// Rows of the streamed forward's windows (WindowCells): of two target planes, of
+// one, and those one tile of that one reaches (tile row 0, then 1).
+std::vector<int> window_row_table() {
+  std::vector<int> t;
+  auto rows = [&](int nz, int y0, int span) {
+    for (int w = 0, base = 0; w < nz + 12; ++w) {
+      const int reach = window_reach(nz, w);
+      for (int y = y0 - reach; y < y0 + span + reach; ++y) t.push_back(y | w << 8 | (base + y - (6 - reach)) << 16);
+      base += 8 + 2 * reach;
+    }
+  };
+  rows(2, 6, 8);
+  rows(1, 6, 8);
+  rows(1, 6, 4);
+  rows(1, 10, 4);
+  for (int w = 0; w < kWin; ++w)   // a whole sub-grid's window keeps its full planes in LDS
+    for (int y = 6 - window_reach(8, w); y < 14 + window_reach(8, w); ++y) t.push_back(y | w << 8 | (y + kWin * w) << 16);
+  return t;
+}
+
+// LDS offsets of the stencil offsets in those windows: from either target plane
+// of two, from the one, and in a whole sub-grid's window.
+std::vector<short> window_offsets(const std::vector<int>& st) {
+  std::vector<short> v;
+  for (int k = 0; k < 4; ++k)
+    for (int i = 0; i < kNStencil; ++i) {
+      const int dz = st[3 * i + 2];
+      const int plane = k == 3 ? kWin * kWin * dz : k == 2 ? window_base(1, dz + 6) : window_base(2, dz + 6 + k);
+      v.push_back((short)(plane + kWin * st[3 * i + 1] + st[3 * i]));
+    }
+  return v;
+}
+
 // ---- harmonic form: fold, round plan and expansion (host)
 
 struct MI3 {
@@ -1887,6 +1962,13 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
   for (int z = 0; z < 8; ++z)
     for (int q = 0; q < kQuads; ++q)
       for (int o = 4 * q; o < 4 * q + 4; ++o) touch[z * kQuads + q] |= plane_blocks(st, z, o);
+  std::vector<uint32_t> ttouch(32 * kQuads, 0u);
+  for (int tile = 0; tile < 32; ++tile)
+    for (int q = 0; q < kQuads; ++q)
+      for (int o = 4 * q; o < 4 * q + 4; ++o) ttouch[tile * kQuads + q] |= tile_blocks(st, tile, o);
+  const std::vector<int> rowtab = window_row_table();
+  const std::vector<short> woff = window_offsets(st);
+  if (rowtab.size() != (size_t)(kWinRows2 + kWinRows1 + 2 * kWinRowsTile + kWinRows8)) return hipErrorInvalidValue;
   // adjoint: offset pairs grouped by dz, blocks each pair writes per target plane
   std::vector<int4> pairs;
   std::vector<int> gstart;
@@ -1905,7 +1987,13 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
   if ((e = hipMalloc(&t->pairs, pairs.size() * sizeof(int4))) != hipSuccess) return e;
   if ((e = hipMalloc(&t->gstart, gstart.size() * sizeof(int))) != hipSuccess) return e;
   if ((e = hipMalloc(&t->ptouch, ptouch.size() * sizeof(uint32_t))) != hipSuccess) return e;
+  if ((e = hipMalloc(&t->ttouch, ttouch.size() * sizeof(uint32_t))) != hipSuccess) return e;
+  if ((e = hipMalloc(&t->rowtab, rowtab.size() * sizeof(int))) != hipSuccess) return e;
+  if ((e = hipMalloc(&t->woff, woff.size() * sizeof(short))) != hipSuccess) return e;
   // synchronous copies: the host vectors die at return
+  if ((e = hipMemcpy(t->ttouch, ttouch.data(), ttouch.size() * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess) return e;
+  if ((e = hipMemcpy(t->rowtab, rowtab.data(), rowtab.size() * sizeof(int), hipMemcpyHostToDevice)) != hipSuccess) return e;
+  if ((e = hipMemcpy(t->woff, woff.data(), woff.size() * sizeof(short), hipMemcpyHostToDevice)) != hipSuccess) return e;
   if ((e = hipMemcpy(t->lds_off, off.data(), off.size() * sizeof(int), hipMemcpyHostToDevice)) != hipSuccess) return e;
   if ((e = hipMemcpy(t->touch, touch.data(), touch.size() * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess) return e;
   if ((e = hipMemcpy(t->pairs, pairs.data(), pairs.size() * sizeof(int4), hipMemcpyHostToDevice)) != hipSuccess) return e;
@@ -1914,7 +2002,7 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
   for (int p = 2; p <= kMaxP; ++p) {
     const size_t nf = fwd_pack_elems(p), nb = bwd_pack_elems(p, t->npairs);
     if ((e = hipMalloc(&t->fwd[p], nf * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&t->fwdl[p], nf * sizeof(double))) != hipSuccess) return e;
+    if ((e = hipMalloc(&t->fwdl[p], (nf + kTablePad) * sizeof(double))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->fwd_hi[p], nf * sizeof(float))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->fwd_lo[p], nf * sizeof(float))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->bwd[p], nb * sizeof(double))) != hipSuccess) return e;
@@ -1926,8 +2014,10 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
     if ((e = hipGetLastError()) != hipSuccess) return e;
     HostHarmonic hh;
     if (!build_harmonic(p, &hh)) return hipErrorInvalidValue;
+    for (const HRound& rd : hh.rounds)
+      if (rd.nsup > harmonic_sup(p)) return hipErrorInvalidValue;
     const size_t nh = hh.rounds.size() * (size_t)kQuads * hh.ng * 32;
-    if ((e = hipMalloc(&t->fwdh[p], nh * sizeof(double))) != hipSuccess) return e;
+    if ((e = hipMalloc(&t->fwdh[p], (nh + kTablePad) * sizeof(double))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->hround[p], hh.rounds.size() * sizeof(HRound))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->hexp[p], hh.exps.size() * sizeof(HExp))) != hipSuccess) return e;
     if ((e = hipMemcpy(t->hround[p], hh.rounds.data(), hh.rounds.size() * sizeof(HRound),
@@ -1977,6 +2067,12 @@ void mfma_tables_destroy(MfmaTables* t) {
   }
   if (t->lds_off) (void)hipFree(t->lds_off);
   if (t->touch) (void)hipFree(t->touch);
+  if (t->ttouch) (void)hipFree(t->ttouch);
+  if (t->rowtab) (void)hipFree(t->rowtab);
+  if (t->woff) (void)hipFree(t->woff);
+  t->ttouch = nullptr;
+  t->rowtab = nullptr;
+  t->woff = nullptr;
   if (t->pairs) (void)hipFree(t->pairs);
   if (t->gstart) (void)hipFree(t->gstart);
   if (t->ptouch) (void)hipFree(t->ptouch);
@@ -1999,52 +2095,52 @@ int mfma_default_config(fmm_precision prec) {
   return 0;
 }
 
-bool mfma_config_fusable(int cfg) { return cfg >= 0 && cfg < kNumConfigs && kConfigs[cfg].ldstab > 0; }
+bool mfma_config_streams(int cfg) { return cfg >= 0 && cfg < kNumConfigs && kConfigs[cfg].stream; }
 
-hipError_t launch_m2l_mfma(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc,
-                           const double* M, double* L, fmm_precision prec, int cfg,
-                           hipStream_t s, const double* pos, const double* mass, double* Mw) {
+bool mfma_config_distinct(int cfg) { return kConfigs[cfg].same_as < 0; }
+
+hipError_t launch_m2l_stream(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc, const double* M,
+                             double* L, bool harmonic, hipStream_t s, const double* pos, const double* mass, double* Mw) {
   if (w.count == 0) return hipSuccess;
-  // (FMM_EXACT_SLICE runs through launch_m2l_slice)
-  if (!mfma_config_supports(cfg, prec) || prec == FMM_EXACT_SLICE) return hipErrorInvalidValue;
-  const bool fuse = pos != nullptr;
-  if (fuse && (!mfma_config_fusable(cfg) || mass == nullptr || Mw != M)) return hipErrorInvalidValue;
-  const int grid = std::min(t.num_cu, w.count);
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, w.counter);
-  const Config& c = kConfigs[cfg];
-  const HRound* nr = nullptr;
-  const HExp* ne = nullptr;
-#define BL_LAUNCH(PIPEV, HARMV, FUSEV, B, HR, HE, ...)                                                    \
-  hipLaunchKernelGGL((m2l_fwd_bl_kernel<PIPEV, HARMV, FUSEV, ##__VA_ARGS__>), dim3(grid), dim3(kBlThreads), 0, s,   \
-                     w.items, w.count, w.counter, d_desc, M, L, B[2], B[3], B[4], t.lds_off, t.touch, \
-                     HR[0], HR[1], HR[2], HE[0], HE[1], HE[2], pos, mass, Mw)
-  const HRound* hr[3] = {t.hround[2], t.hround[3], t.hround[4]};
-  const HExp* he[3] = {t.hexp[2], t.hexp[3], t.hexp[4]};
-  const HRound* hr0[3] = {nr, nr, nr};
-  const HExp* he0[3] = {ne, ne, ne};
-  if (c.prec == FMM_FP64_HARMONIC) {
-    if (c.ldstab == 1 && fuse) BL_LAUNCH(false, true, true, t.fwdh, hr, he);
-    else if (c.ldstab == 1) BL_LAUNCH(false, true, false, t.fwdh, hr, he);
-    else if (c.qdiv == 2 && fuse) BL_LAUNCH(true, true, true, t.fwdh, hr, he, 2);
-    else if (c.qdiv == 2) BL_LAUNCH(true, true, false, t.fwdh, hr, he, 2);
-    else if (fuse) BL_LAUNCH(true, true, true, t.fwdh, hr, he);
-    else BL_LAUNCH(true, true, false, t.fwdh, hr, he);
+  if (pos && (mass == nullptr || Mw != M || w.parts)) return hipErrorInvalidValue;
+  const HRound* const nr[3] = {};
+  const HExp* const ne[3] = {};
+  const HRound* const hr[3] = {t.hround[2], t.hround[3], t.hround[4]};
+  const HExp* const he[3] = {t.hexp[2], t.hexp[3], t.hexp[4]};
+#define STREAM_LAUNCH(KERNEL, GRID, NT, COUNTER, B, HR, HE, ...)                                                  \
+  hipLaunchKernelGGL(KERNEL, dim3(GRID), dim3(NT), 0, s, w.items, w.count, COUNTER, d_desc, M, L, B[2], B[3], B[4], \
+                     t.woff, t.ttouch, t.rowtab, HR[0], HR[1], HR[2], HE[0], HE[1], HE[2], ##__VA_ARGS__)
+  if (w.parts) {
+    const int grid = std::min(2 * t.num_cu, w.count);
+    // no more items than workgroups: each takes its own, without the counter
+    unsigned* counter = w.count > grid ? w.counter : nullptr;
+    if (harmonic) STREAM_LAUNCH((m2l_fwd_part_kernel<true>), grid, kPartThreads, counter, t.fwdh, hr, he);
+    else STREAM_LAUNCH((m2l_fwd_part_kernel<false>), grid, kPartThreads, counter, t.fwdl, nr, ne);
     return hipGetLastError();
   }
+  const int grid = std::min(t.num_cu, w.count);
+  if (harmonic && pos) STREAM_LAUNCH((m2l_fwd_whole_kernel<true, true>), grid, kWholeThreads, w.counter, t.fwdh, hr, he, pos, mass, Mw);
+  else if (harmonic) STREAM_LAUNCH((m2l_fwd_whole_kernel<true, false>), grid, kWholeThreads, w.counter, t.fwdh, hr, he, pos, mass, Mw);
+  else if (pos) STREAM_LAUNCH((m2l_fwd_whole_kernel<false, true>), grid, kWholeThreads, w.counter, t.fwdl, nr, ne, pos, mass, Mw);
+  else STREAM_LAUNCH((m2l_fwd_whole_kernel<false, false>), grid, kWholeThreads, w.counter, t.fwdl, nr, ne, pos, mass, Mw);
+#undef STREAM_LAUNCH
+  return hipGetLastError();
+}
+
+hipError_t launch_m2l_mfma(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc,
+                           const double* M, double* L, fmm_precision prec, int cfg, hipStream_t s) {
+  if (w.count == 0) return hipSuccess;
+  // (FMM_EXACT_SLICE runs through launch_m2l_slice, the streamed forms through launch_m2l_stream)
+  if (!mfma_config_supports(cfg, prec) || prec == FMM_EXACT_SLICE || mfma_config_streams(cfg)) return hipErrorInvalidValue;
+  const Config& c = kConfigs[cfg];
+  const int grid = std::min(t.num_cu, w.count);
+  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, w.counter);
   if (c.prec == FMM_SPLIT_FP32) {
     hipLaunchKernelGGL(m2l_fwd_split_kernel, dim3(grid), dim3(512), 0, s, w.items, w.count, w.counter,
                        d_desc, M, L, t.fwd_hi[2], t.fwd_lo[2], t.fwd_hi[3], t.fwd_lo[3], t.fwd_hi[4],
                        t.fwd_lo[4], t.lds_off, t.touch);
     return hipGetLastError();
   }
-  if (c.ldstab) {
-    if (c.ldstab == 2 && fuse) BL_LAUNCH(true, false, true, t.fwdl, hr0, he0);
-    else if (c.ldstab == 2) BL_LAUNCH(true, false, false, t.fwdl, hr0, he0);
-    else if (fuse) BL_LAUNCH(false, false, true, t.fwdl, hr0, he0);
-    else BL_LAUNCH(false, false, false, t.fwdl, hr0, he0);
-    return hipGetLastError();
-  }
-#undef BL_LAUNCH
 #define FWD_LAUNCH(W, PFV)                                                                         \
   hipLaunchKernelGGL((m2l_fwd_kernel<W, PFV>), dim3(grid), dim3(W * 64), 0, s, w.items, w.count,   \
                      w.counter, d_desc, M, L, t.fwd[2], t.fwd[3], t.fwd[4], t.lds_off, t.touch)
@@ -2054,43 +2150,6 @@ hipError_t launch_m2l_mfma(const MfmaTables& t, const WorkList& w, const DevDesc
   else if (c.waves == 4) FWD_LAUNCH(4, false);
   else return hipErrorInvalidValue;
 #undef FWD_LAUNCH
-  return hipGetLastError();
-}
-
-int m2l_rounds(int p, bool harmonic) {
-  const int cr = harmonic ? (p + 1) * (p + 1) : ncomp(p);
-  return (cr + 1) / 2;
-}
-
-hipError_t launch_m2l_round_split(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc,
-                                  int64_t nsub, const int* d_base, const double* M, double* L,
-                                  double* part, fmm_precision prec, int cfg, hipStream_t s) {
-  if (w.count == 0) return hipSuccess;
-  if (!mfma_config_supports(cfg, prec) || !mfma_config_fusable(cfg) ||
-      w.count > kMaxSplitSlots || nsub > kMaxSplitSubgrids)
-    return hipErrorInvalidValue;
-  const int grid = std::min(t.num_cu, w.count);
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, w.counter);
-  const Config& c = kConfigs[cfg];
-  const bool harm = c.prec == FMM_FP64_HARMONIC;
-  if (harm)
-    hipLaunchKernelGGL((m2l_fwd_round_kernel<true, true>), dim3(grid), dim3(kBlThreads), 0, s, w.items, w.count,
-                       w.counter, d_desc, M, part, t.fwdh[2], t.fwdh[3], t.fwdh[4], t.lds_off, t.touch,
-                       t.hround[2], t.hround[3], t.hround[4]);
-  else if (c.ldstab == 2)
-    hipLaunchKernelGGL((m2l_fwd_round_kernel<true, false>), dim3(grid), dim3(kBlThreads), 0, s, w.items, w.count,
-                       w.counter, d_desc, M, part, t.fwdl[2], t.fwdl[3], t.fwdl[4], t.lds_off, t.touch,
-                       nullptr, nullptr, nullptr);
-  else
-    hipLaunchKernelGGL((m2l_fwd_round_kernel<false, false>), dim3(grid), dim3(kBlThreads), 0, s, w.items, w.count,
-                       w.counter, d_desc, M, part, t.fwdl[2], t.fwdl[3], t.fwdl[4], t.lds_off, t.touch,
-                       nullptr, nullptr, nullptr);
-  if (harm)
-    hipLaunchKernelGGL((m2l_round_sum_kernel<true>), dim3((unsigned)nsub), dim3(kNTarget), 0, s, d_desc, d_base,
-                       part, L, t.hexp[2], t.hexp[3], t.hexp[4]);
-  else
-    hipLaunchKernelGGL((m2l_round_sum_kernel<false>), dim3((unsigned)nsub), dim3(kNTarget), 0, s, d_desc, d_base,
-                       part, L, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 

@@ -1,0 +1,63 @@
+"""The streamed M2L forward: whole sub-grids and each kind of part (two target
+planes, one plane, one tile) give the same bits, in both forms, and match the
+oracle. Batches from one sub-grid (tiles) over eighths and quarters to more
+sub-grids than compute units, mixed orders and masks or all alike."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+from paper_2304_11002_amd import fmm
+
+from _gpu_helpers import ensure_library, split_views, to_dev
+
+pytestmark = pytest.mark.gpu
+HARM, DENSE = fmm.FMM_FP64_HARMONIC, fmm.FMM_FP64
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+def _batch(n, p, uneven):
+    rng = np.random.default_rng([91, n, p])
+    ps = np.full(n, p) if p else np.arange(n) % 3 + 2
+    masks = [synth.random_mask(rng) if uneven else fmm.FULL_MASK for _ in range(n)]
+    lh = rng.integers(0, 3, n) if uneven else np.zeros(n, int)
+    desc, m_el, l_el = fmm.make_descriptors(ps, lh, masks)
+    return desc, rng.standard_normal(m_el), l_el
+
+
+@pytest.mark.parametrize("n,p,uneven", [(1, 2, False), (1, 3, False), (1, 4, True), (5, 0, True), (30, 3, False),
+                                        (47, 0, True), (100, 2, False), (70, 4, True), (263, 0, True), (300, 3, False)])
+@pytest.mark.parametrize("form", [HARM, DENSE])
+def test_parts_match_whole_subgrids_and_the_oracle(torch, form, n, p, uneven):
+    ensure_library()
+    desc, M, l_el = _batch(n, p, uneven)
+    dM = to_dev(M)
+    outs = {}
+    with fmm.Context(0) as ctx:
+        for opt in (-1, 0, 1):
+            ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, opt)
+            for rep in range(2):       # the second call finds the counter as the first left it
+                outs[opt, rep] = torch.full((l_el,), float("nan"), dtype=torch.float64, device="cuda")
+                ctx.m2l(desc, dM, outs[opt, rep], form)
+        ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, -1)
+        if form == DENSE:              # four-block products, tables loaded per wave
+            ctx.set_option(fmm.FMM_OPT_TILE_CONFIG, 3)
+            outs["per wave"] = torch.full((l_el,), float("nan"), dtype=torch.float64, device="cuda")
+            ctx.m2l(desc, dM, outs["per wave"], form)
+        torch.cuda.synchronize()
+    want = outs[0, 0]
+    assert bool(torch.isfinite(want).all())
+    for k, v in outs.items():
+        assert torch.equal(v, want), k
+    Mv, Lv = split_views(M, desc, "M"), split_views(want.cpu().numpy(), desc, "L")
+    for b in sorted({0, n // 2, n - 1}):
+        q, h, mask = int(desc["p"][b]), 2.0 ** -int(desc["log2_inv_h"][b]), int(desc["mask"][b])
+        err = np.abs(Lv[b] - O.m2l(Mv[b], q, h, mask)) / O.m2l_abs(Mv[b], q, h, mask)
+        assert err.max() <= TOL, "sub-grid %d (p=%d): %.3g" % (b, q, err.max())
