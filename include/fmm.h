@@ -243,10 +243,12 @@ fmm_status fmm_p2m_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
  * Each workgroup computes a sub-grid's mass gradients itself, during the
  * M2L adjoint of the sub-grid after it, so the HBM-bound gradient work of
  * some workgroups overlaps the matrix work of the others. The single launch
- * is used for batches of more sub-grids than the GPU has compute units, with
- * ppc = 8, 16-byte aligned pos and dmass and even part_off; otherwise, and
- * with FMM_OPT_M2L_KERNEL = 1, the call runs the two adjoints one after the
- * other, with the same results. FMM_OPT_ADJOINT_FORM applies. */
+ * is used, with ppc = 8, 16-byte aligned pos and dmass and even part_off, for
+ * batches of more sub-grids than the GPU has compute units for which it is
+ * expected to be faster than the two adjoints in turn (the M2L adjoint then by
+ * sub-grids or by output components); otherwise, and with
+ * FMM_OPT_M2L_KERNEL = 1, the call runs the two adjoints one after the other,
+ * with the same results. FMM_OPT_ADJOINT_FORM applies. */
 fmm_status fmm_m2l_p2m_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
                                 const double* pos, int32_t ppc, const double* dL,
                                 double* dM, double* dmass, void* stream);

@@ -111,6 +111,8 @@ struct DescEntry {
   WorkList whole[2];
   WorkList parts[2];
   StreamPlan plan[2];
+  WorkList rounds[2];             // adjoint: the sub-grids' rounds, where planned
+  AdjointPlan adjoint[2];
   bool part_even = true;          // every part_off even: particle blocks 16-byte aligned
   int tuned[4] = {-1, -1, -1, -1};   // autotuned configuration per precision
   // FMM_EXACT_SLICE: the sub-grids' slice planes and exponents (one allocation)
@@ -331,7 +333,7 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     ids[desc[b].p].push_back((int)b);
     if (desc[b].part_off & 1) e->part_even = false;
   }
-  std::vector<WorkItem> items[2], parts[2];   // dense, harmonic
+  std::vector<WorkItem> items[2], parts[2], rounds[2];   // dense, harmonic
   StreamPlan plan[2];
   for (int f = 0; f < 2; ++f) {
     items[f].resize((size_t)nsub);
@@ -342,6 +344,13 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
       parts[f].resize((size_t)max_parts(nsub));
       parts[f].resize((size_t)split_items(parts[f].data(), nsub, ctx->mfma.num_cu));
     }
+    e->adjoint[f] = plan_adjoint(items[f].data(), nsub, ctx->mfma.num_cu, f == 1);
+    if (e->adjoint[f].rounds)
+      for (const WorkItem& it : items[f]) {
+        uint32_t sets[kMaxRounds];
+        const int n = adjoint_round_sets(desc[it.sub].p, f == 1, sets);
+        for (int k = 0; k < n; ++k) rounds[f].push_back(WorkItem{it.sub, (int32_t)sets[k]});
+      }
     whole_items(items[f].data(), nsub);
   }
   size_t off_desc = 0;
@@ -351,12 +360,14 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     off_ids[p] = off;
     off = align_up(off + sizeof(int) * ids[p].size(), 256);
   }
-  size_t off_work[2], off_parts[2], off_counter[2], off_zero[2];
+  size_t off_work[2], off_parts[2], off_rounds[2], off_counter[2], off_zero[2];
   for (int f = 0; f < 2; ++f) {
     off_work[f] = off;
     off = align_up(off + sizeof(WorkItem) * items[f].size(), 256);
     off_parts[f] = off;
     off = align_up(off + sizeof(WorkItem) * parts[f].size(), 256);
+    off_rounds[f] = off;
+    off = align_up(off + sizeof(WorkItem) * rounds[f].size(), 256);
     off_counter[f] = off;
     off = align_up(off + 256, 256);
     off_zero[f] = off;
@@ -372,6 +383,7 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
   for (int f = 0; f < 2; ++f) {
     std::memcpy(hp + off_work[f], items[f].data(), sizeof(WorkItem) * items[f].size());
     std::memcpy(hp + off_parts[f], parts[f].data(), sizeof(WorkItem) * parts[f].size());
+    std::memcpy(hp + off_rounds[f], rounds[f].data(), sizeof(WorkItem) * rounds[f].size());
   }
   char* dp = static_cast<char*>(e->dev);
   e->d_desc = reinterpret_cast<DevDesc*>(dp + off_desc);
@@ -391,6 +403,10 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     e->parts[f].counter = e->whole[f].counter;
     e->parts[f].parts = true;
     e->plan[f] = plan[f];
+    e->rounds[f].items = reinterpret_cast<const WorkItem*>(dp + off_rounds[f]);
+    e->rounds[f].count = (int)rounds[f].size();
+    e->rounds[f].counter = e->whole[f].counter;
+    e->rounds[f].parts = true;
   }
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->ready, hipEventDisableTiming));
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->last_launch, hipEventDisableTiming));
@@ -974,6 +990,10 @@ fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, cons
   return mark_used(ctx, e, s);
 }
 
+static const WorkList& adjoint_list(const DescEntry* e, bool harmonic) {
+  return e->adjoint[harmonic].rounds ? e->rounds[harmonic] : e->whole[harmonic];
+}
+
 fmm_status fmm_m2l_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, const double* dL,
                             double* dM, void* stream) {
   CHECK_OK(check_ctx(ctx));
@@ -992,7 +1012,7 @@ fmm_status fmm_m2l_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
   if (ctx->m2l_kernel == 1) {
     CHECK_OK(run_ref(ctx, e, true, dL, dM, s));
   } else {
-    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, work_for(e, ctx->adjoint_form == 1), e->d_desc, dL, dM,
+    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, adjoint_list(e, ctx->adjoint_form == 1), e->d_desc, dL, dM,
                                           ctx->adjoint_form == 1, s));
   }
   return mark_used(ctx, e, s);
@@ -1017,13 +1037,12 @@ fmm_status fmm_m2l_p2m_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t n
   DescEntry* e = nullptr;
   CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
   const bool aligned = ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(dmass)) & 15u) == 0;
-  if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && nsub > ctx->mfma.num_cu) {
-    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, work_for(e, ctx->adjoint_form == 1), e->d_desc, dL, dM,
-                                          ctx->adjoint_form == 1, s, pos, dmass));
+  const bool harm = ctx->adjoint_form == 1;
+  if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && e->adjoint[harm].fuse) {
+    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, e->whole[harm], e->d_desc, dL, dM, harm, s, pos, dmass));
   } else {
     if (ctx->m2l_kernel == 1) CHECK_OK(run_ref(ctx, e, true, dL, dM, s));
-    else HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, work_for(e, ctx->adjoint_form == 1), e->d_desc, dL, dM,
-                                               ctx->adjoint_form == 1, s));
+    else HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, adjoint_list(e, harm), e->d_desc, dL, dM, harm, s));
     HIP_TRY(ctx, launch_p2m_backward(e->d_desc, nsub, e->d_ids, e->count, pos, ppc, dM, dmass, e->part_even, s));
   }
   return mark_used(ctx, e, s);

@@ -7,18 +7,19 @@
 
 namespace fmm {
 
-// One work item: a sub-grid, or (forward) a part of its targets. Every output
-// element has exactly one writer.
+// One work item: a sub-grid, a part of its targets (streamed forward) or some of
+// its rounds (adjoint). Every output element has exactly one writer.
 struct WorkItem {
   int32_t sub;    // descriptor index
-  int32_t part;   // level | index << 4: part `index` of the kLevelParts[level] the sub-grid is cut into
+  int32_t part;   // level | index << 4: part `index` of the kLevelParts[level] the sub-grid is cut into;
+                  // adjoint: a bit per round, 0 for all
 };
 
 struct WorkList {
   const WorkItem* items = nullptr;   // device, longest first
   int count = 0;
   unsigned* counter = nullptr;       // device work counter, reset by every launch that uses it
-  bool parts = false;                // the items are parts of sub-grids (streamed forward)
+  bool parts = false;                // the items are parts (streamed forward) or rounds (adjoint) of sub-grids
 };
 
 // Host: the sub-grids in out[0 .. nsub), longest first (equal costs by
@@ -46,6 +47,18 @@ constexpr int64_t kMaxExtraItems = 8192;
 constexpr int64_t kMaxSplitSubgrids = 256;   // batches that FMM_OPT_ROUND_SPLIT = 1 applies to
 constexpr int64_t max_parts(int64_t n) { return n * kLevelParts[0] + kMaxExtraItems; }
 int64_t split_items(WorkItem* items, int64_t n, int num_cu);
+
+// The same for the adjoint: by rounds or whole sub-grids, and with the mass
+// gradients in the same launch (whole sub-grids) or in one of their own.
+struct AdjointPlan {
+  bool rounds = false, fuse = false;
+};
+constexpr int64_t kMaxRoundSubgrids = 4096;   // above: less than 1% to win
+AdjointPlan plan_adjoint(const WorkItem* items, int64_t n, int num_cu, bool harmonic);
+// The sets of rounds (a bit each) whose output components no other set writes;
+// returns their number.
+constexpr int kMaxRounds = 18;      // dense p = 4
+int adjoint_round_sets(int p, bool harmonic, uint32_t sets[kMaxRounds]);
 
 constexpr int kQuads = kNStencil / 4;   // offsets are consumed four at a time
 static_assert(kNStencil % 4 == 0, "offset quads");

@@ -1117,8 +1117,8 @@ __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __re
                                             double* dM, const double* __restrict__ Bp,
                                             int npairs, const int* s_gs,
                                             const uint32_t* __restrict__ ptouch, double* smem,
-                                            const int4* __restrict__ pairs, const HFold* __restrict__ hfold = nullptr,
-                                            const HOut* __restrict__ hout = nullptr, Hook hook = Hook()) {
+                                            const int4* __restrict__ pairs, const HFold* __restrict__ hfold,
+                                            const HOut* __restrict__ hout, Hook hook, uint32_t rounds) {
   constexpr int C = ncomp(P);
   constexpr int CR = HARM ? (P + 1) * (P + 1) : C;   // reduced components
   constexpr int KC = (CR + 3) / 4;    // dL component chunks of 4 (the reduction)
@@ -1174,6 +1174,7 @@ __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __re
       const_cast<uint32_t*>(ptouch + wave * npairs), (short)0, npairs * 4, 0x00020000);
   double* out = dM + d.m_off;
   for (int r = 0; r < ROUNDS; ++r) {
+    if (!((rounds >> r) & 1u)) continue;
     __syncthreads();
     if (hook.wants(r, ROUNDS)) {
       hook.run(smem);
@@ -1345,6 +1346,11 @@ struct GradHook {
   __device__ void run(double* lds) const { grads(prev, lds); }
 };
 
+// Work items are sub-grids, or some rounds of one (`part`: a bit per round, 0 for
+// all): each round writes output components of its own, so a batch that cannot
+// fill the GPU is spread over it by rounds, with the same bits. With a counter
+// the workgroups take items from it; without, workgroup i runs item i.
+//
 // FUSE: the kernel also computes the mass gradients (the P2M adjoint of the
 // sub-grid's dM, 8 particles per cell). A workgroup computes them for its
 // previous item, whose dM it has written, at the top of round (workgroup index
@@ -1381,11 +1387,16 @@ __global__ void __launch_bounds__(kBwdThreads) m2l_bwd_kernel(
   // (LDS operations complete in order; the staged values are read after the
   // barrier at the top of the item loop)
   for (;;) {
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
+    if (counter && threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
     __syncthreads();
-    const int item = s_item;
-    if (item >= count) break;
+    const int item = counter ? s_item : (int)blockIdx.x;
+    if (item >= count) {
+      // the last of the numbers past the items clears the counter for the next launch
+      if (counter && threadIdx.x == 0 && item == count + (int)gridDim.x - 1) *counter = 0u;
+      break;
+    }
     const DevDesc d = desc[items[item].sub];
+    const uint32_t rounds = items[item].part ? (uint32_t)items[item].part : ~0u;
     const bool full = d.mask == kFullMask;
     const auto hook = [&]() {
       if constexpr (FUSE) return GradHook<decltype(grads)>{prev, grads};
@@ -1393,21 +1404,22 @@ __global__ void __launch_bounds__(kBwdThreads) m2l_bwd_kernel(
     }();
     switch (d.p) {
       case 2:
-        if (full) bwd_subgrid<2, true, HARM>(d, dL, dM, B2, npairs, s_gs, ptouch, smem, pairs, hf2, ho2, hook);
-        else bwd_subgrid<2, false, HARM>(d, dL, dM, B2, npairs, s_gs, ptouch, smem, pairs, hf2, ho2, hook);
+        if (full) bwd_subgrid<2, true, HARM>(d, dL, dM, B2, npairs, s_gs, ptouch, smem, pairs, hf2, ho2, hook, rounds);
+        else bwd_subgrid<2, false, HARM>(d, dL, dM, B2, npairs, s_gs, ptouch, smem, pairs, hf2, ho2, hook, rounds);
         break;
       case 3:
-        if (full) bwd_subgrid<3, true, HARM>(d, dL, dM, B3, npairs, s_gs, ptouch, smem, pairs, hf3, ho3, hook);
-        else bwd_subgrid<3, false, HARM>(d, dL, dM, B3, npairs, s_gs, ptouch, smem, pairs, hf3, ho3, hook);
+        if (full) bwd_subgrid<3, true, HARM>(d, dL, dM, B3, npairs, s_gs, ptouch, smem, pairs, hf3, ho3, hook, rounds);
+        else bwd_subgrid<3, false, HARM>(d, dL, dM, B3, npairs, s_gs, ptouch, smem, pairs, hf3, ho3, hook, rounds);
         break;
       case 4:
-        if (full) bwd_subgrid<4, true, HARM>(d, dL, dM, B4, npairs, s_gs, ptouch, smem, pairs, hf4, ho4, hook);
-        else bwd_subgrid<4, false, HARM>(d, dL, dM, B4, npairs, s_gs, ptouch, smem, pairs, hf4, ho4, hook);
+        if (full) bwd_subgrid<4, true, HARM>(d, dL, dM, B4, npairs, s_gs, ptouch, smem, pairs, hf4, ho4, hook, rounds);
+        else bwd_subgrid<4, false, HARM>(d, dL, dM, B4, npairs, s_gs, ptouch, smem, pairs, hf4, ho4, hook, rounds);
         break;
       default: break;
     }
     __syncthreads();
     prev = item;
+    if (!counter) break;
   }
   if constexpr (FUSE) {
     if (prev >= 0) {
@@ -1697,6 +1709,29 @@ StreamPlan plan_stream(const WorkItem* items, int64_t n, int num_cu) {
   return p;
 }
 
+// The adjoint's units (p = 3: 28,544 harmonic, 44,600 dense, 1230 and 1660 us of a
+// workgroup). By rounds, a batch takes its work spread evenly (harmonic: 1.04 of
+// it, each round folds dL anew) plus about an eighth of its longest sub-grid:
+// harmonic p = 3, whole against rounds: 1 sub-grid 1160 and 166 us, 256 1379 and
+// 1459, 300 2505 and 1760, 512 2631 and 2776, 600 3795 and 3202, 2048 9853 and
+// 10307; dense, 19 of mixed p 5170 and 326, 900 alike 6655 and 5854. Mass gradients
+// cost 120 us inside a sub-grid's launch, and 1.14 us of the whole GPU per sub-grid
+// in a launch of their own (600 harmonic: 4121 us inside, 3815 apart; 900: 5447 and
+// 5746).
+AdjointPlan plan_adjoint(const WorkItem* items, int64_t n, int num_cu, bool harmonic) {
+  constexpr int64_t kGradsInside = 2800, kGradsApart = 6800;
+  if (n == 0) return AdjointPlan{};
+  int64_t total = 0;
+  for (int64_t i = 0; i < n; ++i) total += items[i].part;
+  const int64_t whole = makespan(items, n, num_cu, total, 0);
+  const int64_t split = (total * (harmonic ? 104 : 100) / num_cu + 12 * (int64_t)items[0].part) / 100;
+  AdjointPlan p;
+  p.rounds = split < whole && n <= kMaxRoundSubgrids;
+  p.fuse = n > num_cu && makespan(items, n, num_cu, total, kGradsInside) <
+                             (p.rounds ? split : whole) + n * kGradsApart / num_cu;
+  return p;
+}
+
 // Where the levels' lines lie (costs c in sub-grids, harmonic p = 3, 256 compute
 // units, us): a sub-grid goes in eighths while a quarter of it on a compute unit
 // of its own takes longer than the whole batch on a full GPU. 32 alike: 288 in
@@ -1929,6 +1964,42 @@ bool build_harmonic(int p, HostHarmonic* out) {
 
 }  // namespace
 
+int adjoint_round_sets(int p, bool harmonic, uint32_t sets[kMaxRounds]) {
+  if (!harmonic) {
+    const int n = (ncomp(p) + 1) / 2;
+    for (int r = 0; r < n; ++r) sets[r] = 1u << r;
+    return n;
+  }
+  // rounds that add to a component of an earlier round go with it, in order
+  static const std::vector<std::vector<uint32_t>> all = [] {
+    std::vector<std::vector<uint32_t>> v(kMaxP + 1);
+    for (int q = 2; q <= kMaxP; ++q) {
+      HostHarmonic hh;
+      if (!build_harmonic(q, &hh)) continue;
+      for (size_t r = 0; r < hh.outs.size(); ++r) {
+        uint32_t set = 1u << r;
+        for (size_t e = 0; e < v[q].size();) {
+          bool shares = false;
+          for (size_t o = 0; o < r; ++o)
+            if ((v[q][e] >> o) & 1u)
+              for (int a = 0; a < hh.outs[r].nout; ++a)
+                for (int b = 0; b < hh.outs[o].nout; ++b) shares |= hh.outs[r].comp[a] == hh.outs[o].comp[b];
+          if (shares) {
+            set |= v[q][e];
+            v[q].erase(v[q].begin() + e);
+          } else {
+            ++e;
+          }
+        }
+        v[q].push_back(set);
+      }
+    }
+    return v;
+  }();
+  for (size_t i = 0; i < all[p].size(); ++i) sets[i] = all[p][i];
+  return (int)all[p].size();
+}
+
 bool harmonic_rounds_host(int p, std::vector<HRound>* rounds) {
   HostHarmonic hh;
   if (!build_harmonic(p, &hh)) return false;
@@ -2157,14 +2228,14 @@ hipError_t launch_m2l_mfma_backward(const MfmaTables& t, const WorkList& w, cons
                                     const double* dL, double* dM, bool harmonic, hipStream_t s,
                                     const double* pos, double* dmass) {
   if (w.count == 0) return hipSuccess;
-  if ((pos == nullptr) != (dmass == nullptr)) return hipErrorInvalidValue;
+  if ((pos == nullptr) != (dmass == nullptr) || (pos && w.parts)) return hipErrorInvalidValue;
   const int grid = std::min(t.num_cu, w.count);
-  hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, w.counter);
+  unsigned* counter = w.count > grid ? w.counter : nullptr;
   const HFold* nf = nullptr;
   const HOut* no = nullptr;
 #define BWD_LAUNCH(HARMV, FUSEV, B, HF0, HF1, HF2, HO0, HO1, HO2)                                  \
   hipLaunchKernelGGL((m2l_bwd_kernel<HARMV, FUSEV>), dim3(grid), dim3(kBwdThreads), 0, s, w.items,  \
-                     w.count, w.counter, d_desc, dL, dM, B[2], B[3], B[4], t.pairs, t.npairs,       \
+                     w.count, counter, d_desc, dL, dM, B[2], B[3], B[4], t.pairs, t.npairs,         \
                      t.gstart, t.ptouch, HF0, HF1, HF2, HO0, HO1, HO2, pos, dmass)
   if (harmonic && pos)
     BWD_LAUNCH(true, true, t.bwdh, t.hfold[2], t.hfold[3], t.hfold[4], t.hout[2], t.hout[3], t.hout[4]);

@@ -61,3 +61,33 @@ def test_parts_match_whole_subgrids_and_the_oracle(torch, form, n, p, uneven):
         q, h, mask = int(desc["p"][b]), 2.0 ** -int(desc["log2_inv_h"][b]), int(desc["mask"][b])
         err = np.abs(Lv[b] - O.m2l(Mv[b], q, h, mask)) / O.m2l_abs(Mv[b], q, h, mask)
         assert err.max() <= TOL, "sub-grid %d (p=%d): %.3g" % (b, q, err.max())
+
+
+@pytest.mark.parametrize("uneven", [False, True])
+@pytest.mark.parametrize("p", [2, 3, 4])
+@pytest.mark.parametrize("form", [0, 1])
+def test_adjoint_by_rounds_matches_whole_subgrids_and_the_oracle(torch, form, p, uneven):
+    # as many equal sub-grids as compute units run whole; the first few of them by
+    # rounds; more of them than compute units by rounds from a work counter
+    ensure_library()
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    mask = synth.random_mask(np.random.default_rng(17)) if uneven else fmm.FULL_MASK
+    desc, m_el, l_el = fmm.make_descriptors(np.full(ncu, p), np.ones(ncu, int), [mask] * ncu)
+    nm, nl = m_el // ncu, l_el // ncu
+    g = torch.Generator(device="cuda")
+    g.manual_seed(29)
+    dL = torch.randn(l_el, dtype=torch.float64, device="cuda", generator=g)
+    whole = torch.full((m_el,), float("nan"), dtype=torch.float64, device="cuda")
+    with fmm.Context(0) as ctx:
+        ctx.set_option(fmm.FMM_OPT_ADJOINT_FORM, form)
+        ctx.m2l_backward(desc, dL, whole)
+        for n in (1, 2, 61):
+            for rep in range(2):
+                dM = torch.full((n * nm,), float("nan"), dtype=torch.float64, device="cuda")
+                ctx.m2l_backward(desc[:n], dL[:n * nl], dM)
+                torch.cuda.synchronize()
+                assert torch.equal(dM, whole[:n * nm]), (n, rep)
+    W = split_views(dL[:nl].cpu().numpy(), desc[:1], "L")[0]
+    want, scale = O.m2l_adjoint(W, p, 0.5, mask), O.m2l_adjoint_abs(W, p, 0.5, mask)
+    err = np.abs(split_views(whole[:nm].cpu().numpy(), desc[:1], "M")[0] - want)
+    assert np.all(err <= TOL * scale)
