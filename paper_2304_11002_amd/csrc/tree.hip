@@ -19,12 +19,12 @@
 //
 // IL(t) depends only on the parity sigma of t: 231 offsets per parity, all
 // inside the shell 5 <= |d|^2 <= 36 with |d_i| <= 5. The level M2L kernel
-// gives each of its 8 waves one parity class of an 8^3 target block, so a
-// wave's 64 targets (four 16-cell tiles, one per plane of that z parity) share
-// one offset list and one table stream: v_mfma_f64_4x4x4_4b over
-// [16 cells x 4 offsets] x [4 offsets x 4 columns] as in the single-level
-// kernels, with the 18^3 source window of two moment components per round in
-// LDS. The harmonic form (as FMM_FP64_HARMONIC: T_d is harmonic in both
+// gives each of its waves one parity class of an 8^3 target block (or of one of
+// its planes), so a wave's 16-cell tiles, one per plane of that z parity, share
+// one offset list and one table stream: [16 cells x 4 offsets] x [4 offsets x
+// columns] on v_mfma_f64_16x16x4 and 4x4x4_4b as in the single-level kernels,
+// with the source window of two moment components per round in LDS. The harmonic
+// form (as FMM_FP64_HARMONIC: T_d is harmonic in both
 // indices, so the moments fold onto the (p+1)^2 components with kz <= 1 and
 // only those columns of L are computed, then expanded) uses the single-level
 // form's fold plan per round and expansion of L.
@@ -41,12 +41,16 @@ namespace {
 constexpr int kTreeW = 18;                         // window (y, z): block cells -5 .. 12
 constexpr int kTreeList = 231;                     // interaction-list length per parity
 constexpr int kTreeQuads = (kTreeList + 3) / 4;    // 58 (the last quad has one empty slot)
-constexpr int kTreeThreads = 512;
 constexpr int kTreeMaxLevels = 8;
-constexpr int kTreeWideMin = 64;                   // levels of at least this many cells per axis: NBLK = 2
+constexpr int kTreeWideMin = 64;                   // levels of at least this many cells per axis: wide workgroups
+
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double mfma4(double a, double b, double c) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ v4d mfma16(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // b^i / i! per axis for i <= P
@@ -172,7 +176,7 @@ __global__ void __launch_bounds__(256) l2l_kernel(const double* __restrict__ Lp,
 }
 
 // Tables of the level kernel, per order p:
-//   B[sigma][round][quad][c2][group][kk * 4 + j] = T_d[2 round + c2][4 group + j]
+//   B[sigma][round][quad][group][kk * 4 + j][c2] = T_d[2 round + c2][4 group + j]
 // at unit spacing, d = the kk-th offset of the quad in sigma's list (zero for
 // the empty slot, k >= C or n >= C). Built from the canonical [892][C][C]
 // tables with the map sidx[sigma][quad][kk] (stencil index or -1).
@@ -183,9 +187,9 @@ __global__ void pack_tree_kernel(const double* __restrict__ T, int C, const int*
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     int64_t r_ = e;
+    const int c2 = (int)(r_ % 2); r_ /= 2;
     const int v = (int)(r_ % 16); r_ /= 16;
     const int g = (int)(r_ % NG); r_ /= NG;
-    const int c2 = (int)(r_ % 2); r_ /= 2;
     const int q = (int)(r_ % kTreeQuads); r_ /= kTreeQuads;
     const int r = (int)(r_ % R);
     const int sigma = (int)(r_ / R);
@@ -196,7 +200,7 @@ __global__ void pack_tree_kernel(const double* __restrict__ T, int C, const int*
   }
 }
 
-// Harmonic tables: Bh[sigma][round][quad][c2][group][kk * 4 + j] =
+// Harmonic tables: Bh[sigma][round][quad][group][kk * 4 + j][c2] =
 // T_d[rowk[2 round + c2]][colk[4 group + j]] (zero where a map is -1).
 struct TreeHMaps {
   int rowk[32];
@@ -208,9 +212,9 @@ __global__ void pack_tree_h_kernel(const double* __restrict__ T, int C, int R, i
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     int64_t r_ = e;
+    const int c2 = (int)(r_ % 2); r_ /= 2;
     const int v = (int)(r_ % 16); r_ /= 16;
     const int g = (int)(r_ % NG); r_ /= NG;
-    const int c2 = (int)(r_ % 2); r_ /= 2;
     const int q = (int)(r_ % kTreeQuads); r_ /= kTreeQuads;
     const int r = (int)(r_ % R);
     const int sigma = (int)(r_ / R);
@@ -232,25 +236,59 @@ struct TreeLevels {
   int64_t off[kTreeMaxLevels];     // element offset of the level in M and L
 };
 
-// NBLK: 8^3 target blocks per workgroup, side by side in x (the table operands
-// of a quad then serve 4 NBLK tiles per wave)
-template <int P, bool HARM, int NBLK>
-__global__ void __launch_bounds__(kTreeThreads) m2l_level_kernel(
+// Columns of a tile: N16 sixteens on 16x16x4 products, then N4 groups of four on
+// 4x4x4 products.
+template <int P, bool HARM>
+struct TreeCols {
+  static constexpr int CR = HARM ? (P + 1) * (P + 1) : ncomp(P);   // contracted components (rows and columns)
+  static constexpr int NG = (CR + 3) / 4;
+  static constexpr int N16 = CR / 16, N4 = NG - 4 * N16;
+};
+// A workgroup's targets. Wide: two 8^3 blocks side by side in x, each wave one
+// parity class of both (8 tiles; one workgroup per CU). Plane: one plane of one
+// block, each wave one of the plane's four parity classes (one tile; two
+// workgroups per CU).
+template <bool WIDE>
+struct TreeShape {
+  static constexpr int NBLK = WIDE ? 2 : 1;
+  static constexpr int NT = WIDE ? 512 : 256;
+  static constexpr int TPW = WIDE ? 8 : 1;
+  static constexpr int WX = 8 * NBLK + 10, WZ = WIDE ? kTreeW : 11;   // window cells in x and z
+  static constexpr int CELLS = WX * kTreeW * WZ;
+  static constexpr int OUT = WIDE ? kNTarget : 64;                    // targets of a write-out pass
+  static constexpr int AD = WIDE ? 1 : 3, AR = AD + 1;                // window operands: quads ahead, sets
+};
+constexpr int kTreeOffPad = 12;   // quads past a list whose offsets are read ahead
+constexpr int kTreePad = 8 * 9 * 32;   // and doubles past the tables
+
+// What bounds it: the matrix units, at sizes that fill them (wide: one b128 table
+// load per four columns or sixteen serves 8 tiles), and on the coarse levels the
+// chain of one tile's products, 2 per quad and round, so the work of a block is
+// spread over eight workgroups (planes) and table operands are loaded up to eight
+// quads ahead. The window stays in LDS; both shapes take each sum in the order of
+// the quads. All levels, harmonic p = 3, against one shape of 4x4x4 products with
+// two 8-byte table loads per four columns: n = 8 327 -> 53 us, 32 354 -> 151,
+// 64 929 -> 707, 128 5119 -> 4592 (p = 4: 16.5 -> 13.2 ms, dense 26.6 -> 20.5).
+template <int P, bool HARM, bool WIDE>
+__global__ void __launch_bounds__(TreeShape<WIDE>::NT, WIDE ? 1 : 2) m2l_level_kernel(
     const double* __restrict__ Mall, double* __restrict__ Lall, TreeLevels lv,
     const double* __restrict__ B, const int* __restrict__ doff, const HRound* __restrict__ hround,
     const HExp* __restrict__ hexp) {
-  constexpr int C = ncomp(P);
-  constexpr int CR = HARM ? (P + 1) * (P + 1) : C;   // contracted components (rows and columns)
-  constexpr int NG = (CR + 3) / 4;
+  using S = TreeShape<WIDE>;
+  using F = TreeCols<P, HARM>;
+  constexpr int C = ncomp(P), CR = F::CR, NG = F::NG;
   constexpr int ROUNDS = (CR + 1) / 2;
-  constexpr int WX = 8 * NBLK + 10;                   // window cells in x
-  constexpr int WCELLS = WX * kTreeW * kTreeW;
-  constexpr int STAGE = (WCELLS + kTreeThreads - 1) / kTreeThreads;
-  constexpr int TPW = 4 * NBLK;                       // 16-cell tiles per wave
-  // the window, and afterwards (harmonic form) the harmonic columns of the blocks
-  constexpr int SMEM = HARM && NBLK * kNTarget * CR / 2 > WCELLS ? NBLK * kNTarget * CR / 2 : WCELLS;
+  constexpr int NBLK = S::NBLK, NT = S::NT, TPW = S::TPW, WX = S::WX, AD = S::AD, AR = S::AR;
+  constexpr int WCELLS = S::CELLS;
+  constexpr int STAGE = (WCELLS + NT - 1) / NT;
+  constexpr int K16 = F::N16 > 0 ? F::N16 : 1, K4 = F::N4 > 0 ? F::N4 : 1;
+  constexpr int U = WIDE ? 2 : F::N16 + F::N4 == 1 ? 8 : 4;   // quads of table operands in flight
+  static_assert(U % AR == 0 && U + AD <= kTreeOffPad && U * NG * 32 <= kTreePad, "read ahead");
+  constexpr int CS = CR | 1;                          // column stride of a cell in the write-out
+  // the window, and afterwards the columns of a block (or plane)
+  constexpr int SMEM = S::OUT * CS / 2 + 1 > WCELLS ? S::OUT * CS / 2 + 1 : WCELLS;
   __shared__ double2 smem[SMEM];
-  __shared__ int s_doff[8 * kTreeQuads * 4];
+  __shared__ short s_doff[(8 * kTreeQuads + kTreeOffPad) * 4];
   int li = 0;
   while (li + 1 < lv.nlev && (int)blockIdx.x >= lv.first[li + 1]) ++li;
   const int n = lv.n[li], lg = lv.lg[li];
@@ -258,45 +296,57 @@ __global__ void __launch_bounds__(kTreeThreads) m2l_level_kernel(
   double* __restrict__ L = Lall + lv.off[li];
   const int nb = n >= 8 ? n / 8 : 1;
   const int nbx = n >= 8 * NBLK ? n / (8 * NBLK) : 1;
-  const int blk = (int)blockIdx.x - lv.first[li];
+  const int planes = WIDE ? 1 : n < 8 ? n : 8;
+  const int blk = ((int)blockIdx.x - lv.first[li]) / planes;
+  const int plane = ((int)blockIdx.x - lv.first[li]) % planes;   // of the block (Plane)
   const int B0x = 8 * NBLK * (blk % nbx), B0y = 8 * ((blk / nbx) % nb), B0z = 8 * (blk / (nbx * nb));
+  const int W0z = B0z + (WIDE ? 0 : plane) - 5;                  // the window's first plane
   const int64_t n3 = (int64_t)n * n * n;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // parity class of this wave
-  const int sx = wave & 1, sy = (wave >> 1) & 1, sz = wave >> 2;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sigma = WIDE ? wave : wave + 4 * (plane & 1);        // parity class of this wave
+  const int sx = sigma & 1, sy = (sigma >> 1) & 1, sz = sigma >> 2;
   const int kk = lane >> 4, ci = lane & 15;
   // offsets of the lists, packed (dx + 8) | (dy + 8) << 5 | (dz + 8) << 10, as window deltas
-  for (int i = tid; i < 8 * kTreeQuads * 4; i += kTreeThreads) {
-    const int v = doff[i];
-    s_doff[i] = ((v & 31) - 8) + WX * (((v >> 5) & 31) - 8) + WX * kTreeW * (((v >> 10) & 31) - 8);
+  for (int i = tid; i < (8 * kTreeQuads + kTreeOffPad) * 4; i += NT) {
+    const int v = i < 8 * kTreeQuads * 4 ? doff[i] : 8 | (8 << 5) | (8 << 10);
+    s_doff[i] = (short)(((v & 31) - 8) + WX * (((v >> 5) & 31) - 8) + WX * kTreeW * (((v >> 10) & 31) - 8));
   }
 
   // tile t: block t / 4, plane z = 2 (t % 4) + sz, cells (8 (t / 4) + 2 (ci & 3) + sx, 2 (ci >> 2) + sy)
+  auto tile_z = [&](int t) { return WIDE ? 2 * (t & 3) + sz : plane; };
   int abase[TPW];
 #pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int z = 2 * (t & 3) + sz, x = 8 * (t >> 2) + 2 * (ci & 3) + sx, y = 2 * (ci >> 2) + sy;
-    abase[t] = (x + 5) + WX * (y + 5) + WX * kTreeW * (z + 5);
-  }
-  double acc[TPW][NG];
-#pragma unroll
   for (int t = 0; t < TPW; ++t)
+    abase[t] = (8 * (t >> 2) + 2 * (ci & 3) + sx + 5) + WX * (2 * (ci >> 2) + sy + 5) +
+               WX * kTreeW * ((WIDE ? tile_z(t) : 0) + 5);
+  v4d acc16[TPW][K16];
+  double acc4[TPW][K4];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) acc[t][g] = 0.0;
+  for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+    for (int g = 0; g < F::N16; ++g) acc16[t][g] = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int g = 0; g < F::N4; ++g) acc4[t][g] = 0.0;
+  }
 
-  const int* dq = s_doff + wave * kTreeQuads * 4 + kk;
   // this thread's window cells: global index, or -1 outside the domain
   // (n^3 <= 2^21 cells per level, so a cell index fits 32 bits)
   int wg[STAGE];
 #pragma unroll
   for (int i = 0; i < STAGE; ++i) {
-    const int c = tid + i * kTreeThreads;
-    const int gx = B0x - 5 + c % WX, gy = B0y - 5 + (c / WX) % kTreeW,
-              gz = B0z - 5 + c / (WX * kTreeW);
+    const int c = tid + i * NT;
+    const int gx = B0x - 5 + c % WX, gy = B0y - 5 + (c / WX) % kTreeW, gz = W0z + c / (WX * kTreeW);
     wg[i] = (c < WCELLS && gx >= 0 && gx < n && gy >= 0 && gy < n && gz >= 0 && gz < n)
                 ? gx + n * gy + n * n * gz
                 : -1;
   }
+  // tables through a buffer resource: a per-quad scalar offset and fixed lane
+  // offsets (quads read ahead in the last round fall in the tables' padding)
+  const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<double*>(B), (short)0, 8 * ROUNDS * kTreeQuads * NG * 256 + kTreePad * 8, 0x00020000);
+  const int vb16 = ((ci >> 2) * 16 + kk * 4 + (lane & 3)) * 16;      // column ci of a sixteen
+  const int vb4 = (4 * F::N16 * 16 + kk * 4 + (lane & 3)) * 16;
   for (int r = 0; r < ROUNDS; ++r) {
     double s0, s1;
     double2 v[STAGE];
@@ -346,96 +396,111 @@ __global__ void __launch_bounds__(kTreeThreads) m2l_level_kernel(
     __syncthreads();   // the previous round's window reads are done
 #pragma unroll
     for (int i = 0; i < STAGE; ++i) {
-      const int c = tid + i * kTreeThreads;
+      const int c = tid + i * NT;
       if (c < WCELLS) smem[c] = make_double2(v[i].x * s0, v[i].y * s1);
     }
     __syncthreads();
-    const double* Br = B + ((int64_t)(wave * ROUNDS + r) * kTreeQuads) * 2 * NG * 16 + kk * 4 + (lane & 3);
-    // table operands are loaded two quads ahead of their products
-    double nb0[NG], nb1[NG], mb0[NG], mb1[NG];
+    int sq = (sigma * ROUNDS + r) * kTreeQuads * NG * 256;    // table offset of the quad group
+    const short* sp = s_doff + sigma * kTreeQuads * 4 + kk;   // and its window deltas
+    double2 b16[U][K16], b4[U][K4], a[AR][TPW];
+    int o[U];
+#define TR_LOADB(SET, Q)                                                                           \
+  {                                                                                                \
+    _Pragma("unroll") for (int g = 0; g < F::N16; ++g) b16[SET][g] = __builtin_bit_cast(double2,   \
+        __builtin_amdgcn_raw_buffer_load_b128(brs, vb16 + 4 * g * 256, sq + (Q) * NG * 256, 0));   \
+    _Pragma("unroll") for (int g = 0; g < F::N4; ++g) b4[SET][g] = __builtin_bit_cast(double2,     \
+        __builtin_amdgcn_raw_buffer_load_b128(brs, vb4 + g * 256, sq + (Q) * NG * 256, 0));        \
+  }
+#define TR_LOADA(SET, OSET) \
+  _Pragma("unroll") for (int t = 0; t < TPW; ++t) a[SET][t] = smem[abase[t] + o[OSET]];
+#define TR_MMA(u, X)                                                                               \
+  _Pragma("unroll") for (int t = 0; t < TPW; ++t) {                                                \
+    _Pragma("unroll") for (int g = 0; g < F::N16; ++g) acc16[t][g] = mfma16(a[(u) % AR][t].X, b16[u][g].X, acc16[t][g]); \
+    _Pragma("unroll") for (int g = 0; g < F::N4; ++g) acc4[t][g] = mfma4(a[(u) % AR][t].X, b4[u][g].X, acc4[t][g]); \
+  }
+// one quad: window operands AD quads ahead, then the delta that operand set needs
+// next; the products; the table operands of quad u + U. The fences keep the reads
+// in issue order, so that every wait covers the oldest reads only.
+#define TR_STEP(u)                                                                                 \
+  {                                                                                                \
+    __builtin_amdgcn_sched_barrier(0);                                                             \
+    TR_LOADA(((u) + AD) % AR, ((u) + AD) % U);                                                     \
+    o[((u) + AD) % U] = sp[((u) + AD + U) * 4];                                                    \
+    TR_MMA(u, x);                                                                                  \
+    TR_MMA(u, y);                                                                                  \
+    TR_LOADB(u, (u) + U);                                                                          \
+    __builtin_amdgcn_sched_barrier(0);                                                             \
+  }
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      nb0[g] = Br[g * 16];
-      nb1[g] = Br[(NG + g) * 16];
-      mb0[g] = Br[2 * NG * 16 + g * 16];
-      mb1[g] = Br[2 * NG * 16 + (NG + g) * 16];
+    for (int u = 0; u < U; ++u) {
+      TR_LOADB(u, u);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    for (int q = 0; q < kTreeQuads; ++q) {
-      double b0[NG], b1[NG];
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        b0[g] = nb0[g];
-        b1[g] = nb1[g];
-        nb0[g] = mb0[g];
-        nb1[g] = mb1[g];
-      }
-      if (q + 2 < kTreeQuads) {
-        const double* Bn = Br + (int64_t)(q + 2) * 2 * NG * 16;
+    for (int u = 0; u < U; ++u) o[u] = sp[u * 4];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          mb0[g] = Bn[g * 16];
-          mb1[g] = Bn[(NG + g) * 16];
-        }
-      }
-      const int dl = dq[q * 4];
-      double2 a[TPW];
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) a[t] = smem[abase[t] + dl];
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-#pragma unroll
-        for (int g = 0; g < NG; ++g) acc[t][g] = mfma4(a[t].x, b0[g], acc[t][g]);
-#pragma unroll
-        for (int g = 0; g < NG; ++g) acc[t][g] = mfma4(a[t].y, b1[g], acc[t][g]);
-      }
+    for (int u = 0; u < AD; ++u) {
+      TR_LOADA(u, u % U);
+      o[u % U] = sp[(u + U) * 4];
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll 1
+    for (int q = 0; q < kTreeQuads / U * U; q += U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) TR_STEP(u);
+      sq += U * NG * 256;
+      sp += U * 4;
+    }
+#pragma unroll
+    for (int u = 0; u < kTreeQuads % U; ++u) TR_STEP(u);
+#undef TR_LOADB
+#undef TR_LOADA
+#undef TR_MMA
+#undef TR_STEP
   }
 
-  // D layout: this lane holds cell (2 xi + sx, 2 yi + sy) of each tile, column j
+  // This lane's sums: cells (2 xi + sx, 2 y + sy) of each tile, column 16 g + ci with
+  // y = v, or 4 g + j with y = yi. Through LDS, a block (or the plane) at a time,
+  // then each thread writes components of single cells (harmonic form: expanded
+  // from the columns; column c has order floor(sqrt(c))).
   const int xi = lane >> 4, yi = (lane & 15) >> 2, j = lane & 3;
-  if (!HARM) {
+  double* sh = reinterpret_cast<double*>(smem);     // [cells][CS], x fastest
 #pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      const int gx = B0x + 8 * (t >> 2) + 2 * xi + sx, gy = B0y + 2 * yi + sy, gz = B0z + 2 * (t & 3) + sz;
+  for (int b = 0; b < NBLK; ++b) {
+    __syncthreads();                                // the window, or the previous block, is no longer read
+#pragma unroll
+    for (int t = b * (TPW / NBLK); t < (b + 1) * (TPW / NBLK); ++t) {
+      auto put = [&](int c, int y, double sum) __attribute__((always_inline)) {
+        int ord = order_of(c < C ? c : 0);
+        if constexpr (HARM)
+          for (ord = 0; (ord + 1) * (ord + 1) <= c;) ++ord;
+        const int cell = (2 * xi + sx) + 8 * (2 * y + sy) + (WIDE ? 64 * tile_z(t) : 0);
+        if (c < CR) sh[cell * CS + c] = ldexp(sum, -lg * (1 + ord));
+      };
+#pragma unroll
+      for (int g = 0; g < F::N16; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) put(16 * g + ci, v, acc16[t][g][v]);
+#pragma unroll
+      for (int g = 0; g < F::N4; ++g) put(16 * F::N16 + 4 * g + j, yi, acc4[t][g]);
+    }
+    __syncthreads();
+    for (int e = tid; e < S::OUT * C; e += NT) {
+      const int cell = e % S::OUT, nn = e / S::OUT;
+      const int gx = B0x + 8 * b + cell % 8, gy = B0y + (cell / 8) % 8,
+                gz = B0z + (WIDE ? cell / 64 : plane);
       if (gx >= n || gy >= n || gz >= n) continue;
-      const int64_t g = gx + (int64_t)n * gy + (int64_t)n * n * gz;
-#pragma unroll
-      for (int gg = 0; gg < NG; ++gg) {
-        const int nn = 4 * gg + j;
-        if (nn < C) L[nn * n3 + g] = ldexp(acc[t][gg], -lg * (1 + order_of(nn)));
-      }
-    }
-    return;
-  }
-  // harmonic columns (column c has order floor(sqrt(c))) through LDS, then each
-  // thread expands one target cell to all C components
-  __syncthreads();                                  // the window is no longer read
-  double* sh = reinterpret_cast<double*>(smem);     // [512 NBLK cells][CR], x fastest over 8 NBLK
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int cell = (8 * (t >> 2) + 2 * xi + sx) + 8 * NBLK * ((2 * yi + sy) + 8 * (2 * (t & 3) + sz));
-#pragma unroll
-    for (int gg = 0; gg < NG; ++gg) {
-      const int c = 4 * gg + j;
-      if (c < CR) {
-        int ord = 0;
-        while ((ord + 1) * (ord + 1) <= c) ++ord;
-        sh[cell * CR + c] = ldexp(acc[t][gg], -lg * (1 + ord));
-      }
-    }
-  }
-  __syncthreads();
-  for (int cell = tid; cell < NBLK * kNTarget; cell += kTreeThreads) {
-    const int gx = B0x + cell % (8 * NBLK), gy = B0y + (cell / (8 * NBLK)) % 8, gz = B0z + cell / (64 * NBLK);
-    if (gx < n && gy < n && gz < n) {
-      const int64_t g = gx + (int64_t)n * gy + (int64_t)n * n * gz;
-      const double* lh = sh + cell * CR;
-      for (int nn = 0; nn < C; ++nn) {
+      const double* lh = sh + cell * CS;
+      double val;
+      if constexpr (HARM) {
         const HExp& ex = hexp[nn];
-        double v = 0.0;
-        for (int u = 0; u < ex.nterm; ++u) v = __builtin_fma(ex.coef[u], lh[ex.col[u]], v);
-        L[nn * n3 + g] = v;
+        val = 0.0;
+        for (int u = 0; u < ex.nterm; ++u) val = __builtin_fma(ex.coef[u], lh[ex.col[u]], val);
+      } else {
+        val = lh[nn];
       }
+      L[nn * n3 + gx + (int64_t)n * gy + (int64_t)n * n * gz] = val;
     }
   }
 }
@@ -499,7 +564,7 @@ hipError_t tree_tables_create(TreeTables* tt, const double* const* d_T, const in
   for (int p = 2; p <= kMaxP; ++p) {
     const int C = ncomp(p), NG = (C + 3) / 4, R = (C + 1) / 2;
     const size_t count = (size_t)8 * R * kTreeQuads * 2 * NG * 16;
-    if ((e = hipMalloc(&tt->B[p], sizeof(double) * count)) != hipSuccess) break;
+    if ((e = hipMalloc(&tt->B[p], sizeof(double) * (count + kTreePad))) != hipSuccess) break;
     hipLaunchKernelGGL(pack_tree_kernel, dim3(1024), dim3(256), 0, s, d_T[p], C, d_sidx, tt->B[p]);
     if ((e = hipGetLastError()) != hipSuccess) break;
     TreeHMaps mp;
@@ -510,7 +575,7 @@ hipError_t tree_tables_create(TreeTables* tt, const double* const* d_T, const in
     }
     const int CRh = (p + 1) * (p + 1), NGh = (CRh + 3) / 4;
     const size_t counth = (size_t)8 * rh * kTreeQuads * 2 * NGh * 16;
-    if ((e = hipMalloc(&tt->Bh[p], sizeof(double) * counth)) != hipSuccess) break;
+    if ((e = hipMalloc(&tt->Bh[p], sizeof(double) * (counth + kTreePad))) != hipSuccess) break;
     hipLaunchKernelGGL(pack_tree_h_kernel, dim3(1024), dim3(256), 0, s, d_T[p], C, rh, NGh, d_sidx, mp,
                        tt->Bh[p]);
     if ((e = hipGetLastError()) != hipSuccess) break;
@@ -570,48 +635,44 @@ hipError_t launch_tree_m2l(int p, const TreeTables& tt, const MfmaTables& mt, bo
                            const double* M, double* L, int nlev, const int* n, const int* lg,
                            const int64_t* off, hipStream_t s) {
   if (nlev < 1 || nlev > kTreeMaxLevels) return hipErrorInvalidValue;
-  // Two 8^3 blocks per workgroup (NBLK = 2) where a level has many of them, one
-  // (NBLK = 1) on the coarse levels and at p = 4 (registers). Each workgroup of a
-  // launch has the same work, at one workgroup per CU, so a launch whose count is
-  // just over a multiple of the CU count ends with a nearly idle wave: on 128^3,
-  // 2304 wide workgroups for the 128 and 64 levels (9 full waves) then the 32..4
-  // levels as 74 narrow ones (each ~0.6 of a wide one), instead of 2342 wide ones
-  // in one launch (a tenth wave of 38).
-  auto wide = [&](int l) { return p <= 3 && n[l] >= kTreeWideMin; };
+  // Wide workgroups where a level has at least one for every CU (64^3: 256), planes
+  // on the coarser levels. Planes everywhere, harmonic p = 3: 64^3 936 us against
+  // 707, 128^3 6542 against 4592 (11 planes staged for one); wide everywhere would
+  // leave most of the CUs without work below 64^3.
   for (int pass = 0; pass < 2; ++pass) {
-    const int nblk = pass == 0 ? 2 : 1;
+    const bool wide = pass == 0;
     TreeLevels lv{};
     int total = 0, cnt = 0;
     for (int i = 0; i < nlev; ++i) {            // coarsest level first
       const int l = nlev - 1 - i;
-      if (wide(l) != (pass == 0)) continue;
+      if ((n[l] >= kTreeWideMin) != wide) continue;
       const int nb = n[l] >= 8 ? n[l] / 8 : 1;
-      const int nbx = n[l] >= 8 * nblk ? n[l] / (8 * nblk) : 1;
       lv.first[cnt] = total;
       lv.n[cnt] = n[l];
       lv.lg[cnt] = lg[l];
       lv.off[cnt] = off[l];
-      total += nbx * nb * nb;
+      total += wide ? nb / 2 * nb * nb : nb * nb * nb * (n[l] < 8 ? n[l] : 8);
       ++cnt;
     }
     if (cnt == 0) continue;
     lv.nlev = cnt;
     lv.first[cnt] = total;
-    const dim3 grid((unsigned)total), block(kTreeThreads);
-#define TREE_LAUNCH(P, H, NB)                                                                   \
-  hipLaunchKernelGGL((m2l_level_kernel<P, H, NB>), grid, block, 0, s, M, L, lv,                \
-                     H ? tt.Bh[P] : tt.B[P], tt.doff, mt.hround[P], mt.hexp[P])
+#define TREE_LAUNCH(P, H, W)                                                                         \
+  hipLaunchKernelGGL((m2l_level_kernel<P, H, W>), dim3((unsigned)total), dim3(TreeShape<W>::NT), 0, s, \
+                     M, L, lv, H ? tt.Bh[P] : tt.B[P], tt.doff, mt.hround[P], mt.hexp[P])
     switch ((p * 2 + (harmonic ? 1 : 0)) * 2 + pass) {
-      case 8: TREE_LAUNCH(2, false, 2); break;
-      case 9: TREE_LAUNCH(2, false, 1); break;
-      case 10: TREE_LAUNCH(2, true, 2); break;
-      case 11: TREE_LAUNCH(2, true, 1); break;
-      case 12: TREE_LAUNCH(3, false, 2); break;
-      case 13: TREE_LAUNCH(3, false, 1); break;
-      case 14: TREE_LAUNCH(3, true, 2); break;
-      case 15: TREE_LAUNCH(3, true, 1); break;
-      case 17: TREE_LAUNCH(4, false, 1); break;
-      case 19: TREE_LAUNCH(4, true, 1); break;
+      case 8: TREE_LAUNCH(2, false, true); break;
+      case 9: TREE_LAUNCH(2, false, false); break;
+      case 10: TREE_LAUNCH(2, true, true); break;
+      case 11: TREE_LAUNCH(2, true, false); break;
+      case 12: TREE_LAUNCH(3, false, true); break;
+      case 13: TREE_LAUNCH(3, false, false); break;
+      case 14: TREE_LAUNCH(3, true, true); break;
+      case 15: TREE_LAUNCH(3, true, false); break;
+      case 16: TREE_LAUNCH(4, false, true); break;
+      case 17: TREE_LAUNCH(4, false, false); break;
+      case 18: TREE_LAUNCH(4, true, true); break;
+      case 19: TREE_LAUNCH(4, true, false); break;
       default: return hipErrorInvalidValue;
     }
 #undef TREE_LAUNCH

@@ -163,6 +163,27 @@ def test_tree_m2l_wide_and_narrow_launches(ctx, torch):
             check(g, w, s, "64^3 L level %d (harmonic %d)" % (lvl, harmonic))
 
 
+@pytest.mark.parametrize("p", [2, 3, 4])
+@pytest.mark.parametrize("harmonic", [0, 1])
+def test_tree_m2l_wide_workgroups_match_planes(ctx, torch, p, harmonic):
+    # the finest level of 32^3 runs by planes, that of 64^3 by wide workgroups: with
+    # its moments in one corner (nothing elsewhere) the corner's expansions have the
+    # same bits
+    C = fmm.ncomp(p)
+    small, large = fmm.Tree(p, 32, 1, -1, harmonic), fmm.Tree(p, 64, 1, -1, harmonic)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(40 + p)
+    M = torch.randn(fmm.tree_size(small)[1], dtype=torch.float64, device="cuda", generator=g)
+    M64 = torch.zeros(fmm.tree_size(large)[1], dtype=torch.float64, device="cuda")
+    M64[:C * 64 ** 3].view(C, 64, 64, 64)[:, 32:, :32, 32:] = M[:C * 32 ** 3].view(C, 32, 32, 32)
+    L, L64 = torch.full_like(M, float("nan")), torch.full_like(M64, float("nan"))
+    ctx.tree_m2l(small, M, L)
+    ctx.tree_m2l(large, M64, L64)
+    torch.cuda.synchronize()
+    got = L64[:C * 64 ** 3].view(C, 64, 64, 64)[:, 32:, :32, 32:]
+    assert torch.equal(got, L[:C * 32 ** 3].view(C, 32, 32, 32))
+
+
 # a seeded sweep over order, spacing (the extremes of log2_h), form and particle count
 SWEEP = [(p, lh, harm, ppc) for p, lh, harm, ppc in
          zip([2, 3, 4, 2, 3, 4, 3, 2], [-4, 4, 2, -3, -2, 3, 1, 0], [1, 0, 1, 0, 1, 0, 1, 1], [1, 2, 1, 9, 1, 1, 4, 2])]
