@@ -122,8 +122,8 @@ typedef struct {
 /* Library options (fmm_set_option). */
 #define FMM_OPT_M2L_KERNEL  1  /* 0 auto (default), 1 reference VALU kernel, 2 MFMA kernel */
 #define FMM_OPT_USE_GRAPH   2  /* 1 (default): replay cached hipGraphs for the M2L forms that take more than
-                                  one launch (FMM_FP64 tile configurations 2 to 5, FMM_SPLIT_FP32); 0: plain
-                                  launches. FMM_FP64 and FMM_FP64_HARMONIC by default are one launch */
+                                  one launch (FMM_FP64 tile configurations 2 to 5); 0: plain launches. FMM_FP64 by
+                                  default, FMM_FP64_HARMONIC and FMM_SPLIT_FP32 are one launch */
 #define FMM_OPT_TILE_CONFIG 3  /* -1 (default): autotuned/built-in choice; >= 0 forces a table entry */
 #define FMM_OPT_P2M_WINDOW  5  /* fmm_p2m: 0 (default) writes every cell of the frame; 1 reads and writes
                                   only the frame rows (y, z) in [2,22)^2 (all 24 cells of each), which

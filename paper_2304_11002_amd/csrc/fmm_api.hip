@@ -876,6 +876,10 @@ static fmm_status run_m2l(fmm_ctx* ctx, DescEntry* e, const double* M, double* L
     HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s));
     return FMM_OK;
   }
+  if (prec == FMM_SPLIT_FP32) {
+    HIP_TRY(ctx, launch_m2l_split(ctx->mfma, e->whole[0], e->d_desc, M, L, s));
+    return FMM_OK;
+  }
   return run_mfma(ctx, e, M, L, prec, cfg, s);
 }
 
@@ -946,10 +950,12 @@ fmm_status fmm_m2l_noalloc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, 
   HIP_TRY(ctx, hipEventRecord(ctx->noalloc_uploaded, s));
   wl.items = reinterpret_cast<const WorkItem*>(ctx->noalloc_dev + kNoAllocWorkOff);
   wl.count = (int)count;
-  // (the streamed forward's counter is zero between its calls, the other is reset by the launch)
-  wl.counter = reinterpret_cast<unsigned*>(ctx->noalloc_dev + kNoAllocCounterOff) + (streams ? 0 : 1);
+  // (the first counter is zero between launches, the other is reset by the launch)
+  const bool split = prec == FMM_SPLIT_FP32;
+  wl.counter = reinterpret_cast<unsigned*>(ctx->noalloc_dev + kNoAllocCounterOff) + (streams || split ? 0 : 1);
   const DevDesc* d_desc = reinterpret_cast<const DevDesc*>(ctx->noalloc_dev);
   if (streams) HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, wl, d_desc, M, L, harm, s));
+  else if (split) HIP_TRY(ctx, launch_m2l_split(ctx->mfma, wl, d_desc, M, L, s));
   else HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, d_desc, M, L, prec, cfg, s));
   return FMM_OK;
 }
@@ -1095,6 +1101,7 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
     auto launch = [&]() {
       const bool harm = prec == FMM_FP64_HARMONIC;
       return mfma_config_streams(cfg) ? launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s)
+             : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, e->whole[0], e->d_desc, M, L, s)
                                       : launch_m2l_mfma(ctx->mfma, work_for(e, harm), e->d_desc, M, L, prec, cfg, s);
     };
     HIP_TRY(ctx, launch());

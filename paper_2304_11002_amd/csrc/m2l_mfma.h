@@ -108,9 +108,8 @@ struct MfmaTables {
   double* fwd[kMaxP + 1] = {};
   // forward with LDS-staged tables, per order p: [rounds][quad][n-group][kk*4 + j][comp of pair]
   double* fwdl[kMaxP + 1] = {};
-  // split precision, per order p: the same layout, float32 hi and lo parts
-  float* fwd_hi[kMaxP + 1] = {};
-  float* fwd_lo[kMaxP + 1] = {};
+  // split precision, per order p: [rounds][quad][n-group][kk*4 + j][comp of pair][hi, lo] float32
+  float* fwds[kMaxP + 1] = {};
   // adjoint, per order p: [rounds][offset pair][dL chunk][kk*4 + j] float64
   double* bwd[kMaxP + 1] = {};
   int4* pairs = nullptr;        // adjoint offset pairs: (LDS offset 1, LDS offset 2, stencil 1, stencil 2 or -1)
@@ -185,6 +184,10 @@ hipError_t launch_m2l_slice(const MfmaTables& mt, const SliceTables& st, const W
 int mfma_num_configs();
 bool mfma_config_supports(int cfg, fmm_precision prec);
 int mfma_default_config(fmm_precision prec);
+
+// FMM_SPLIT_FP32 over a list of whole sub-grids (w.counter is zero between launches)
+hipError_t launch_m2l_split(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc, const double* M,
+                            double* L, hipStream_t s);
 
 // the streamed forward, which takes parts of sub-grids and can compute moments (FMM_FP64, FMM_FP64_HARMONIC)
 bool mfma_config_streams(int cfg);

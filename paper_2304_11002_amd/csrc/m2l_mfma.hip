@@ -365,13 +365,20 @@ struct WindowCells {
 };
 static_assert(kWin * kWin * kWin < 1 << 15 && kNCell < 1 << 16, "packed cells");
 
+// a window cell: the two components, or their float32 parts hi, lo, hi, lo
+__device__ __forceinline__ void put_cell(double2& w, double a0, double a1) { w = make_double2(a0, a1); }
+__device__ __forceinline__ void put_cell(float4& w, double a0, double a1) {
+  const float h0 = (float)a0, h1 = (float)a1;
+  w = make_float4(h0, (float)(a0 - (double)h0), h1, (float)(a1 - (double)h1));
+}
+
 // Round r's two components of the part's window cells, scaled, into LDS; in the
 // harmonic form each of the two is a combination of the round's moment
 // components. All loads of a pass are in flight together. Barriers: one before
 // the first store; the caller's follows.
-template <int P, bool HARM, int ROWS, int COUNT, int NT>
+template <int P, bool HARM, int ROWS, int COUNT, int NT, class Cell>
 __device__ __forceinline__ void stage_window(const WindowCells<COUNT, NT>& wc, int l2, const double* __restrict__ src,
-                                             const HRound* __restrict__ hround, int r, double2* win) {
+                                             const HRound* __restrict__ hround, int r, Cell* win) {
   constexpr int C = ncomp(P);
   constexpr int SUP = HARM ? harmonic_sup(P) : 2;        // components read per round, at most
   constexpr int kPasses = SUP * COUNT > 60 ? 2 : 1;      // (registers)
@@ -420,8 +427,9 @@ __device__ __forceinline__ void stage_window(const WindowCells<COUNT, NT>& wc, i
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int k = pass * kPer + i;
+      const bool in = (wc.on >> k) & 1u;
       if (k < COUNT && (int)threadIdx.x + k * NT < ROWS * kWin)
-        win[wc.lds(k)] = (wc.on >> k) & 1u ? make_double2(v[i].x * s0, v[i].y * s1) : make_double2(0.0, 0.0);
+        put_cell(win[wc.lds(k)], in ? v[i].x * s0 : 0.0, in ? v[i].y * s1 : 0.0);
     }
   }
 }
@@ -823,9 +831,9 @@ __global__ void __launch_bounds__(kWholeThreads) m2l_fwd_whole_kernel(
 // accumulators, and the h^(-1-|n|) scaling is applied in float64. One block
 // is 16 offset quads (64 offsets) of one staged component pair.
 //
-// Columns n < 16 * NCT use v_mfma_f32_16x16x4 (A: lane -> cell l%16, offset
+// Columns n < 16 * N16 use v_mfma_f32_16x16x4 (A: lane -> cell l%16, offset
 // slot l/16; B: lane -> offset slot l/16, column l%16; D: lane, v -> cell
-// 4*(l/16)+v, column l%16). The remaining C - 16 * NCT columns use
+// 4*(l/16)+v, column l%16). The remaining C - 16 * N16 columns use
 // v_mfma_f32_4x4x1_16b on the same A register: block b = l/4 takes offset
 // slot b/4 and cells 4*(b%4)..+3, so its D (lane, v -> cell 4*((l/4)%4)+v,
 // column l%4) holds one partial sum per offset slot, added across slots
@@ -840,232 +848,250 @@ __device__ __forceinline__ v4f mfma4x1(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
 }
 
+// One launch takes every sub-grid in quarters (two target planes, each wave two
+// tiles) or eighths (one plane, one tile a wave), two 256-thread workgroups per
+// compute unit, with the streamed forward's windows; a lane's hi and lo parts of
+// both components are one 16-byte LDS read and one 16-byte table load, from L2,
+// four quads ahead. Every block sum is taken in the order of the quads.
+// What bounds it: the matrix units (float32: 6 products a quad, component pair and
+// 16 columns), 0.8 of their time in use. Against one 512-thread workgroup per
+// sub-grid with 4-byte table loads (p = 3): 1 sub-grid 2600 -> 350 us, 513 8.0 ->
+// 4.57 ms, 1024 10.4 -> 8.46, 3000 31.1 -> 23.5; 1024 of p = 4 38.6 -> 24.9 (which
+// took two passes over its columns).
 constexpr int kSplitBlockQuads = 16;   // 64 offsets per float32 block sum
 
-// Columns handled in this call: 16-wide tiles [CT0, CT0 + NCTP) and, if WREM,
-// the remainder columns (p = 4 runs two calls so its accumulators fit).
-template <int P, int CT0, int NCTP, bool WREM>
-__device__ __forceinline__ void fwd_split_subgrid(const DevDesc& d, const double* __restrict__ M,
-                                                  double* __restrict__ L,
-                                                  const float* __restrict__ Bhi,
-                                                  const float* __restrict__ Blo,
-                                                  const int* __restrict__ lds_off,
-                                                  const uint32_t* __restrict__ touch, float4* smem) {
-  constexpr int C = ncomp(P);
-  constexpr int NG = (C + 3) / 4;                   // groups of 4 columns in the packed tables
+template <int P>
+struct SplitCols {
+  static constexpr int C = ncomp(P);
+  static constexpr int N16 = C >= 16 ? C / 16 : 1;   // 16-wide column tiles
+  static constexpr int REM = C > 16 * N16 ? 1 : 0;   // and a group of four on 4x4x1
+  static constexpr int NG = 4 * N16 + REM;           // groups of 4 columns in the packed tables
+};
+
+template <int P, bool FULL, int LEVEL>
+__device__ __forceinline__ void fwd_split_part(const DevDesc& d, const double* __restrict__ M, double* __restrict__ L,
+                                               const float4* __restrict__ Bs, const uint32_t* __restrict__ ttouch,
+                                               const int* __restrict__ rowtab, float4* win,
+                                               const short4 (*s_off)[kQuads + kOffPad], int part) {
+  using S = PartShape<LEVEL>;
+  using F = SplitCols<P>;
+  static_assert(LEVEL == 0 || LEVEL == 1, "quarters and eighths");
+  constexpr int C = F::C, N16 = F::N16, REM = F::REM, NG = F::NG;
   constexpr int ROUNDS = (C + 1) / 2;
-  constexpr int NCT_ALL = C >= 16 ? C / 16 : 1;     // 16-wide column tiles in total
-  constexpr int NCT = NCTP;                         // ... in this call
-  constexpr int REM = WREM && C - 16 * NCT_ALL > 0 ? C - 16 * NCT_ALL : 0;   // 4x4x1 columns
-  constexpr int WAVES = 8, TPW = 4, NT = WAVES * 64;
+  constexpr int TPW = S::TPW;
+  constexpr int U = 4;                                 // sets of table operands
+  constexpr int AD = TPW * (N16 + REM) > 4 ? 1 : 3, AR = AD + 1;   // window operands: quads ahead (registers), sets
+  static_assert(kSplitBlockQuads % U == 0 && U + AD <= kOffPad && U * NG * 32 <= (int)kTablePad, "read ahead");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kk = lane >> 4, ci = lane & 15;
+  const int tile0 = part * S::TILES + wave * TPW;      // 4 plane + 2 y + x in the 2 x 2 tiles of a plane
+  const int plane = tile0 >> 2, z0 = (part * S::TILES) >> 2;
+  auto tile_x = [&](int t) { return (TPW == 1 ? tile0 & 1 : t & 1) * 4; };
+  const int ty = ((tile0 >> 1) & 1) * 4;
   int abase[TPW];
 #pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int gt = wave * TPW + t;
-    const int z = gt >> 2, x = (gt & 1) * 4 + (ci & 3), y = ((gt >> 1) & 1) * 4 + (ci >> 2);
-    abase[t] = (x + 6) + kWin * (y + 6) + kWin * kWin * (z + 6);
-  }
-  const int zp = wave;   // one target plane per wave
-
-  double acc[TPW][NCT][4];
-  double racc[TPW][4];
+  for (int t = 0; t < TPW; ++t) abase[t] = (tile_x(t) + (ci & 3) + 6) + kWin * (ty + (ci >> 2) + 6);
+  const short* so = reinterpret_cast<const short*>(s_off[LEVEL == 0 ? plane - z0 : 2]) + kk;
+  double acc[TPW][N16 + REM][4];                       // (the group of four last)
 #pragma unroll
-  for (int t = 0; t < TPW; ++t) {
+  for (int t = 0; t < TPW; ++t)
 #pragma unroll
-    for (int c = 0; c < NCT; ++c)
+    for (int c = 0; c < N16 + REM; ++c)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[t][c][v] = 0.0;
+  // per tile: the quads with a present source, one bit each; lane 4 t + i holds word i of tile t
+  uint64_t live = 0;
+  if constexpr (!FULL) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) racc[t][v] = 0.0;
-  }
-
-  // lane offsets into one (round, quad, comp) chunk of the packed tables
-  int boff[NCT];
-  bool bvalid[NCT];
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
-  for (int c = 0; c < NCT; ++c) {
-    const int g = 4 * (CT0 + c) + (ci >> 2);
-    bvalid[c] = g < NG;
-    boff[c] = (bvalid[c] ? g : 0) * 16 + kk * 4 + (lane & 3);
+      for (int i = 0; i < 4; ++i) {
+        const int q = 64 * i + lane;
+        const uint64_t w = __ballot(q < kQuads && (ttouch[(tile0 + t) * kQuads + min(q, kQuads - 1)] & d.mask) != 0);
+        live = lane == 4 * t + i ? w : live;
+      }
   }
-  const int roff = 4 * NCT_ALL * 16 + kk * 4 + (lane & 3);   // remainder group
-
   const int l2 = d.log2_inv_h;
-  const double* src = M + d.m_off;
+  WindowCells<(S::STAGED * kWin + S::NT - 1) / S::NT, S::NT> wc;
+  wc.set(d, rowtab + S::FIRST, S::STAGED, z0);
+  const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float4*>(Bs), (short)0, ROUNDS * kQuads * NG * 256 + (int)kTablePad * 8, 0x00020000);
+  const int vb16 = ((ci >> 2) * 16 + kk * 4 + (lane & 3)) * 16;      // column ci of a sixteen
+  const int vb4 = (4 * N16 * 16 + kk * 4 + (lane & 3)) * 16;
   for (int r = 0; r < ROUNDS; ++r) {
-    const int k0 = 2 * r, k1 = 2 * r + 1;
-    const double s0 = ldexp(1.0, l2 * order_of(k0));
-    const double s1 = k1 < C ? ldexp(1.0, l2 * order_of(k1)) : 0.0;
-    const double* src0 = src + (size_t)k0 * kNCell;
-    const double* src1 = src + (size_t)(k1 < C ? k1 : k0) * kNCell;
-    // two halves of loads-then-stores keep the staging registers small
-    constexpr int kStage = (kWinCells + NT - 1) / NT;
-    constexpr int kHalf = (kStage + 1) / 2;
-#pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      double2 v[kHalf];
-#pragma unroll
-      for (int i = 0; i < kHalf; ++i) {
-        const int c = tid + (hb * kHalf + i) * NT;
-        v[i] = make_double2(0.0, 0.0);
-        if (hb * kHalf + i < kStage && c < kWinCells) {
-          const int wx = c % kWin, wy = (c / kWin) % kWin, wz = c / (kWin * kWin);
-          const int jx = wx + kWin0, jy = wy + kWin0, jz = wz + kWin0;
-          const int cell = jx + kFrame * jy + kFrame * kFrame * jz;
-          if (block_present(d.mask, jx, jy, jz)) {
-            v[i].x = src0[cell];
-            v[i].y = src1[cell];
-          }
-        }
-      }
-      if (hb == 0) __syncthreads();   // previous round's reads of smem are done
-#pragma unroll
-      for (int i = 0; i < kHalf; ++i) {
-        const int c = tid + (hb * kHalf + i) * NT;
-        if (hb * kHalf + i < kStage && c < kWinCells) {
-          const double a0 = v[i].x * s0, a1 = v[i].y * s1;
-          const float h0 = (float)a0, h1 = (float)a1;
-          smem[c] = make_float4(h0, (float)(a0 - (double)h0), h1, (float)(a1 - (double)h1));
-        }
-      }
-    }
+    stage_window<P, false, S::STAGED>(wc, l2, M + d.m_off, nullptr, r, win);
     __syncthreads();
-
-    const size_t chunk = (size_t)NG * 16;                     // one comp of one quad
-    const float* Rh = Bhi + (size_t)r * kQuads * 2 * chunk;
-    const float* Rl = Blo + (size_t)r * kQuads * 2 * chunk;
-    const int4* off4 = reinterpret_cast<const int4*>(lds_off);
-    uint32_t tm_next = touch[zp * kQuads];
-    int4 o_next = off4[0];
-    v4f f[TPW][NCT], fr[TPW];
-    for (int q = 0; q < kQuads; ++q) {
-      if (q % kSplitBlockQuads == 0) {
+    int sq = r * kQuads * NG * 256;
+    const short* sp = so;
+    v4f f[TPW][N16 + REM];
+    float4 b[U][N16 + REM], a[AR][TPW];
+    int o[U];
+    uint64_t lw[TPW][4];                               // live quads from the loop's first quad on
+    auto load_b = [&](int set, int q) __attribute__((always_inline)) {
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
+      for (int c = 0; c < N16; ++c)
+        b[set][c] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(brs, vb16 + 4 * c * 256, sq + q * NG * 256, 0));
+      if (REM) b[set][N16 + REM - 1] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(brs, vb4, sq + q * NG * 256, 0));
+    };
+    auto load_a = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-          for (int c = 0; c < NCT; ++c) f[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-          fr[t] = (v4f){0.f, 0.f, 0.f, 0.f};
-        }
-      }
-      const uint32_t tm = tm_next;
-      const int4 o = o_next;
-      if (q + 1 < kQuads) {
-        tm_next = touch[zp * kQuads + q + 1];
-        o_next = off4[q + 1];
-      }
-      if ((tm & d.mask) != 0) {
-        int doff = o.x;
-        doff = kk == 1 ? o.y : doff;
-        doff = kk == 2 ? o.z : doff;
-        doff = kk == 3 ? o.w : doff;
-        const float* Qh = Rh + (size_t)q * 2 * chunk;
-        const float* Ql = Rl + (size_t)q * 2 * chunk;
-        float bh[2][NCT], bl[2][NCT], rh[2], rl[2];
+      for (int t = 0; t < TPW; ++t) a[u % AR][t] = win[abase[t] + o[u % U]];
+    };
+    // the products of tile t (of all tiles, interleaved, for t < 0)
+    auto mma = [&](int u, int t0, int t1) __attribute__((always_inline)) {
 #pragma unroll
-        for (int cp = 0; cp < 2; ++cp) {
+      for (int i = 0; i < 6; ++i)                      // per component: hi hi, hi lo, lo hi
 #pragma unroll
-          for (int c = 0; c < NCT; ++c) {
-            bh[cp][c] = bvalid[c] ? Qh[cp * chunk + boff[c]] : 0.f;
-            bl[cp][c] = bvalid[c] ? Ql[cp * chunk + boff[c]] : 0.f;
-          }
-          rh[cp] = REM ? Qh[cp * chunk + roff] : 0.f;
-          rl[cp] = REM ? Ql[cp * chunk + roff] : 0.f;
-        }
-        float4 a[TPW];
+        for (int t = t0; t < t1; ++t) {
+          const float av = i == 0 || i == 1 ? a[u % AR][t].x : i == 2 ? a[u % AR][t].y : i == 5 ? a[u % AR][t].w : a[u % AR][t].z;
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) a[t] = smem[abase[t] + doff];
-#pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-#pragma unroll
-          for (int cp = 0; cp < 2; ++cp) {
-            const float ah = cp ? a[t].z : a[t].x, al = cp ? a[t].w : a[t].y;
-#pragma unroll
-            for (int c = 0; c < NCT; ++c) {
-              f[t][c] = mfma16(ah, bh[cp][c], f[t][c]);
-              f[t][c] = mfma16(ah, bl[cp][c], f[t][c]);
-              f[t][c] = mfma16(al, bh[cp][c], f[t][c]);
-            }
-            if (REM) {
-              fr[t] = mfma4x1(ah, rh[cp], fr[t]);
-              fr[t] = mfma4x1(ah, rl[cp], fr[t]);
-              fr[t] = mfma4x1(al, rh[cp], fr[t]);
-            }
+          for (int c = 0; c < N16 + REM; ++c) {
+            const float4 bb = b[u][c];
+            const float bv = i == 0 || i == 2 ? bb.x : i == 1 ? bb.y : i == 4 ? bb.w : bb.z;
+            f[t][c] = c < N16 ? mfma16(av, bv, f[t][c]) : mfma4x1(av, bv, f[t][c]);
           }
         }
+    };
+    auto fold_block = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int c = 0; c < N16 + REM; ++c)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[t][c][v] += (double)f[t][c][v];
+    };
+    // one quad, as in the streamed forward: window operands AD quads ahead, the
+    // offset that operand set needs next, the products, the table operands of quad u + U
+    auto step = [&](int u) __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_a(u + AD);
+      o[(u + AD) % U] = sp[(u + AD + U) * 4];
+      if constexpr (FULL) {
+        mma(u, 0, TPW);
+      } else {
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+          if ((uint32_t)lw[t][0] >> u & 1u) mma(u, t, t + 1);
+        asm volatile("" ::: "memory");
       }
-      if (q % kSplitBlockQuads == kSplitBlockQuads - 1 || q == kQuads - 1) {
+      load_b(u, u + U);
+      __builtin_amdgcn_sched_barrier(0);
+    };
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-#pragma unroll
-          for (int c = 0; c < NCT; ++c)
-#pragma unroll
-            for (int v2 = 0; v2 < 4; ++v2) acc[t][c][v2] += (double)f[t][c][v2];
-#pragma unroll
-          for (int v2 = 0; v2 < 4; ++v2) racc[t][v2] += (double)fr[t][v2];
-        }
-      }
+    for (int u = 0; u < U; ++u) {
+      load_b(u, u);
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) o[u] = sp[u * 4];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < AD; ++u) {
+      load_a(u);
+      o[u] = sp[(u + U) * 4];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (!FULL) {
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          lw[t][i] = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)live, 4 * t + i) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(live >> 32), 4 * t + i) << 32;
+    }
+#pragma unroll 1
+    for (int q = 0; q < kQuads / U * U; q += U) {
+      if (q % kSplitBlockQuads == 0) {
+        if (q > 0) fold_block();
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+          for (int c = 0; c < N16 + REM; ++c) f[t][c] = (v4f){0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) step(u);
+      if constexpr (!FULL) {
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+          for (int i = 0; i < 3; ++i) lw[t][i] = lw[t][i] >> U | lw[t][i + 1] << (64 - U);
+          lw[t][3] >>= U;
+        }
+      }
+      sq += U * NG * 256;
+      sp += U * 4;
+    }
+    static_assert(kQuads / U * U % kSplitBlockQuads != 0, "the last quads belong to the last block");
+#pragma unroll
+    for (int u = 0; u < kQuads % U; ++u) step(u);
+    fold_block();
   }
 
   double* out = L + d.l_off;
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
-    const int gt = wave * TPW + t;
-    const int z = gt >> 2, x0 = (gt & 1) * 4, y0 = ((gt >> 1) & 1) * 4;
+    const int t0 = tile_x(t) + kBlock * ty + kBlock * kBlock * plane;
     // 16x16 tiles: lane, v -> cell 4*(lane/16) + v (x = v, y = lane/16), column lane%16
 #pragma unroll
-    for (int c = 0; c < NCT; ++c) {
-      const int n = 16 * (CT0 + c) + (lane & 15);
+    for (int c = 0; c < N16; ++c) {
+      const int n = 16 * c + ci;
 #pragma unroll
-      for (int v2 = 0; v2 < 4; ++v2) {
-        const int tcell = (x0 + v2) + kBlock * (y0 + (lane >> 4)) + kBlock * kBlock * z;
-        if (n < C) out[(size_t)n * kNTarget + tcell] = ldexp(acc[t][c][v2], l2 * (1 + order_of(n)));
-      }
+      for (int v = 0; v < 4; ++v)
+        if (n < C) out[(size_t)n * kNTarget + t0 + v + kBlock * kk] = ldexp(acc[t][c][v], l2 * (1 + order_of(n)));
     }
-    if (REM) {
+    if constexpr (REM > 0) {
       // sum the four offset-slot partials (lanes l, l^16, l^32, l^48)
 #pragma unroll
-      for (int v2 = 0; v2 < 4; ++v2) {
-        double s = racc[t][v2];
+      for (int v = 0; v < 4; ++v) {
+        double s = acc[t][N16][v];
         s += __shfl_xor(s, 16);
         s += __shfl_xor(s, 32);
-        const int cell = 4 * ((lane >> 2) & 3) + v2;          // x = v2, y = (lane/4)%4
-        const int n = 16 * NCT_ALL + (lane & 3);
-        const int tcell = (x0 + (cell & 3)) + kBlock * (y0 + (cell >> 2)) + kBlock * kBlock * z;
-        if (lane < 16 && n < C) out[(size_t)n * kNTarget + tcell] = ldexp(s, l2 * (1 + order_of(n)));
+        const int n = 16 * N16 + (lane & 3);           // x = v, y = (lane/4)%4
+        if (lane < 16 && n < C)
+          out[(size_t)n * kNTarget + t0 + v + kBlock * ((lane >> 2) & 3)] = ldexp(s, l2 * (1 + order_of(n)));
       }
     }
   }
 }
 
-__global__ void __launch_bounds__(512) m2l_fwd_split_kernel(
+// Work: 4 (LEVEL 0) or 8 parts of every sub-grid of `items`, count in total. With
+// a counter the workgroups take parts from it; without, workgroup i runs part i.
+template <int LEVEL>
+__global__ void __launch_bounds__(kPartThreads, 2) m2l_fwd_split_kernel(
     const WorkItem* __restrict__ items, int count, unsigned* __restrict__ counter,
     const DevDesc* __restrict__ desc, const double* __restrict__ M, double* __restrict__ L,
-    const float* __restrict__ H2, const float* __restrict__ L2v, const float* __restrict__ H3,
-    const float* __restrict__ L3v, const float* __restrict__ H4, const float* __restrict__ L4v,
-    const int* __restrict__ lds_off, const uint32_t* __restrict__ touch) {
-  __shared__ float4 smem[kWinCells];
+    const float4* __restrict__ B2, const float4* __restrict__ B3, const float4* __restrict__ B4,
+    const short4* __restrict__ woff, const uint32_t* __restrict__ ttouch, const int* __restrict__ rowtab) {
+  constexpr int kCut = kLevelParts[LEVEL];
+  __shared__ float4 win[kWin * kWinRows2];
+  __shared__ short4 s_off[3][kQuads + kOffPad];
   __shared__ int s_item;
+  load_offsets<3, kPartThreads>(s_off, woff, 0);
   for (;;) {
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
+    if (counter && threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
     __syncthreads();
-    const int item = s_item;
-    if (item >= count) break;
-    const DevDesc d = desc[items[item].sub];
+    const int item = counter ? s_item : (int)blockIdx.x;
+    if (item >= count) {
+      // the last of the numbers past the items clears the counter for the next launch
+      if (counter && threadIdx.x == 0 && item == count + (int)gridDim.x - 1) *counter = 0u;
+      break;
+    }
+    const DevDesc d = desc[items[item / kCut].sub];
+    auto run = [&](auto order, const float4* B) __attribute__((always_inline)) {
+      constexpr int P = decltype(order)::value;
+      if (d.mask == kFullMask) fwd_split_part<P, true, LEVEL>(d, M, L, B, ttouch, rowtab, win, s_off, item % kCut);
+      else fwd_split_part<P, false, LEVEL>(d, M, L, B, ttouch, rowtab, win, s_off, item % kCut);
+    };
     switch (d.p) {
-      case 2: fwd_split_subgrid<2, 0, 1, true>(d, M, L, H2, L2v, lds_off, touch, smem); break;
-      case 3: fwd_split_subgrid<3, 0, 1, true>(d, M, L, H3, L3v, lds_off, touch, smem); break;
-      case 4:
-        fwd_split_subgrid<4, 0, 1, false>(d, M, L, H4, L4v, lds_off, touch, smem);
-        __syncthreads();
-        fwd_split_subgrid<4, 1, 1, true>(d, M, L, H4, L4v, lds_off, touch, smem);
-        break;
+      case 2: run(std::integral_constant<int, 2>{}, B2); break;
+      case 3: run(std::integral_constant<int, 3>{}, B3); break;
+      case 4: run(std::integral_constant<int, 4>{}, B4); break;
       default: break;
     }
-    __syncthreads();
+    if (!counter) break;
+    __syncthreads();   // every thread has read s_item; the item's LDS use is done
   }
 }
 
@@ -1436,7 +1462,6 @@ __global__ void __launch_bounds__(kBwdThreads) m2l_bwd_kernel(
 // forward: [r][q][c][g][kk*4 + j] = T_{4q+kk}[2r+c][4g+j]
 // LDS-staged forward: [r][q][g][kk*4 + j][c], same values
 __global__ void pack_fwd_kernel(const double* __restrict__ T, int p, double* __restrict__ out,
-                                float* __restrict__ hi, float* __restrict__ lo,
                                 double* __restrict__ outl) {
   const int C = ncomp(p), NG = (C + 3) / 4, ROUNDS = (C + 1) / 2;
   const int total = ROUNDS * kQuads * 2 * NG * 16;
@@ -1452,9 +1477,24 @@ __global__ void pack_fwd_kernel(const double* __restrict__ T, int p, double* __r
   const double v = (k < C && n < C) ? T[((size_t)s * C + k) * C + n] : 0.0;
   out[i] = v;
   outl[((((size_t)r * kQuads + q) * NG + g) * 16 + kk * 4 + j) * 2 + c] = v;
+}
+
+// split precision: [r][q][g][kk*4 + j] = the hi and lo parts of component 2r, then of 2r + 1
+__global__ void pack_split_kernel(const double* __restrict__ T, int p, int ng, float* __restrict__ out) {
+  const int C = ncomp(p), ROUNDS = (C + 1) / 2;
+  const int total = ROUNDS * kQuads * ng * 32;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  const int c = i & 1, jj = (i >> 1) & 15;
+  int rest = i >> 5;
+  const int g = rest % ng; rest /= ng;
+  const int q = rest % kQuads;
+  const int r = rest / kQuads;
+  const int k = 2 * r + c, n = 4 * g + (jj & 3), s = 4 * q + (jj >> 2);
+  const double v = (k < C && n < C) ? T[((size_t)s * C + k) * C + n] : 0.0;
   const float h = (float)v;
-  hi[i] = h;
-  lo[i] = (float)(v - (double)h);
+  out[2 * (size_t)i] = h;
+  out[2 * (size_t)i + 1] = (float)(v - (double)h);
 }
 
 // harmonic: [r][q][g][kk*4 + j][c] = T_{4q+kk}[rowk[2r + c]][colk[4g + j]] (0 where a map is -1)
@@ -1521,6 +1561,10 @@ __global__ void pack_bwd_kernel(const double* __restrict__ T, int p, const int4*
 size_t fwd_pack_elems(int p) {
   const int C = ncomp(p), NG = (C + 3) / 4, ROUNDS = (C + 1) / 2;
   return (size_t)ROUNDS * kQuads * 2 * NG * 16;
+}
+
+int split_groups(int p) {
+  return p == 2 ? SplitCols<2>::NG : p == 3 ? SplitCols<3>::NG : SplitCols<4>::NG;
 }
 
 size_t bwd_pack_elems(int p, int npairs) {
@@ -1638,7 +1682,7 @@ std::vector<int> host_stencil() {
 // Forward configurations.
 struct Config {
   fmm_precision prec;
-  bool stream;          // m2l_fwd_stream_kernel; otherwise (FMM_FP64) m2l_fwd_kernel with
+  bool stream;          // m2l_fwd_whole_kernel or m2l_fwd_part_kernel; otherwise (FMM_FP64) m2l_fwd_kernel with
   int waves = 8;        //   this many waves per workgroup (16-cell tiles per wave = 32 / waves)
   bool prefetch = false;   // and the table operands of the next offset quad loaded one quad ahead
                            // (not at p = 4 with 8 waves: the registers would spill)
@@ -2074,11 +2118,14 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
     const size_t nf = fwd_pack_elems(p), nb = bwd_pack_elems(p, t->npairs);
     if ((e = hipMalloc(&t->fwd[p], nf * sizeof(double))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->fwdl[p], (nf + kTablePad) * sizeof(double))) != hipSuccess) return e;
-    if ((e = hipMalloc(&t->fwd_hi[p], nf * sizeof(float))) != hipSuccess) return e;
-    if ((e = hipMalloc(&t->fwd_lo[p], nf * sizeof(float))) != hipSuccess) return e;
+    const int ngs = split_groups(p), ns = (ncomp(p) + 1) / 2 * kQuads * ngs * 32;
+    if ((e = hipMalloc(&t->fwds[p], (ns + kTablePad) * 2 * sizeof(float))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->bwd[p], nb * sizeof(double))) != hipSuccess) return e;
     hipLaunchKernelGGL(pack_fwd_kernel, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, s, d_T[p], p,
-                       t->fwd[p], t->fwd_hi[p], t->fwd_lo[p], t->fwdl[p]);
+                       t->fwd[p], t->fwdl[p]);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(pack_split_kernel, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, s, d_T[p], p, ngs,
+                       t->fwds[p]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(pack_bwd_kernel, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, d_T[p], p,
                        t->pairs, t->npairs, t->bwd[p]);
@@ -2118,8 +2165,7 @@ void mfma_tables_destroy(MfmaTables* t) {
     if (t->fwd[p]) (void)hipFree(t->fwd[p]);
     if (t->fwdl[p]) (void)hipFree(t->fwdl[p]);
     t->fwdl[p] = nullptr;
-    if (t->fwd_hi[p]) (void)hipFree(t->fwd_hi[p]);
-    if (t->fwd_lo[p]) (void)hipFree(t->fwd_lo[p]);
+    if (t->fwds[p]) (void)hipFree(t->fwds[p]);
     if (t->bwd[p]) (void)hipFree(t->bwd[p]);
     if (t->fwdh[p]) (void)hipFree(t->fwdh[p]);
     if (t->hround[p]) (void)hipFree(t->hround[p]);
@@ -2134,7 +2180,7 @@ void mfma_tables_destroy(MfmaTables* t) {
     t->hround[p] = nullptr;
     t->hexp[p] = nullptr;
     t->fwd[p] = t->bwd[p] = nullptr;
-    t->fwd_hi[p] = t->fwd_lo[p] = nullptr;
+    t->fwds[p] = nullptr;
   }
   if (t->lds_off) (void)hipFree(t->lds_off);
   if (t->touch) (void)hipFree(t->touch);
@@ -2198,20 +2244,36 @@ hipError_t launch_m2l_stream(const MfmaTables& t, const WorkList& w, const DevDe
   return hipGetLastError();
 }
 
+hipError_t launch_m2l_split(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc, const double* M,
+                            double* L, hipStream_t s) {
+  if (w.count == 0) return hipSuccess;
+  if (w.parts) return hipErrorInvalidValue;
+  const float4* B[3];
+  for (int p = 2; p <= 4; ++p) B[p - 2] = reinterpret_cast<const float4*>(t.fwds[p]);
+  // Eighths while all of them run at once: 1 sub-grid (p = 3) 350 us in eighths, 548
+  // in quarters; 30 402 and 585, 50 of mixed p 1237 and 1870; 64 704 and 663, 100
+  // 1266 and 1126, 1024 9087 and 8459.
+  const int level = w.count * (int)kLevelParts[1] < 2 * t.num_cu ? 1 : 0;
+  const int count = w.count * (int)kLevelParts[level];
+  const int grid = std::min(2 * t.num_cu, count);
+  unsigned* counter = count > grid ? w.counter : nullptr;
+#define SPLIT_LAUNCH(LEVEL)                                                                              \
+  hipLaunchKernelGGL(m2l_fwd_split_kernel<LEVEL>, dim3(grid), dim3(kPartThreads), 0, s, w.items, count,  \
+                     counter, d_desc, M, L, B[0], B[1], B[2], t.woff, t.ttouch, t.rowtab)
+  if (level == 1) SPLIT_LAUNCH(1);
+  else SPLIT_LAUNCH(0);
+#undef SPLIT_LAUNCH
+  return hipGetLastError();
+}
+
 hipError_t launch_m2l_mfma(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc,
                            const double* M, double* L, fmm_precision prec, int cfg, hipStream_t s) {
   if (w.count == 0) return hipSuccess;
-  // (FMM_EXACT_SLICE runs through launch_m2l_slice, the streamed forms through launch_m2l_stream)
-  if (!mfma_config_supports(cfg, prec) || prec == FMM_EXACT_SLICE || mfma_config_streams(cfg)) return hipErrorInvalidValue;
+  // (the per-wave FMM_FP64 configurations; the others have launches of their own)
+  if (!mfma_config_supports(cfg, prec) || prec != FMM_FP64 || mfma_config_streams(cfg)) return hipErrorInvalidValue;
   const Config& c = kConfigs[cfg];
   const int grid = std::min(t.num_cu, w.count);
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, w.counter);
-  if (c.prec == FMM_SPLIT_FP32) {
-    hipLaunchKernelGGL(m2l_fwd_split_kernel, dim3(grid), dim3(512), 0, s, w.items, w.count, w.counter,
-                       d_desc, M, L, t.fwd_hi[2], t.fwd_lo[2], t.fwd_hi[3], t.fwd_lo[3], t.fwd_hi[4],
-                       t.fwd_lo[4], t.lds_off, t.touch);
-    return hipGetLastError();
-  }
 #define FWD_LAUNCH(W, PFV)                                                                         \
   hipLaunchKernelGGL((m2l_fwd_kernel<W, PFV>), dim3(grid), dim3(W * 64), 0, s, w.items, w.count,   \
                      w.counter, d_desc, M, L, t.fwd[2], t.fwd[3], t.fwd[4], t.lds_off, t.touch)

@@ -64,6 +64,34 @@ def test_parts_match_whole_subgrids_and_the_oracle(torch, form, n, p, uneven):
 
 
 @pytest.mark.parametrize("uneven", [False, True])
+def test_split_precision_quarters_match_eighths_and_the_oracle(torch, uneven):
+    # FMM_SPLIT_FP32: few sub-grids run in eighths, more in quarters, from a work
+    # counter where the parts outnumber the workgroups; the same bits, within the
+    # split form's bound (1e-6 of the rounding scale) of the oracle
+    ensure_library()
+    n = 3 * torch.cuda.get_device_properties(0).multi_processor_count // 4
+    desc, M, l_el = _batch(n, 0, uneven)
+    dM = to_dev(M)
+    L = {}
+    with fmm.Context(0) as ctx:
+        for count in (n, n // 2, 7, 1):
+            for rep in range(2):
+                L[count] = torch.full((l_el,), float("nan"), dtype=torch.float64, device="cuda")
+                ctx.m2l(desc[:count], dM, L[count], fmm.FMM_SPLIT_FP32)
+        torch.cuda.synchronize()
+    want = L[n]
+    assert bool(torch.isfinite(want).all())
+    for count, got in L.items():
+        end = int(desc["l_off"][count]) if count < n else l_el
+        assert torch.equal(got[:end], want[:end]), count
+    Mv, Lv = split_views(M, desc, "M"), split_views(want.cpu().numpy(), desc, "L")
+    for b in (0, 1, 2):                # p = 2, 3, 4
+        q, h, mask = int(desc["p"][b]), 2.0 ** -int(desc["log2_inv_h"][b]), int(desc["mask"][b])
+        err = np.abs(Lv[b] - O.m2l(Mv[b], q, h, mask)) / O.m2l_abs(Mv[b], q, h, mask)
+        assert err.max() <= 1e-6
+
+
+@pytest.mark.parametrize("uneven", [False, True])
 @pytest.mark.parametrize("p", [2, 3, 4])
 @pytest.mark.parametrize("form", [0, 1])
 def test_adjoint_by_rounds_matches_whole_subgrids_and_the_oracle(torch, form, p, uneven):
