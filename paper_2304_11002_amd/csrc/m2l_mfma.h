@@ -110,7 +110,7 @@ struct MfmaTables {
   double* fwdl[kMaxP + 1] = {};
   // split precision, per order p: [rounds][quad][n-group][kk*4 + j][comp of pair][hi, lo] float32
   float* fwds[kMaxP + 1] = {};
-  // adjoint, per order p: [rounds][offset pair][dL chunk][kk*4 + j] float64
+  // adjoint, per order p: [rounds][offset pair][dL chunk / 2][kk*4 + j][dL chunk % 2] float64
   double* bwd[kMaxP + 1] = {};
   int4* pairs = nullptr;        // adjoint offset pairs: (LDS offset 1, LDS offset 2, stencil 1, stencil 2 or -1)
   int npairs = 0;
@@ -130,7 +130,7 @@ struct MfmaTables {
   double* fwdh[kMaxP + 1] = {};
   HRound* hround[kMaxP + 1] = {};
   HExp* hexp[kMaxP + 1] = {};
-  // harmonic adjoint, per order p: tables [rounds][offset pair][n' chunk][kk*4 + j], the
+  // harmonic adjoint, per order p: tables [rounds][offset pair][n' chunk / 2][kk*4 + j][n' chunk % 2], the
   // fold of dL per harmonic column and the output plan per round
   double* bwdh[kMaxP + 1] = {};
   HFold* hfold[kMaxP + 1] = {};

@@ -1148,6 +1148,7 @@ __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __re
   constexpr int C = ncomp(P);
   constexpr int CR = HARM ? (P + 1) * (P + 1) : C;   // reduced components
   constexpr int KC = (CR + 3) / 4;    // dL component chunks of 4 (the reduction)
+  constexpr int KC2 = (KC + 1) / 2;   // and pairs of chunks, one table load each
   constexpr int ROUNDS = (CR + 1) / 2;
   constexpr int TPW = 4;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1211,11 +1212,14 @@ __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __re
     }
     // tables through a buffer resource: a per-pair scalar offset and this lane's
     // fixed byte offset, so no per-pair address registers (reads past the end of
-    // the tables would return zeros)
+    // the tables would return zeros). Two chunks per 16-byte load, which occupies
+    // the texture pipe no longer than 8 bytes (one chunk per load, 2048 sub-grids
+    // of p = 3: harmonic 9.85 ms, dense 13.27, now 9.66 and 12.82; 1024 of p = 4
+    // 12.05 and 19.25, now 11.7 and 18.5).
     const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<double*>(Bp), (short)0, ROUNDS * npairs * KC * 16 * (int)sizeof(double), 0x00020000);
-    const int sbase = r * npairs * KC * 16 * (int)sizeof(double);
-    const int vboff = (kk * 4 + j) * (int)sizeof(double);
+        const_cast<double*>(Bp), (short)0, ROUNDS * npairs * KC2 * 256, 0x00020000);
+    const int sbase = r * npairs * KC2 * 256;
+    const int vboff = (kk * 4 + j) * 16;
     // Three sets (tables, touch mask, products, output offset) rotate over the
     // pairs: at pair q the set of pair q - 1, whose products are issued, takes
     // the tables of pair q + 2 and the output offset of pair q - 1, and a set's
@@ -1232,10 +1236,13 @@ __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __re
 #define BW_LOAD(BS, FS, TS, Q)                                                      \
   {                                                                                 \
     const int q_ = (Q);                                                             \
-    const int so_ = sbase + q_ * KC * 16 * (int)sizeof(double);                     \
-    _Pragma("unroll") for (int kc = 0; kc < KC; ++kc)                               \
-      BS[kc] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(     \
-                   brs, vboff + kc * 16 * (int)sizeof(double), so_, 0));            \
+    const int so_ = sbase + q_ * KC2 * 256;                                         \
+    _Pragma("unroll") for (int kc = 0; kc < KC2; ++kc) {                            \
+      const double2 b_ = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128( \
+                                                         brs, vboff + kc * 256, so_, 0)); \
+      BS[2 * kc] = b_.x;                                                            \
+      if (2 * kc + 1 < KC) BS[2 * kc + 1] = b_.y;                                   \
+    }                                                                               \
     if (!FULL) TS = __builtin_amdgcn_raw_buffer_load_b32(trs, 0, q_ * 4, 0);        \
     FS = BW_OFFSET(q_ - 3);                                                         \
   }
@@ -1253,7 +1260,7 @@ __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __re
 #define BW_INTERLEAVE()                                                             \
   {                                                                                 \
     constexpr int NMF = TPW * KC;                                                   \
-    _Pragma("unroll") for (int i_ = 0; i_ < KC; ++i_) {                             \
+    _Pragma("unroll") for (int i_ = 0; i_ < KC2; ++i_) {                            \
       __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                            \
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            \
     }                                                                               \
@@ -1261,7 +1268,7 @@ __device__ __forceinline__ void bwd_subgrid(const DevDesc& d, const double* __re
       __builtin_amdgcn_sched_group_barrier(0x080, 1, 0);                            \
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            \
     }                                                                               \
-    __builtin_amdgcn_sched_group_barrier(0x008, NMF - TPW - KC, 0);                 \
+    __builtin_amdgcn_sched_group_barrier(0x008, NMF - TPW - KC2, 0);                     \
   }
 // pair Q from set S (products AS, pending products of pair Q - 3 at FS); set N
 // (pair Q - 1) takes the tables of Q + 2 and the offset of pair Q - 1
@@ -1521,7 +1528,7 @@ __global__ void pack_fwdh_kernel(const double* __restrict__ T, int p, HPackMaps 
   out[i] = (k >= 0 && n >= 0) ? T[((size_t)s * C + k) * C + n] : 0.0;
 }
 
-// harmonic adjoint: [r][pair][kc][kk*4 + j] = T_{s_(j/2)}[rowk[2r + j%2]][colk[4kc + kk]]
+// harmonic adjoint: [r][pair][kc/2][kk*4 + j][kc%2] = T_{s_(j/2)}[rowk[2r + j%2]][colk[4kc + kk]]
 __global__ void pack_bwdh_kernel(const double* __restrict__ T, int p, const int4* __restrict__ pairs,
                                  int npairs, HPackMaps mp, int rounds, int kcn, double* __restrict__ out) {
   const int C = ncomp(p);
@@ -1537,10 +1544,11 @@ __global__ void pack_bwdh_kernel(const double* __restrict__ T, int p, const int4
   const int4 pr = pairs[q];
   const int so = (j >> 1) ? pr.w : pr.z;
   const int k = mp.rowk[2 * r + (j & 1)], n = mp.colk[4 * kc + kk];
-  out[i] = (so >= 0 && k >= 0 && n >= 0) ? T[((size_t)so * C + k) * C + n] : 0.0;
+  out[((((size_t)r * npairs + q) * ((kcn + 1) / 2) + kc / 2) * 16 + (i & 15)) * 2 + kc % 2] =
+      (so >= 0 && k >= 0 && n >= 0) ? T[((size_t)so * C + k) * C + n] : 0.0;
 }
 
-// adjoint: [r][pair][kc][kk*4 + j] = T_{s_(j/2)}[2r + j%2][4kc + kk] (0 for a missing offset)
+// adjoint: [r][pair][kc/2][kk*4 + j][kc%2] = T_{s_(j/2)}[2r + j%2][4kc + kk] (0 for a missing offset)
 __global__ void pack_bwd_kernel(const double* __restrict__ T, int p, const int4* __restrict__ pairs,
                                 int npairs, double* __restrict__ out) {
   const int C = ncomp(p), KC = (C + 3) / 4, ROUNDS = (C + 1) / 2;
@@ -1555,7 +1563,8 @@ __global__ void pack_bwd_kernel(const double* __restrict__ T, int p, const int4*
   const int4 pr = pairs[q];
   const int so = (j >> 1) ? pr.w : pr.z;
   const int k = 2 * r + (j & 1), n = 4 * kc + kk;
-  out[i] = (so >= 0 && k < C && n < C) ? T[((size_t)so * C + k) * C + n] : 0.0;
+  out[((((size_t)r * npairs + q) * ((KC + 1) / 2) + kc / 2) * 16 + (i & 15)) * 2 + kc % 2] =
+      (so >= 0 && k < C && n < C) ? T[((size_t)so * C + k) * C + n] : 0.0;
 }
 
 size_t fwd_pack_elems(int p) {
@@ -1565,6 +1574,11 @@ size_t fwd_pack_elems(int p) {
 
 int split_groups(int p) {
   return p == 2 ? SplitCols<2>::NG : p == 3 ? SplitCols<3>::NG : SplitCols<4>::NG;
+}
+
+// (an odd chunk's pair is half empty)
+size_t bwd_table_bytes(int rounds, int npairs, int chunks) {
+  return (size_t)rounds * npairs * ((chunks + 1) / 2) * 256;
 }
 
 size_t bwd_pack_elems(int p, int npairs) {
@@ -2120,7 +2134,7 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
     if ((e = hipMalloc(&t->fwdl[p], (nf + kTablePad) * sizeof(double))) != hipSuccess) return e;
     const int ngs = split_groups(p), ns = (ncomp(p) + 1) / 2 * kQuads * ngs * 32;
     if ((e = hipMalloc(&t->fwds[p], (ns + kTablePad) * 2 * sizeof(float))) != hipSuccess) return e;
-    if ((e = hipMalloc(&t->bwd[p], nb * sizeof(double))) != hipSuccess) return e;
+    if ((e = hipMalloc(&t->bwd[p], bwd_table_bytes((ncomp(p) + 1) / 2, t->npairs, (ncomp(p) + 3) / 4))) != hipSuccess) return e;
     hipLaunchKernelGGL(pack_fwd_kernel, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, s, d_T[p], p,
                        t->fwd[p], t->fwdl[p]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -2146,7 +2160,7 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
                        hh.maps, (int)hh.rounds.size(), hh.ng, t->fwdh[p]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const size_t nbh = hh.rounds.size() * (size_t)t->npairs * hh.ng * 16;   // ng = n'-chunks of 4
-    if ((e = hipMalloc(&t->bwdh[p], nbh * sizeof(double))) != hipSuccess) return e;
+    if ((e = hipMalloc(&t->bwdh[p], bwd_table_bytes((int)hh.rounds.size(), t->npairs, hh.ng))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->hfold[p], hh.folds.size() * sizeof(HFold))) != hipSuccess) return e;
     if ((e = hipMalloc(&t->hout[p], hh.outs.size() * sizeof(HOut))) != hipSuccess) return e;
     if ((e = hipMemcpy(t->hfold[p], hh.folds.data(), hh.folds.size() * sizeof(HFold),
