@@ -125,7 +125,8 @@ __device__ __forceinline__ bool cell_present(uint32_t mask, int cell) {
 constexpr int kWinBlock0 = (kWin0 * kFrame * kFrame) / 128;                            // 9
 constexpr int kWinBlocks = ((kWin0 + kWin) * kFrame * kFrame + 127) / 128 - kWinBlock0;   // 90
 
-// Each workgroup takes K cell blocks (strided by the grid; K = 4 measured best of 4, 8, 16). The coalesced loads
+// Each workgroup takes K cell blocks, strided by the grid (K = 4 measured best of
+// 4, 8, 16 on large batches; one on batches that fit the GPU at once, see p2m8_spread). The coalesced loads
 // of the next block are issued into registers before this block's moments are
 // computed, so every workgroup keeps loads in flight through its compute and
 // store phases (4 workgroups fit a CU by LDS). p = 4 needs those registers for
@@ -280,6 +281,11 @@ __global__ void __launch_bounds__(kT8) p2m8_bwd_kernel(const DevDesc* __restrict
 #undef P2M8B_ISSUE
 }
 
+// Workgroups the GPU holds at once (four per compute unit by LDS). A batch of no
+// more cell blocks takes one block per workgroup (the adjoint of 1 to 8 sub-grids,
+// p = 3: 31 -> 22 us).
+static bool p2m8_spread(int nblocks) { return nblocks <= 1024; }
+
 // The 8-particle kernels use 16-byte loads: they need 16-byte aligned particle
 // arrays (always true for part_off of a whole sub-grid and hipMalloc'd buffers).
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -297,13 +303,18 @@ hipError_t launch_p2m(const DevDesc* d_desc, int64_t nsub, const int* const* d_i
         const int nblocks = (int)(n * (window ? kWinBlocks : kCellBlocks8));
         const dim3 grid4((unsigned)((nblocks + 3) / 4)), grid1((unsigned)nblocks);
         const int* ids = d_ids[p] + b0;
+        const bool spread = p2m8_spread(nblocks);
         if (window) {
-          if (p == 2) hipLaunchKernelGGL((p2m8_kernel<2, 4, true>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
-          if (p == 3) hipLaunchKernelGGL((p2m8_kernel<3, 4, true>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          if (p == 2 && spread) hipLaunchKernelGGL((p2m8_kernel<2, 1, true>), grid1, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          else if (p == 2) hipLaunchKernelGGL((p2m8_kernel<2, 4, true>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          if (p == 3 && spread) hipLaunchKernelGGL((p2m8_kernel<3, 1, true>), grid1, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          else if (p == 3) hipLaunchKernelGGL((p2m8_kernel<3, 4, true>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
           if (p == 4) hipLaunchKernelGGL((p2m8_kernel<4, 1, true>), grid1, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
         } else {
-          if (p == 2) hipLaunchKernelGGL((p2m8_kernel<2, 4, false>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
-          if (p == 3) hipLaunchKernelGGL((p2m8_kernel<3, 4, false>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          if (p == 2 && spread) hipLaunchKernelGGL((p2m8_kernel<2, 1, false>), grid1, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          else if (p == 2) hipLaunchKernelGGL((p2m8_kernel<2, 4, false>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          if (p == 3 && spread) hipLaunchKernelGGL((p2m8_kernel<3, 1, false>), grid1, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
+          else if (p == 3) hipLaunchKernelGGL((p2m8_kernel<3, 4, false>), grid4, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
           if (p == 4) hipLaunchKernelGGL((p2m8_kernel<4, 1, false>), grid1, dim3(kT8), 0, s, d_desc, ids, nblocks, pos, mass, M);
         }
       }
@@ -330,8 +341,11 @@ hipError_t launch_p2m_backward(const DevDesc* d_desc, int64_t nsub, const int* c
         const int64_t n = counts[p] - b0 < per_launch ? counts[p] - b0 : per_launch;
         const int nblocks = (int)(n * kCellBlocks8);
         const dim3 grid8((unsigned)((nblocks + 7) / 8)), grid1((unsigned)nblocks);
-        if (p == 2) hipLaunchKernelGGL((p2m8_bwd_kernel<2, 8>), grid8, dim3(kT8), 0, s, d_desc, d_ids[p] + b0, nblocks, pos, dM, dmass);
-        if (p == 3) hipLaunchKernelGGL((p2m8_bwd_kernel<3, 8>), grid8, dim3(kT8), 0, s, d_desc, d_ids[p] + b0, nblocks, pos, dM, dmass);
+        const bool spread = p2m8_spread(nblocks);
+        if (p == 2 && spread) hipLaunchKernelGGL((p2m8_bwd_kernel<2, 1>), grid1, dim3(kT8), 0, s, d_desc, d_ids[p] + b0, nblocks, pos, dM, dmass);
+        else if (p == 2) hipLaunchKernelGGL((p2m8_bwd_kernel<2, 8>), grid8, dim3(kT8), 0, s, d_desc, d_ids[p] + b0, nblocks, pos, dM, dmass);
+        if (p == 3 && spread) hipLaunchKernelGGL((p2m8_bwd_kernel<3, 1>), grid1, dim3(kT8), 0, s, d_desc, d_ids[p] + b0, nblocks, pos, dM, dmass);
+        else if (p == 3) hipLaunchKernelGGL((p2m8_bwd_kernel<3, 8>), grid8, dim3(kT8), 0, s, d_desc, d_ids[p] + b0, nblocks, pos, dM, dmass);
         if (p == 4) hipLaunchKernelGGL((p2m8_bwd_kernel<4, 1>), grid1, dim3(kT8), 0, s, d_desc, d_ids[p] + b0, nblocks, pos, dM, dmass);
       }
     }

@@ -119,3 +119,31 @@ def test_adjoint_by_rounds_matches_whole_subgrids_and_the_oracle(torch, form, p,
     want, scale = O.m2l_adjoint(W, p, 0.5, mask), O.m2l_adjoint_abs(W, p, 0.5, mask)
     err = np.abs(split_views(whole[:nm].cpu().numpy(), desc[:1], "M")[0] - want)
     assert np.all(err <= TOL * scale)
+
+
+@pytest.mark.parametrize("window", [0, 1])
+@pytest.mark.parametrize("p", [2, 3])
+def test_p2m_of_few_cell_blocks_matches_many(torch, p, window):
+    # 12 sub-grids are more cell blocks than the GPU holds at once, 1 and 3 fewer:
+    # the moments and the mass gradients of a sub-grid have the same bits
+    ensure_library()
+    n = 12
+    rng = np.random.default_rng(7)
+    desc, m_el, _ = fmm.make_descriptors(np.full(n, p), np.zeros(n, int), [synth.random_mask(rng) for _ in range(n)])
+    parts = n * 13824 * 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    pos = 24 * torch.rand(3 * parts, dtype=torch.float64, device="cuda", generator=g)
+    mass = torch.rand(parts, dtype=torch.float64, device="cuda", generator=g)
+    out = {}
+    with fmm.Context(0) as ctx:
+        ctx.set_option(fmm.FMM_OPT_P2M_WINDOW, window)
+        for count in (n, 3, 1):
+            M, dm = torch.zeros(m_el, dtype=torch.float64, device="cuda"), torch.zeros_like(mass)
+            ctx.p2m(desc[:count], pos, mass, 8, M)
+            ctx.p2m_backward(desc[:count], pos, 8, M, dm)
+            torch.cuda.synchronize()
+            out[count] = (M[:m_el // n * count], dm[:parts // n * count])
+    for count in (3, 1):
+        for got, want in zip(out[count], out[n]):
+            assert torch.equal(got, want[:got.numel()])
