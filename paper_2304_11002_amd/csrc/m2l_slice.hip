@@ -152,16 +152,20 @@ __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
   return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
 }
 
-// Part of one round (slice I of the moments) of one sub-grid: the products
-// with the table slices j = J0 .. J0 + NJP - 1 over every live offset quad,
-// then their sums into the float64 accumulators with weight 2^-7(I+j+2). A
-// round runs its table slices (i + j <= S) in passes of at most 4, which keeps
-// the int32 sums of the wave's 8 tiles in 128 registers; the window operands
-// are read from LDS once per pass.
+// One pass of a round (slice I of the moments) of one sub-grid: the products with
+// the table slices j = J0 .. J0 + NJP - 1 over every live offset quad, then their
+// sums into the float64 accumulators with weight 2^-7(I+j+2). The window operands
+// are read from LDS once per pass, and the LDS and the matrix units are about
+// equally busy with two table slices a pass, so a round takes all its slices in
+// one pass while their int32 sums (32 registers each) fit beside the operands.
+// Seven passes at S = 7, p = 3 and 256 sub-grids take 1284 us, 2000 7.74 ms; passes
+// of at most 4 table slices, 13 of them, 1355 us and 8.08 ms (without the fences
+// around a quad, 1431 us and 8.95 ms).
 template <bool FULL, int I, int J0, int NJP>
 __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4i* __restrict__ Bt,
                                            const int* __restrict__ s_off, const uint64_t (&live)[4],
                                            const int (&abase)[8], int lane, double (&fa)[8][4]) {
+  constexpr int NB = NJP > 4 ? 2 : 4;   // sets of table operands
   const int g = lane >> 4;
   v4i acc[NJP][8];
 #pragma unroll
@@ -169,62 +173,54 @@ __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[j][t] = v4i{0, 0, 0, 0};
   // Software pipeline (one wave per SIMD, so nothing else hides latency): the
-  // table operands, from L2, are loaded four quads ahead into a ring of four
-  // sets (each set reloaded right after its products are issued); the window
+  // table operands, from L2, are loaded NB quads ahead into a ring of NB sets
+  // (each set reloaded right after its products are issued); the window
   // operands, from LDS, one quad ahead into two sets; the window offsets two
   // quads ahead. Loads are unconditional, with the
   // quad index clamped to the last quad, so every path into the products sees the
   // same outstanding loads; operands loaded past the last quad are never used.
-  v4i a0[8], a1[8], b0[NJP], b1[NJP], b2[NJP], b3[NJP];
+  v4i a[2][8], b[NB][NJP];
   int o0, o1;   // window offsets (this lane's offset of the quad) of the next two quads
-  auto ldB = [&](v4i(&db)[NJP], int q) __attribute__((always_inline)) {
+  auto ldB = [&](int set, int q) __attribute__((always_inline)) {
     q = min(q, kQuadsS - 1);
 #pragma unroll
-    for (int j = 0; j < NJP; ++j) db[j] = Bt[((size_t)(J0 + j) * kQuadsS + q) * 64 + lane];
+    for (int j = 0; j < NJP; ++j) b[set][j] = Bt[((size_t)(J0 + j) * kQuadsS + q) * 64 + lane];
   };
-  auto ldA = [&](v4i(&da)[8], int off) __attribute__((always_inline)) {
+  auto ldA = [&](int set, int off) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) da[t] = win[abase[t] + off];
+    for (int t = 0; t < 8; ++t) a[set][t] = win[abase[t] + off];
   };
   auto ldO = [&](int q) __attribute__((always_inline)) { return s_off[4 * min(q, kQuadsS - 1) + g]; };
-  auto mma = [&](const v4i(&sa)[8], const v4i(&sb)[NJP]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < NJP; ++j)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) acc[j][t] = mfma_i8(sa[t], sb[j], acc[j][t]);
-  };
   auto is_live = [&](int q) { return (live[q >> 6] >> (q & 63)) & 1ull; };
-  // one step: the window operands of quad Q + 1 go to DA (its offset o0 was read
-  // a step ago), the offset of quad Q + 3 is read, quad Q's products run from
-  // (SA, SB), and SB, free again, takes the table operands of quad Q + 4
-#define SL_STEP(SA, SB, DA, Q)                  \
-  {                                             \
-    ldA(DA, o0);                                \
-    o0 = o1;                                    \
-    o1 = ldO((Q) + 3);                          \
-    if (FULL || is_live(Q)) mma(SA, SB);        \
-    ldB(SB, (Q) + 4);                           \
-  }
+  // quad q + u: the window operands of the next quad (its offset o0 was read a step
+  // ago), the offset of the third next, the products, and the freed table set
+  auto step = [&](int q, int u) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    ldA((u + 1) & 1, o0);
+    o0 = o1;
+    o1 = ldO(q + u + 3);
+    if (FULL || is_live(q + u)) {
+#pragma unroll
+      for (int j = 0; j < NJP; ++j)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[j][t] = mfma_i8(a[u & 1][t], b[u % NB][j], acc[j][t]);
+    }
+    ldB(u % NB, q + u + NB);
+    __builtin_amdgcn_sched_barrier(0);
+  };
   static_assert(kQuadsS % 4 == 3, "groups of four quads, then three");
-  // prologue: window operands of quad 0, offsets of quads 1 and 2, tables of quads 0-3
-  ldA(a0, ldO(0));
+  ldA(0, ldO(0));
   o0 = ldO(1);
   o1 = ldO(2);
-  ldB(b0, 0);
-  ldB(b1, 1);
-  ldB(b2, 2);
-  ldB(b3, 3);
+#pragma unroll
+  for (int u = 0; u < NB; ++u) ldB(u, u);
 #pragma unroll 1
   for (int q = 0; q + 4 < kQuadsS; q += 4) {
-    SL_STEP(a0, b0, a1, q);
-    SL_STEP(a1, b1, a0, q + 1);
-    SL_STEP(a0, b2, a1, q + 2);
-    SL_STEP(a1, b3, a0, q + 3);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) step(q, u);
   }
-  SL_STEP(a0, b0, a1, kQuadsS - 3);
-  SL_STEP(a1, b1, a0, kQuadsS - 2);
-  SL_STEP(a0, b2, a1, kQuadsS - 1);
-#undef SL_STEP
+#pragma unroll
+  for (int u = 0; u < 3; ++u) step(kQuadsS - 3, u);
 #pragma unroll
   for (int j = 0; j < NJP; ++j) {
     const double wgt = ldexp(1.0, -7 * (I + J0 + j + 2));
@@ -235,13 +231,15 @@ __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4
   }
 }
 
-// Round I: table slices j < NJ = min(S, S - I + 1), in passes of at most 4.
+// Round I: table slices j < NJ = min(S, S - I + 1), in one pass up to kPassMax of
+// them, else in passes of at most 4.
+constexpr int kPassMax = 7;
 template <bool FULL, int I, int J0, int NJ>
 __device__ __forceinline__ void slice_round(const v4i* __restrict__ win, const v4i* __restrict__ Bt,
                                             const int* __restrict__ s_off, const uint64_t (&live)[4],
                                             const int (&abase)[8], int lane, double (&fa)[8][4]) {
   if constexpr (J0 < NJ) {
-    constexpr int NJP = NJ - J0 < 4 ? NJ - J0 : 4;
+    constexpr int NJP = NJ <= kPassMax ? NJ : NJ - J0 < 4 ? NJ - J0 : 4;
     slice_pass<FULL, I, J0, NJP>(win, Bt, s_off, live, abase, lane, fa);
     slice_round<FULL, I, J0 + NJP, NJ>(win, Bt, s_off, live, abase, lane, fa);
   }
