@@ -10,15 +10,15 @@
 // |d|^2 <= 4, in present blocks. The near sums dominate (263 pairs per
 // particle at 8 per cell) and are bound by FP64 VALU issue.
 //
-// Work decomposition: one workgroup per (sub-grid, target z-plane): 64 target
-// cells, each thread owning R particles of one cell. The source planes
+// Work decomposition: one workgroup per (sub-grid, target z-plane or half of
+// one): 64 or 32 target cells, each thread owning R particles of one cell. The source planes
 // z-2 .. z+2 pass through LDS one at a time (only the cells the plane's
 // offsets reach: 12^2, 10^2 or 8^2), in chunks of 8 particles per cell.
 // Absent blocks are staged as zero mass far away, which adds exact zeros, so
 // the inner loop has no tests; a full chunk's loop is unrolled, a last chunk of
 // fewer particles runs as many as it has (300 sub-grids: 1 particle per cell 269 ->
-// 95 us, 3 275 -> 153, 5 298 -> 235, 13 1100 -> 985). The eight
-// planes of one sub-grid run on one XCD (workgroups are dealt round-robin
+// 95 us, 3 275 -> 153, 5 298 -> 235, 13 1100 -> 985). The
+// workgroups of one sub-grid run on one XCD (they are dealt round-robin
 // over the 8 XCDs), so overlapping source planes are re-read from that
 // XCD's L2.
 #include <type_traits>
@@ -30,7 +30,17 @@ namespace fmm {
 constexpr int kEvThreads = 256;
 constexpr int kEvKC = 8;                 // source particles per cell per staged chunk
 constexpr int kEvW = 12;                 // staged plane width: frame cells [6, 18) per axis
-constexpr int kEvR = 2;                  // target particles per thread (one cell)
+// Shapes of a workgroup's targets: R particles of one cell per thread, NY rows of a
+// z-plane. EvWide where workgroups are many; EvHalf, with half the chain of pairs
+// in a thread and twice the workgroups, where they are few.
+struct EvWide {
+  static constexpr int R = 2, NY = 8;
+};
+struct EvHalf {
+  static constexpr int R = 1, NY = 4;
+};
+template <class Shape>
+constexpr int kEvSlices = 8 * (8 / Shape::NY);   // workgroups per block
 constexpr double kEvFar = 1e100;         // coordinate of padding sources (zero mass)
 
 // 1/sqrt(x) to float64 accuracy: the single-precision hardware estimate
@@ -52,13 +62,13 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
 // buffer resource: lane offset vo (the cell), component c at the scalar
 // offset c * cstride bytes, so no per-load address registers; each component
 // is read once for all R targets.
-template <int P>
+template <int P, int R>
 __device__ __forceinline__ void l2p_add(__amdgpu_buffer_rsrc_t Lr, int vo, int cstride,
-                                        const double (&b)[kEvR][3], double (&acc)[kEvR][4]) {
+                                        const double (&b)[R][3], double (&acc)[R][4]) {
   constexpr int C = ncomp(P);
-  double pw[kEvR][3][P + 1];                    // b_axis^i / i!
+  double pw[R][3][P + 1];                    // b_axis^i / i!
 #pragma unroll
-  for (int r = 0; r < kEvR; ++r)
+  for (int r = 0; r < R; ++r)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       pw[r][a][0] = 1.0;
@@ -71,7 +81,7 @@ __device__ __forceinline__ void l2p_add(__amdgpu_buffer_rsrc_t Lr, int vo, int c
     const double l = __builtin_bit_cast(
         double, __builtin_amdgcn_raw_buffer_load_b64(Lr, vo, c * cstride, 0));
 #pragma unroll
-    for (int r = 0; r < kEvR; ++r) {
+    for (int r = 0; r < R; ++r) {
       const double(&x)[P + 1] = pw[r][0];
       const double(&y)[P + 1] = pw[r][1];
       const double(&z)[P + 1] = pw[r][2];
@@ -85,12 +95,12 @@ __device__ __forceinline__ void l2p_add(__amdgpu_buffer_rsrc_t Lr, int vo, int c
 }
 
 // One source particle against the thread's R targets.
-template <bool SELF>
-__device__ __forceinline__ void near_pair(const double (&ty)[kEvR][3], double (&acc)[kEvR][4],
-                                          const int (&tk)[kEvR], double sx, double sy, double sz,
+template <bool SELF, int R>
+__device__ __forceinline__ void near_pair(const double (&ty)[R][3], double (&acc)[R][4],
+                                          const int (&tk)[R], double sx, double sy, double sz,
                                           double sm, int k) {
 #pragma unroll
-  for (int r = 0; r < kEvR; ++r) {
+  for (int r = 0; r < R; ++r) {
     const double dx = ty[r][0] - sx, dy = ty[r][1] - sy, dz = ty[r][2] - sz;
     double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
     double m = sm;
@@ -151,18 +161,18 @@ struct GridGeom {
 };
 
 // Stages particles ch*8 .. min(ch*8+8, ppc) of the cells of frame plane fz that
-// the offsets of reach RR (|dx|, |dy| <= RR) touch: (8 + 2 RR)^2 cells.
-template <int RR, class Geom>
+// the offsets of reach RR (|dx|, |dy| <= RR) touch: (8 + 2 RR) x (NY + 2 RR) cells.
+template <int RR, int NY, class Geom>
 __device__ __forceinline__ void stage_plane(double* __restrict__ s, const Geom& geo,
                                             const double* __restrict__ pos,
-                                            const double* __restrict__ mass, int ppc, int fz,
+                                            const double* __restrict__ mass, int ppc, int y0, int fz,
                                             int ch) {
   constexpr int WR = 8 + 2 * RR;
-  constexpr int NITEMS = WR * WR * kEvKC;
+  constexpr int NITEMS = WR * (NY + 2 * RR) * kEvKC;
   for (int it = threadIdx.x; it < NITEMS; it += kEvThreads) {
     const int kk = it % kEvKC;
     const int c = it / kEvKC;
-    const int fx = 8 - RR + c % WR, fy = 8 - RR + c / WR;
+    const int fx = 8 - RR + c % WR, fy = 8 - RR + y0 + c / WR;
     const int k = ch * kEvKC + kk;
     if (k >= ppc) continue;                    // (a slot that a short chunk does not read)
     double2 xy = make_double2(kEvFar, kEvFar), zm = make_double2(kEvFar, 0.0);
@@ -181,9 +191,9 @@ __device__ __forceinline__ void stage_plane(double* __restrict__ s, const Geom& 
 
 // The staged particles of one source cell (s: its first slot) against the thread's
 // targets; k0: index of the first particle within its cell (SELF).
-template <bool SELF, bool FULL>
-__device__ __forceinline__ void near_cell(const double* s, const double (&ty)[kEvR][3], double (&acc)[kEvR][4],
-                                          const int (&tk)[kEvR], int k0, int nk) {
+template <bool SELF, bool FULL, int R>
+__device__ __forceinline__ void near_cell(const double* s, const double (&ty)[R][3], double (&acc)[R][4],
+                                          const int (&tk)[R], int k0, int nk) {
   auto pair = [&](int kk) __attribute__((always_inline)) {
     const double2 xy = *reinterpret_cast<const double2*>(s + kk * kEvSlot);
     const double2 zm = *reinterpret_cast<const double2*>(s + kk * kEvSlot + 2);
@@ -198,30 +208,31 @@ __device__ __forceinline__ void near_cell(const double* s, const double (&ty)[kE
   }
 }
 
-// One target z-plane tz of one block: near sums over the staged source planes,
-// then L2P, written for the block's 64 x ppc particles.
-template <class Geom>
+// Rows y0 .. y0 + NY - 1 of target z-plane tz of one block: near sums over the staged
+// source planes, then L2P, written for their 8 NY x ppc particles.
+template <class Shape, class Geom>
 __device__ __forceinline__ void evaluate_plane(double* __restrict__ s_src, const Geom& geo, int p,
-                                               double h, int tz, const double* __restrict__ pos,
+                                               double h, int tz, int y0, const double* __restrict__ pos,
                                                const double* __restrict__ mass, int ppc,
                                                const double* __restrict__ L, double* __restrict__ out) {
+  constexpr int R = Shape::R, NY = Shape::NY;
   const int64_t p0 = geo.part0();
-  const int G = (ppc + kEvR - 1) / kEvR;       // threads per target cell
-  const int nslot = 64 * G;
+  const int G = (ppc + R - 1) / R;       // threads per target cell
+  const int nslot = 8 * NY * G;
   const int nch = (ppc + kEvKC - 1) / kEvKC;
   const int64_t ncell = geo.ncells_out();
 
   for (int slot0 = 0; slot0 < nslot; slot0 += kEvThreads) {
     const int slot = slot0 + (int)threadIdx.x;
-    const int q = slot / G;                    // target cell within the plane (>= 64: idle)
+    const int q = slot / G;                    // target cell within the plane (>= 8 NY: idle)
     const int g = slot - q * G;
-    const bool active = q < 64;
-    const int cx = q & 7, cy = (q >> 3) & 7;
+    const bool active = q < 8 * NY;
+    const int cx = q & 7, cy = y0 + ((q >> 3) & (NY - 1));
     const int64_t tcell = geo.cell(8 + cx, 8 + cy, 8 + tz);
-    double ty[kEvR][3], acc[kEvR][4];
-    int tk[kEvR];
+    double ty[R][3], acc[R][4];
+    int tk[R];
 #pragma unroll
-    for (int r = 0; r < kEvR; ++r) {
+    for (int r = 0; r < R; ++r) {
       tk[r] = g + r * G;
       // idle slots take a point outside the domain (their results are not written)
       ty[r][0] = ty[r][1] = ty[r][2] = -1e30;
@@ -242,9 +253,9 @@ __device__ __forceinline__ void evaluate_plane(double* __restrict__ s_src, const
       for (int ch = 0; ch < nch; ++ch) {
         __syncthreads();                       // the previous chunk is consumed
         const int nk = min(ppc - ch * kEvKC, kEvKC);   // staged particles per cell
-        if (rr == 2) stage_plane<2>(s_src, geo, pos, mass, ppc, fz, ch);
-        else if (rr == 1) stage_plane<1>(s_src, geo, pos, mass, ppc, fz, ch);
-        else stage_plane<0>(s_src, geo, pos, mass, ppc, fz, ch);
+        if (rr == 2) stage_plane<2, NY>(s_src, geo, pos, mass, ppc, y0, fz, ch);
+        else if (rr == 1) stage_plane<1, NY>(s_src, geo, pos, mass, ppc, y0, fz, ch);
+        else stage_plane<0, NY>(s_src, geo, pos, mass, ppc, y0, fz, ch);
         __syncthreads();
         auto near_cells = [&](auto full) __attribute__((always_inline)) {
           for (int oy = -rr; oy <= rr; ++oy) {
@@ -270,9 +281,9 @@ __device__ __forceinline__ void evaluate_plane(double* __restrict__ s_src, const
       const double ccx = (geo.coord(8 + cx, 0) + 0.5) * h, ccy = (geo.coord(8 + cy, 1) + 0.5) * h,
                    ccz = (geo.coord(8 + tz, 2) + 0.5) * h;
       double* o = out + t * ppc;
-      double bb[kEvR][3];
+      double bb[R][3];
 #pragma unroll
-      for (int r = 0; r < kEvR; ++r) {
+      for (int r = 0; r < R; ++r) {
         bb[r][0] = ty[r][0] - ccx;
         bb[r][1] = ty[r][1] - ccy;
         bb[r][2] = ty[r][2] - ccz;
@@ -284,7 +295,7 @@ __device__ __forceinline__ void evaluate_plane(double* __restrict__ s_src, const
         default: break;
       }
 #pragma unroll
-      for (int r = 0; r < kEvR; ++r) {
+      for (int r = 0; r < R; ++r) {
         if (tk[r] >= ppc) continue;
 #pragma unroll
         for (int c = 0; c < 4; ++c) o[(int64_t)c * ncell * ppc + tk[r]] = acc[r][c];
@@ -293,24 +304,27 @@ __device__ __forceinline__ void evaluate_plane(double* __restrict__ s_src, const
   }
 }
 
+template <class Shape>
 __global__ void __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(4))) evaluate_kernel(
     const DevDesc* __restrict__ desc, int nsub, const double* __restrict__ pos,
     const double* __restrict__ mass, int ppc, const double* __restrict__ L,
     double* __restrict__ out) {
   __shared__ __attribute__((aligned(16))) double s_src[kEvLds];
-  // block i -> XCD i % 8; the 8 planes of sub-grid b are blocks 8 apart
+  // block i -> XCD i % 8; the workgroups of sub-grid b are blocks 8 apart
   const int i = blockIdx.x;
-  const int b = (i / 64) * 8 + (i % 8);
-  const int tz = (i / 8) % 8;
+  constexpr int kSlices = kEvSlices<Shape>;
+  const int b = i / (8 * kSlices) * 8 + i % 8;
+  const int slice = i / 8 % kSlices, tz = slice * 8 / kSlices, y0 = Shape::NY * (slice % (kSlices / 8));
   if (b >= nsub) return;                       // whole workgroup: no barrier is skipped by part of it
   FrameGeom geo;
   geo.d = desc[b];
-  evaluate_plane(s_src, geo, geo.d.p, ldexp(1.0, -geo.d.log2_inv_h), tz, pos, mass, ppc,
+  evaluate_plane<Shape>(s_src, geo, geo.d.p, ldexp(1.0, -geo.d.log2_inv_h), tz, y0, pos, mass, ppc,
                  L + geo.d.l_off, out + (int64_t)b * 4 * kNTarget * ppc);
 }
 
 // The finest level of a uniform n^3 domain: (n/8)^3 blocks x 8 planes, the
 // planes of one block dealt to one XCD as above.
+template <class Shape>
 __global__ void __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu(4))) evaluate_grid_kernel(
     int p, int n, double h, const double* __restrict__ pos, const double* __restrict__ mass, int ppc,
     const double* __restrict__ L, double* __restrict__ out) {
@@ -318,32 +332,47 @@ __global__ void __launch_bounds__(kEvThreads) __attribute__((amdgpu_waves_per_eu
   const int nb = n / 8;
   const int nblk = nb * nb * nb;
   const int i = blockIdx.x;
-  const int b = (i / 64) * 8 + (i % 8);
-  const int tz = (i / 8) % 8;
+  constexpr int kSlices = kEvSlices<Shape>;
+  const int b = i / (8 * kSlices) * 8 + i % 8;
+  const int slice = i / 8 % kSlices, tz = slice * 8 / kSlices, y0 = Shape::NY * (slice % (kSlices / 8));
   if (b >= nblk) return;
   GridGeom geo;
   geo.n = n;
   geo.ox = 8 * (b % nb) - 8;
   geo.oy = 8 * ((b / nb) % nb) - 8;
   geo.oz = 8 * (b / (nb * nb)) - 8;
-  evaluate_plane(s_src, geo, p, h, tz, pos, mass, ppc, L, out);
+  evaluate_plane<Shape>(s_src, geo, p, h, tz, y0, pos, mass, ppc, L, out);
 }
+
+// Half planes while whole planes would be fewer than two workgroups per CU (256 of
+// them): 1 sub-grid of 8 particles per cell 47.5 -> 34.6 us, 43 77.1 -> 62.2 (3
+// particles 42.8 -> 38.7); at 64 as long (83.0 and 81.2; 3 particles 44.9 and 47.4),
+// beyond slower (300: 328 and 334; 155 and 179), as each LDS read serves one target.
+static bool ev_half(int64_t blocks) { return blocks < 64; }
 
 hipError_t launch_evaluate(const DevDesc* d_desc, int64_t nsub, const double* pos,
                            const double* mass, int ppc, const double* L, double* out,
                            hipStream_t s) {
-  const int64_t groups = (nsub + 7) / 8 * 64;
-  hipLaunchKernelGGL(evaluate_kernel, dim3((unsigned)groups), dim3(kEvThreads), 0, s, d_desc,
-                     (int)nsub, pos, mass, ppc, L, out);
+  const int64_t octs = (nsub + 7) / 8;
+  if (ev_half(nsub))
+    hipLaunchKernelGGL(evaluate_kernel<EvHalf>, dim3((unsigned)(octs * 8 * kEvSlices<EvHalf>)), dim3(kEvThreads), 0, s,
+                       d_desc, (int)nsub, pos, mass, ppc, L, out);
+  else
+    hipLaunchKernelGGL(evaluate_kernel<EvWide>, dim3((unsigned)(octs * 8 * kEvSlices<EvWide>)), dim3(kEvThreads), 0, s,
+                       d_desc, (int)nsub, pos, mass, ppc, L, out);
   return hipGetLastError();
 }
 
 hipError_t launch_evaluate_grid(int p, int n, double h, const double* pos, const double* mass,
                                 int ppc, const double* L, double* out, hipStream_t s) {
   const int64_t nblk = (int64_t)(n / 8) * (n / 8) * (n / 8);
-  const int64_t groups = (nblk + 7) / 8 * 64;
-  hipLaunchKernelGGL(evaluate_grid_kernel, dim3((unsigned)groups), dim3(kEvThreads), 0, s, p, n, h,
-                     pos, mass, ppc, L, out);
+  const int64_t octs = (nblk + 7) / 8;
+  if (ev_half(nblk))
+    hipLaunchKernelGGL(evaluate_grid_kernel<EvHalf>, dim3((unsigned)(octs * 8 * kEvSlices<EvHalf>)), dim3(kEvThreads), 0,
+                       s, p, n, h, pos, mass, ppc, L, out);
+  else
+    hipLaunchKernelGGL(evaluate_grid_kernel<EvWide>, dim3((unsigned)(octs * 8 * kEvSlices<EvWide>)), dim3(kEvThreads), 0,
+                       s, p, n, h, pos, mass, ppc, L, out);
   return hipGetLastError();
 }
 

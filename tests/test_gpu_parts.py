@@ -147,3 +147,32 @@ def test_p2m_of_few_cell_blocks_matches_many(torch, p, window):
     for count in (3, 1):
         for got, want in zip(out[count], out[n]):
             assert torch.equal(got, want[:got.numel()])
+
+
+@pytest.mark.parametrize("ppc", [1, 3, 8, 11])
+def test_evaluation_by_half_planes_matches_whole_planes(torch, ppc):
+    # up to 63 sub-grids run by half planes with one target per thread, more by
+    # whole planes with two: the same bits (the oracle checks both sizes elsewhere
+    # by the few sub-grids)
+    ensure_library()
+    n = 65
+    rng = np.random.default_rng([5, ppc])
+    desc, _, l_el = fmm.make_descriptors(np.arange(n) % 3 + 2, np.zeros(n, int),
+                                         [synth.random_mask(rng) for _ in range(n)], ppc)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ppc)
+    parts = n * 13824 * ppc
+    cell = torch.arange(13824, device="cuda")
+    corner = torch.stack((cell % 24, cell // 24 % 24, cell // 576), 1).double().repeat_interleave(ppc, 0)
+    pos = (corner.repeat(n, 1) + torch.rand(parts, 3, dtype=torch.float64, device="cuda", generator=g)).reshape(-1)
+    mass = torch.rand(parts, dtype=torch.float64, device="cuda", generator=g)
+    L = torch.randn(l_el, dtype=torch.float64, device="cuda", generator=g)
+    out = {}
+    with fmm.Context(0) as ctx:
+        for count in (n, 63, 2):
+            out[count] = torch.full((count * 4 * 512 * ppc,), float("nan"), dtype=torch.float64, device="cuda")
+            ctx.evaluate(desc[:count], pos, mass, ppc, L, out[count])
+        torch.cuda.synchronize()
+    assert bool(torch.isfinite(out[n]).all())
+    for count in (63, 2):
+        assert torch.equal(out[count], out[n][:out[count].numel()])
