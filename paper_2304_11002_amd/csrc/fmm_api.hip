@@ -103,11 +103,10 @@ struct DescEntry {
   DevDesc* d_desc = nullptr;
   int* d_ids[kMaxP + 1] = {};     // reference kernels: sub-grids per order
   int count[kMaxP + 1] = {};
-  WorkList work;                  // matrix-core kernels, dense-form costs (C^2 per pair)
-  WorkList work_h;                // the same items ordered by harmonic-form costs ((p+1)^4)
-  // streamed forward, per form (dense, harmonic): whole sub-grids, and their parts
-  // (where planned or small enough to be asked for), with a counter that its
-  // launches leave at zero
+  WorkList work;                  // per-wave kernels: whole[0]'s items, a counter that its launches reset
+  // per form (dense, harmonic): whole sub-grids, longest first, and their parts
+  // (streamed forward, where planned or small enough to be asked for), with a
+  // counter that the launches leave at zero
   WorkList whole[2];
   WorkList parts[2];
   StreamPlan plan[2];
@@ -360,7 +359,7 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     off_ids[p] = off;
     off = align_up(off + sizeof(int) * ids[p].size(), 256);
   }
-  size_t off_work[2], off_parts[2], off_rounds[2], off_counter[2], off_zero[2];
+  size_t off_work[2], off_parts[2], off_rounds[2], off_zero[2];
   for (int f = 0; f < 2; ++f) {
     off_work[f] = off;
     off = align_up(off + sizeof(WorkItem) * items[f].size(), 256);
@@ -368,11 +367,11 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     off = align_up(off + sizeof(WorkItem) * parts[f].size(), 256);
     off_rounds[f] = off;
     off = align_up(off + sizeof(WorkItem) * rounds[f].size(), 256);
-    off_counter[f] = off;
-    off = align_up(off + 256, 256);
     off_zero[f] = off;
     off = align_up(off + 256, 256);
   }
+  const size_t off_counter = off;
+  off = align_up(off + 256, 256);
   e->bytes = off;
   HIP_TRY(ctx, hipMalloc(&e->dev, e->bytes));
   HIP_TRY(ctx, hipHostMalloc(&e->pinned, e->bytes, hipHostMallocDefault));
@@ -392,11 +391,8 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     e->count[p] = (int)ids[p].size();
   }
   for (int f = 0; f < 2; ++f) {
-    WorkList& w = f ? e->work_h : e->work;
-    w.items = reinterpret_cast<const WorkItem*>(dp + off_work[f]);
-    w.count = (int)items[f].size();
-    w.counter = reinterpret_cast<unsigned*>(dp + off_counter[f]);
-    e->whole[f] = w;
+    e->whole[f].items = reinterpret_cast<const WorkItem*>(dp + off_work[f]);
+    e->whole[f].count = (int)items[f].size();
     e->whole[f].counter = reinterpret_cast<unsigned*>(dp + off_zero[f]);
     e->parts[f].items = reinterpret_cast<const WorkItem*>(dp + off_parts[f]);
     e->parts[f].count = (int)parts[f].size();
@@ -408,6 +404,8 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     e->rounds[f].counter = e->whole[f].counter;
     e->rounds[f].parts = true;
   }
+  e->work = e->whole[0];
+  e->work.counter = reinterpret_cast<unsigned*>(dp + off_counter);
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->ready, hipEventDisableTiming));
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->last_launch, hipEventDisableTiming));
   HIP_TRY(ctx, hipMemcpyAsync(e->dev, e->pinned, e->bytes, hipMemcpyHostToDevice, stream));
@@ -417,9 +415,6 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
   ctx->descs.push_back(std::move(e));
   return FMM_OK;
 }
-
-// the work list ordered by the costs of the form that runs
-const WorkList& work_for(const DescEntry* e, bool harmonic) { return harmonic ? e->work_h : e->work; }
 
 fmm_status mark_used(fmm_ctx* ctx, DescEntry* e, hipStream_t stream) {
   HIP_TRY(ctx, hipEventRecord(e->last_launch, stream));
@@ -788,7 +783,7 @@ static fmm_status run_ref(fmm_ctx* ctx, DescEntry* e, bool backward, const doubl
 // graph if enabled.
 static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* L,
                            fmm_precision prec, int cfg, hipStream_t s) {
-  const WorkList& wl = work_for(e, prec == FMM_FP64_HARMONIC);
+  const WorkList& wl = e->work;
   if (!ctx->use_graph) {
     HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, e->d_desc, M, L, prec, cfg, s));
     return FMM_OK;
@@ -851,7 +846,7 @@ static fmm_status run_slice(fmm_ctx* ctx, DescEntry* e, const double* M, double*
   }
   int8_t* pl = static_cast<int8_t*>(e->slice_dev);
   int32_t* ex = reinterpret_cast<int32_t*>(pl + planes);
-  HIP_TRY(ctx, launch_m2l_slice(ctx->mfma, ctx->slice, e->work_h, e->d_desc, nsub, M, L, ctx->slices, pl, ex, s));
+  HIP_TRY(ctx, launch_m2l_slice(ctx->mfma, ctx->slice, e->whole[1], e->d_desc, nsub, M, L, ctx->slices, pl, ex, s));
   return FMM_OK;
 }
 
@@ -1102,7 +1097,7 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
       const bool harm = prec == FMM_FP64_HARMONIC;
       return mfma_config_streams(cfg) ? launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s)
              : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, e->whole[0], e->d_desc, M, L, s)
-                                      : launch_m2l_mfma(ctx->mfma, work_for(e, harm), e->d_desc, M, L, prec, cfg, s);
+                                      : launch_m2l_mfma(ctx->mfma, e->work, e->d_desc, M, L, prec, cfg, s);
     };
     HIP_TRY(ctx, launch());
     float cfg_ms = 1e30f;

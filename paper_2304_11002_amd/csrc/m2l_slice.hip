@@ -19,11 +19,12 @@
 //   components, round-plan order, zero past (p+1)^2 and on absent blocks).
 // * m2l_fwd_slice_kernel: persistent, one workgroup of 4 waves per CU (one
 //   wave per SIMD, up to 512 registers each). Wave w owns target planes
-//   2w, 2w+1: eight 16-cell tiles. Per round i the workgroup stages slice
-//   plane i in LDS (128,000 bytes); per offset quad each wave reads its 8 A
+//   2w, 2w+1: eight 16-cell tiles (of a half sub-grid, one plane of its four,
+//   four tiles). Per round i the workgroup stages slice
+//   plane i in LDS (128,000 bytes); per offset quad each wave reads its A
 //   operands (16 bytes per lane: cell t + d of the lane's offset, 16 folded
 //   components) and, for every j with i + j <= S, one B operand from the
-//   L2-resident tables, and issues 8 v_mfma_i32_16x16x64_i8 into the int32
+//   L2-resident tables, and issues a v_mfma_i32_16x16x64_i8 per tile into the int32
 //   sums of (tile, j). At the end of the round the sums are added to float64
 //   accumulators with weight 2^-7(i+j+2). The epilogue scales by
 //   2^(e_A + e_B), expands L~ to all C components through LDS and applies
@@ -59,8 +60,6 @@ struct SliceConst {
   int32_t f[2][16];    // [p - 2][byte]: prescale exponents of the folded rows
   int32_t eB[2][16];   // [p - 2][column]: table column exponents
 };
-
-__global__ void reset_slice_counter(unsigned* c) { *c = 0u; }
 
 // The folded, h-scaled and prescaled moments of window cell c (zero on absent
 // blocks), in round-plan order: byte 2 r + u is the round's u-th folded component.
@@ -161,17 +160,17 @@ __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
 // Seven passes at S = 7, p = 3 and 256 sub-grids take 1284 us, 2000 7.74 ms; passes
 // of at most 4 table slices, 13 of them, 1355 us and 8.08 ms (without the fences
 // around a quad, 1431 us and 8.95 ms).
-template <bool FULL, int I, int J0, int NJP>
+template <bool FULL, int TPW, int I, int J0, int NJP>
 __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4i* __restrict__ Bt,
                                            const int* __restrict__ s_off, const uint64_t (&live)[4],
-                                           const int (&abase)[8], int lane, double (&fa)[8][4]) {
+                                           const int (&abase)[TPW], int lane, double (&fa)[TPW][4]) {
   constexpr int NB = NJP > 4 ? 2 : 4;   // sets of table operands
   const int g = lane >> 4;
-  v4i acc[NJP][8];
+  v4i acc[NJP][TPW];
 #pragma unroll
   for (int j = 0; j < NJP; ++j)
 #pragma unroll
-    for (int t = 0; t < 8; ++t) acc[j][t] = v4i{0, 0, 0, 0};
+    for (int t = 0; t < TPW; ++t) acc[j][t] = v4i{0, 0, 0, 0};
   // Software pipeline (one wave per SIMD, so nothing else hides latency): the
   // table operands, from L2, are loaded NB quads ahead into a ring of NB sets
   // (each set reloaded right after its products are issued); the window
@@ -179,7 +178,7 @@ __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4
   // quads ahead. Loads are unconditional, with the
   // quad index clamped to the last quad, so every path into the products sees the
   // same outstanding loads; operands loaded past the last quad are never used.
-  v4i a[2][8], b[NB][NJP];
+  v4i a[2][TPW], b[NB][NJP];
   int o0, o1;   // window offsets (this lane's offset of the quad) of the next two quads
   auto ldB = [&](int set, int q) __attribute__((always_inline)) {
     q = min(q, kQuadsS - 1);
@@ -188,7 +187,7 @@ __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4
   };
   auto ldA = [&](int set, int off) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) a[set][t] = win[abase[t] + off];
+    for (int t = 0; t < TPW; ++t) a[set][t] = win[abase[t] + off];
   };
   auto ldO = [&](int q) __attribute__((always_inline)) { return s_off[4 * min(q, kQuadsS - 1) + g]; };
   auto is_live = [&](int q) { return (live[q >> 6] >> (q & 63)) & 1ull; };
@@ -203,7 +202,7 @@ __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4
 #pragma unroll
       for (int j = 0; j < NJP; ++j)
 #pragma unroll
-        for (int t = 0; t < 8; ++t) acc[j][t] = mfma_i8(a[u & 1][t], b[u % NB][j], acc[j][t]);
+        for (int t = 0; t < TPW; ++t) acc[j][t] = mfma_i8(a[u & 1][t], b[u % NB][j], acc[j][t]);
     }
     ldB(u % NB, q + u + NB);
     __builtin_amdgcn_sched_barrier(0);
@@ -225,7 +224,7 @@ __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4
   for (int j = 0; j < NJP; ++j) {
     const double wgt = ldexp(1.0, -7 * (I + J0 + j + 2));
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) fa[t][v] = __builtin_fma((double)acc[j][t][v], wgt, fa[t][v]);
   }
@@ -234,34 +233,36 @@ __device__ __forceinline__ void slice_pass(const v4i* __restrict__ win, const v4
 // Round I: table slices j < NJ = min(S, S - I + 1), in one pass up to kPassMax of
 // them, else in passes of at most 4.
 constexpr int kPassMax = 7;
-template <bool FULL, int I, int J0, int NJ>
+template <bool FULL, int TPW, int I, int J0, int NJ>
 __device__ __forceinline__ void slice_round(const v4i* __restrict__ win, const v4i* __restrict__ Bt,
                                             const int* __restrict__ s_off, const uint64_t (&live)[4],
-                                            const int (&abase)[8], int lane, double (&fa)[8][4]) {
+                                            const int (&abase)[TPW], int lane, double (&fa)[TPW][4]) {
   if constexpr (J0 < NJ) {
     constexpr int NJP = NJ <= kPassMax ? NJ : NJ - J0 < 4 ? NJ - J0 : 4;
-    slice_pass<FULL, I, J0, NJP>(win, Bt, s_off, live, abase, lane, fa);
-    slice_round<FULL, I, J0 + NJP, NJ>(win, Bt, s_off, live, abase, lane, fa);
+    slice_pass<FULL, TPW, I, J0, NJP>(win, Bt, s_off, live, abase, lane, fa);
+    slice_round<FULL, TPW, I, J0 + NJP, NJ>(win, Bt, s_off, live, abase, lane, fa);
   }
 }
 
-template <bool FULL, int S, int I>
+template <bool FULL, int TPW, int S, int I>
 __device__ __forceinline__ void slice_rounds(const int8_t* __restrict__ pl, v4i* win,
                                              const v4i* __restrict__ Bt, const int* s_off,
-                                             const uint64_t (&live)[4], const int (&abase)[8], int lane,
-                                             double (&fa)[8][4]) {
+                                             const uint64_t (&live)[4], const int (&abase)[TPW], int lane,
+                                             double (&fa)[TPW][4], int c0, int c1) {
   if constexpr (I < S) {
     __syncthreads();   // the previous round's reads of the window are done
     const v4i* gp = reinterpret_cast<const v4i*>(pl + (size_t)I * kSlicePlane);
-    for (int c = threadIdx.x; c < kWinCells; c += kSliceThreads) win[c] = gp[c];
+    for (int c = c0 + threadIdx.x; c < c1; c += kSliceThreads) win[c] = gp[c];
     __syncthreads();
     constexpr int NJ = (S - I + 1) < S ? (S - I + 1) : S;
-    slice_round<FULL, I, 0, NJ>(win, Bt, s_off, live, abase, lane, fa);
-    slice_rounds<FULL, S, I + 1>(pl, win, Bt, s_off, live, abase, lane, fa);
+    slice_round<FULL, TPW, I, 0, NJ>(win, Bt, s_off, live, abase, lane, fa);
+    slice_rounds<FULL, TPW, S, I + 1>(pl, win, Bt, s_off, live, abase, lane, fa, c0, c1);
   }
 }
 
-template <int S>
+// Work: every sub-grid of `items` whole (TPW = 8) or in halves (4), count in total.
+// With a counter the workgroups take from it; without, workgroup i runs number i.
+template <int S, int TPW>
 __global__ void __launch_bounds__(kSliceThreads) m2l_fwd_slice_kernel(
     const WorkItem* __restrict__ items, int count, unsigned* __restrict__ counter,
     const DevDesc* __restrict__ desc, double* __restrict__ L, const int8_t* __restrict__ planes,
@@ -271,72 +272,82 @@ __global__ void __launch_bounds__(kSliceThreads) m2l_fwd_slice_kernel(
   __shared__ v4i win[kWinCells];            // 128,000 bytes: one slice plane of the window
   __shared__ int s_off[kNStencil];
   __shared__ int s_item;
+  constexpr int NZ = TPW / 4;                 // planes of a wave
+  constexpr int NTG = kNTarget * TPW / 8;     // targets of the item
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ci = lane & 15;
   for (int i = tid; i < kNStencil; i += kSliceThreads) s_off[i] = lds_off[i];
-  // tile t of this wave: target plane 2 wave + t / 4, 4x4 patch ((t & 1) * 4, ((t >> 1) & 1) * 4)
-  int abase[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int x = (t & 1) * 4 + (ci & 3), y = ((t >> 1) & 1) * 4 + (ci >> 2), z = 2 * wave + (t >> 2);
-    abase[t] = (x + 6) + kWin * (y + 6) + kWin * kWin * (z + 6);
-  }
   for (;;) {
-    if (tid == 0) s_item = (int)atomicAdd(counter, 1u);
+    if (counter && tid == 0) s_item = (int)atomicAdd(counter, 1u);
     __syncthreads();
-    const int item = s_item;
-    if (item >= count) break;
-    const int b = items[item].sub;
+    const int item = counter ? s_item : (int)blockIdx.x;
+    if (item >= count) {
+      // the last of the numbers past the items clears the counter for the next launch
+      if (counter && tid == 0 && item == count + (int)gridDim.x - 1) *counter = 0u;
+      break;
+    }
+    constexpr int kCut = 8 / TPW;
+    const int b = items[item / kCut].sub;
     const DevDesc d = desc[b];
-    const int pi = d.p - 2;
-    // live quads of this wave's two planes (some source block present)
+    const v4i* Bt = d.p == 2 ? Bt2 : Bt3;
+    const HExp* he = d.p == 2 ? he2 : he3;
+    const int half = item % kCut, pi = d.p - 2;
+    // tile t of this wave: target plane z0 + t / 4, 4x4 patch ((t & 1) * 4, ((t >> 1) & 1) * 4)
+    const int z0 = 4 * NZ * half + NZ * wave;
+    int abase[TPW];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      const int x = (t & 1) * 4 + (ci & 3), y = ((t >> 1) & 1) * 4 + (ci >> 2), z = z0 + (t >> 2);
+      abase[t] = (x + 6) + kWin * (y + 6) + kWin * kWin * (z + 6);
+    }
+    // live quads of this wave's planes (some source block present)
     uint64_t live[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int q = 64 * c + lane;
       bool on = false;
-      if (q < kQuadsS) on = ((touch[(2 * wave) * kQuadsS + q] | touch[(2 * wave + 1) * kQuadsS + q]) & d.mask) != 0;
+      if (q < kQuadsS) on = ((touch[z0 * kQuadsS + q] | touch[(z0 + NZ - 1) * kQuadsS + q]) & d.mask) != 0;
       live[c] = __ballot(on);
     }
-    double fa[8][4];
+    double fa[TPW][4];
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) fa[t][v] = 0.0;
     const int8_t* pl = planes + (size_t)b * S * kSlicePlane;
-    const v4i* Bt = pi == 0 ? Bt2 : Bt3;
+    // the window planes that the item's targets reach
+    const int c0 = 4 * NZ * half * kWin * kWin, c1 = c0 + (4 * NZ + 12) * kWin * kWin;
     // sub-grids with every neighbour block present run the quad loop without skip tests
-    if (d.mask == kFullMask) slice_rounds<true, S, 0>(pl, win, Bt, s_off, live, abase, lane, fa);
-    else slice_rounds<false, S, 0>(pl, win, Bt, s_off, live, abase, lane, fa);
+    if (d.mask == kFullMask) slice_rounds<true, TPW, S, 0>(pl, win, Bt, s_off, live, abase, lane, fa, c0, c1);
+    else slice_rounds<false, TPW, S, 0>(pl, win, Bt, s_off, live, abase, lane, fa, c0, c1);
     // epilogue: L~ columns (scaled back) to LDS [n'][target], then each thread
-    // expands two targets to all C components
+    // expands its targets to all C components
     __syncthreads();   // every wave is done with the window
     double* lh = reinterpret_cast<double*>(win);
     const int n = lane & 15, g = lane >> 4;
     const double sc_n = ldexp(1.0, expo[b] + sc.eB[pi][n]);
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int x = (t & 1) * 4 + v, y = ((t >> 1) & 1) * 4 + g, z = 2 * wave + (t >> 2);
+        const int x = (t & 1) * 4 + v, y = ((t >> 1) & 1) * 4 + g, z = z0 + (t >> 2);
         lh[n * kNTarget + x + kBlock * y + kBlock * kBlock * z] = fa[t][v] * sc_n;
       }
     __syncthreads();
-    const HExp* he = pi == 0 ? he2 : he3;
     const int C = ncomp(d.p);
     const int l2 = d.log2_inv_h;
     double* out = L + d.l_off;
     for (int k = 0; k < C; ++k) {
       const HExp e = he[k];
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const int tc = tid + r * kSliceThreads;
+      for (int tc = tid + NTG * half; tc < NTG * (half + 1); tc += kSliceThreads) {
         double v = 0.0;
         for (int u = 0; u < e.nterm; ++u) v = __builtin_fma(e.coef[u], lh[e.col[u] * kNTarget + tc], v);
         out[(size_t)k * kNTarget + tc] = ldexp(v, l2 * (1 + order_of(k)));
       }
     }
+    if (!counter) break;
     __syncthreads();   // s_item and the LDS are free for the next item
   }
 }
@@ -450,14 +461,27 @@ hipError_t launch_m2l_slice(const MfmaTables& mt, const SliceTables& st, const W
     }
   hipLaunchKernelGGL(slice_window_kernel, dim3((unsigned)nsub), dim3(kPrepThreads), 0, s, d_desc, M,
                      mt.hround[2], mt.hround[3], sc, S, planes, expo);
-  hipLaunchKernelGGL(reset_slice_counter, dim3(1), dim3(1), 0, s, w.counter);
-  const int grid = std::min(mt.num_cu, w.count);
+  // Whole sub-grids take the CUs in turns; if the last turn would use at most half of
+  // them, its sub-grids run in halves, in a launch of their own. S = 7, p = 3, whole
+  // against this: 1 sub-grid 884 and 585 us, 128 1161 and 871, 384 uneven 1987 and
+  // 1753; 640 of p = 2 2779 and 2471. Halves throughout would load the tables twice
+  // as often as the products of four tiles a wave can hide.
+  const int rest = w.count % mt.num_cu, halved = 2 * rest <= mt.num_cu ? rest : 0, whole = w.count - halved;
+  const int grid = std::min(mt.num_cu, whole);
+  unsigned* counter = whole > grid ? w.counter : nullptr;
   const v4i* b2 = reinterpret_cast<const v4i*>(st.B[2]);
   const v4i* b3 = reinterpret_cast<const v4i*>(st.B[3]);
 #define SLICE_LAUNCH(SV)                                                                              \
-  hipLaunchKernelGGL((m2l_fwd_slice_kernel<SV>), dim3(grid), dim3(kSliceThreads), 0, s, w.items,      \
-                     w.count, w.counter, d_desc, L, planes, expo, b2, b3, mt.lds_off, mt.touch, sc,    \
-                     mt.hexp[2], mt.hexp[3])
+  {                                                                                                   \
+    if (whole > 0)                                                                                    \
+      hipLaunchKernelGGL((m2l_fwd_slice_kernel<SV, 8>), dim3(grid), dim3(kSliceThreads), 0, s,        \
+                         w.items, whole, counter, d_desc, L, planes, expo, b2, b3, mt.lds_off,        \
+                         mt.touch, sc, mt.hexp[2], mt.hexp[3]);                                       \
+    if (halved > 0)                                                                                   \
+      hipLaunchKernelGGL((m2l_fwd_slice_kernel<SV, 4>), dim3(2 * halved), dim3(kSliceThreads), 0, s,  \
+                         w.items + whole, 2 * halved, (unsigned*)nullptr, d_desc, L, planes, expo,    \
+                         b2, b3, mt.lds_off, mt.touch, sc, mt.hexp[2], mt.hexp[3]);                   \
+  }
   switch (S) {
     case 6: SLICE_LAUNCH(6); break;
     case 7: SLICE_LAUNCH(7); break;

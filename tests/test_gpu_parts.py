@@ -149,6 +149,33 @@ def test_p2m_of_few_cell_blocks_matches_many(torch, p, window):
             assert torch.equal(got, want[:got.numel()])
 
 
+@pytest.mark.parametrize("slices", [6, 7, 8])
+def test_exact_slice_halves_match_whole_subgrids(torch, slices):
+    # as many sub-grids as compute units run whole, a few in halves, one more than the
+    # compute units both ways: the same bits (exact integer sums)
+    ensure_library()
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    n = ncu + 1
+    rng = np.random.default_rng(31)
+    desc, m_el, l_el = fmm.make_descriptors(np.arange(n) % 2 + 2, np.arange(n) % 3,
+                                            [fmm.FULL_MASK if b % 3 else synth.random_mask(rng) for b in range(n)])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(slices)
+    M = torch.randn(m_el, dtype=torch.float64, device="cuda", generator=g)
+    L = {}
+    with fmm.Context(0) as ctx:
+        ctx.set_option(fmm.FMM_OPT_SLICES, slices)
+        for count in (n, ncu, 5):
+            L[count] = torch.full((l_el,), float("nan"), dtype=torch.float64, device="cuda")
+            for rep in range(2):
+                ctx.m2l(desc[:count], M, L[count], fmm.FMM_EXACT_SLICE)
+        torch.cuda.synchronize()
+    assert bool(torch.isfinite(L[n]).all())
+    for count in (ncu, 5):
+        end = int(desc["l_off"][count])
+        assert torch.equal(L[count][:end], L[n][:end]), count
+
+
 @pytest.mark.parametrize("ppc", [1, 3, 8, 11])
 def test_evaluation_by_half_planes_matches_whole_planes(torch, ppc):
     # up to 63 sub-grids run by half planes with one target per thread, more by
