@@ -610,7 +610,7 @@ def main():
     achieved = fl_exec / (fused_ms * 1e-3) / 1e12
     traffic = read_traffic(pairs)
     out["roofline"] = {"bound": "mfma",
-                       "kernel": "m2l_fwd_bl_kernel<PIPE, HARM, FUSE> (v_mfma_f64_4x4x4, harmonic form, "
+                       "kernel": "m2l_fwd_whole_kernel<HARM, FUSE> (v_mfma_f64_16x16x4, harmonic form, "
                                  "configuration %d, with the P2M moment phase inside)" % tuned,
                        "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                        "frac": achieved / FP64_PEAK_TFLOPS, "traffic": traffic,
@@ -733,7 +733,7 @@ def main():
             if ev: ev[1].record()
 
         _, seg1 = timed(torch, step_one, K, W, marks=1)
-        # the same with the rounds of the sub-grid spread over workgroups
+        # the same with parts of the sub-grid asked for
         ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, 1)
         try:
             _, seg1s = timed(torch, step_one, K, W, marks=1)
@@ -744,12 +744,12 @@ def main():
                                  "step_ms_min": float(seg1[:, 0].min()),
                                  "round_split_step_ms_median": float(np.median(seg1s[:, 0])),
                                  "round_split_step_ms_min": float(seg1s[:, 0].min())}
-        log("single sub-grid step %.3f ms (median), %.3f ms with the rounds split over workgroups"
+        log("single sub-grid step %.3f ms (median), %.3f ms in parts of its targets"
             % (np.median(seg1[:, 0]), np.median(seg1s[:, 0])))
         del pos1, mass1, M1, L1
 
         # ---------------- a small uneven batch (128 sub-grids drawn like the uneven
-        # workload): M2L with one workgroup per sub-grid and with the rounds split
+        # workload): M2L with one workgroup per sub-grid and in parts
         w128 = synth.config(3, nsub=128)
         d128, m128, l128 = fmm.make_descriptors(w128.p, w128.log2_inv_h, w128.mask)
         p128, ms128 = upload_batch(torch, w128)
@@ -768,7 +768,7 @@ def main():
             _, seg_ss = timed(torch, step_small, K, W, marks=1)
         finally:
             ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, -1)
-        # and as the autotuner leaves it (it times the round split too at this size)
+        # and as the autotuner leaves it (parts, as planned at this size)
         Lt128 = torch.empty_like(L128)
         tuned128 = ctx.autotune(d128, M128, Lt128, fmm.FMM_FP64_HARMONIC)
         del Lt128
@@ -779,7 +779,7 @@ def main():
                                      "round_split_m2l_ms": float(np.median(seg_ss[:, 0])),
                                      "autotuned_m2l_ms": float(np.median(seg_st[:, 0])),
                                      "autotune_choice": tuned128}
-        log("uneven 128: M2L %.3f ms, %.3f ms with the rounds split over workgroups, %.3f ms autotuned"
+        log("uneven 128: M2L %.3f ms, %.3f ms in parts of its targets, %.3f ms autotuned"
             % (np.median(seg_sw[:, 0]), np.median(seg_ss[:, 0]), np.median(seg_st[:, 0])))
         del p128, ms128, M128, L128
 
