@@ -297,7 +297,7 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
         std::memcmp(e->host.data(), desc, nbytes) == 0) {
       e->last_use = ++ctx->clock;
       // order after the previous call on this set, whatever its stream: calls
-      // share the set's work-list counters and round-split partials (the event
+      // share the set's work-list counters (the event
       // was first recorded after the upload, so this also covers the upload)
       HIP_TRY(ctx, hipStreamWaitEvent(stream, e->last_launch, 0));
       *out = e.get();
