@@ -190,14 +190,13 @@ fmm_status fmm_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
  * has not tuned: FMM_OPT_TILE_CONFIG, else the precision's default), with the
  * descriptor copy, the work list and the work counter in a statically
  * allocated device array instead of memory the context allocates per
- * descriptor set. The array holds FMM_NOALLOC_MAX_SUBGRIDS sub-grids (about
- * 0.8 MB) and exists once per device until the process ends. The call
+ * descriptor set. The array holds FMM_NOALLOC_MAX_SUBGRIDS sub-grids (1.25 MB)
+ * and exists once per device until the process ends. The call
  * allocates nothing: it waits on the host for the previous fmm_m2l_noalloc
  * call of this context to have copied its descriptors out of a pinned host
- * buffer that fmm_create allocated, writes this call's descriptors and
- * longest-first work list there, copies them to the array on `stream`, resets
- * the counter with a kernel and launches the persistent matrix-core kernel
- * (no graph). FMM_FP64, FMM_SPLIT_FP32 and FMM_FP64_HARMONIC; FMM_EXACT_SLICE
+ * buffer that fmm_create allocated, writes this call's descriptors, a cleared
+ * work counter and the work list there, copies them to the array on `stream`
+ * and launches the matrix-core kernel (no graph). FMM_FP64, FMM_SPLIT_FP32 and FMM_FP64_HARMONIC; FMM_EXACT_SLICE
  * and FMM_OPT_M2L_KERNEL = 1 return FMM_EUNSUPPORTED, nsub above
  * FMM_NOALLOC_MAX_SUBGRIDS returns FMM_EINVAL. Every call on one device shares
  * that device's array, whatever its context: calls that can overlap on one

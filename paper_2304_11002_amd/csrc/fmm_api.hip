@@ -14,16 +14,16 @@
 
 using namespace fmm;
 
-// Device memory of fmm_m2l_noalloc: descriptors, work list and work counter of
+// Device memory of fmm_m2l_noalloc: descriptors, work counter and work list of
 // one call, at most FMM_NOALLOC_MAX_SUBGRIDS sub-grids. One copy per device,
 // held until the process ends; every call on a device shares it. Host code
 // never passes this name to a kernel or a copy: fmm_create looks up each
 // device's address of it (fmm_ctx::noalloc_dev) and that address is used.
 constexpr size_t kNoAllocDescBytes = sizeof(fmm_subgrid) * FMM_NOALLOC_MAX_SUBGRIDS;
-constexpr size_t kNoAllocWorkOff = (kNoAllocDescBytes + 255) / 256 * 256;
+constexpr size_t kNoAllocCounterOff = (kNoAllocDescBytes + 255) / 256 * 256;   // inside every call's upload
+constexpr size_t kNoAllocWorkOff = kNoAllocCounterOff + 256;
 constexpr size_t kNoAllocItems = (size_t)max_parts(FMM_NOALLOC_MAX_SUBGRIDS);   // parts of the sub-grids
-constexpr size_t kNoAllocCounterOff = (kNoAllocWorkOff + sizeof(WorkItem) * kNoAllocItems + 255) / 256 * 256;
-constexpr size_t kNoAllocBytes = kNoAllocCounterOff + 256;
+constexpr size_t kNoAllocBytes = kNoAllocWorkOff + sizeof(WorkItem) * kNoAllocItems;
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 namespace {
@@ -152,7 +152,7 @@ struct fmm_ctx {
   int round_split = -1;     // FMM_OPT_ROUND_SPLIT: -1 as planned, 0 whole sub-grids, 1 parts (small batches)
   int slices = 7;           // FMM_OPT_SLICES
   // fmm_m2l_noalloc: this device's address of the static array, a pinned host
-  // copy of its descriptor and work-list part, and the event after its upload
+  // copy of it, and the event after its upload
   unsigned char* noalloc_dev = nullptr;
   unsigned char* noalloc_host = nullptr;
   hipEvent_t noalloc_uploaded = nullptr;
@@ -498,7 +498,7 @@ fmm_status fmm_create(fmm_ctx** out, int32_t device) {
   CREATE_TRY(tree_tables_create(&c->tree, c->d_T, st.data(), (int)(st.size() / 3), c->internal));
   // fmm_m2l_noalloc: the device's address of the static array (the device is current)
   CREATE_TRY(hipGetSymbolAddress(reinterpret_cast<void**>(&c->noalloc_dev), HIP_SYMBOL(scratch)));
-  CREATE_TRY(hipHostMalloc(reinterpret_cast<void**>(&c->noalloc_host), kNoAllocCounterOff, hipHostMallocDefault));
+  CREATE_TRY(hipHostMalloc(reinterpret_cast<void**>(&c->noalloc_host), kNoAllocBytes, hipHostMallocDefault));
   CREATE_TRY(hipEventCreateWithFlags(&c->noalloc_uploaded, hipEventDisableTiming));
   sort_by_cost(nullptr, 0, false, nullptr);   // the work-list builder's tables, set up once
   CREATE_TRY(hipStreamSynchronize(c->internal));
@@ -930,6 +930,9 @@ fmm_status fmm_m2l_noalloc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, 
   HIP_TRY(ctx, hipEventSynchronize(ctx->noalloc_uploaded));
   unsigned char* hp = ctx->noalloc_host;
   std::memcpy(hp, desc, sizeof(fmm_subgrid) * (size_t)nsub);
+  // the upload clears the counter, whatever earlier calls left in it (every
+  // context's calls on the device share it, and overlapping ones may leave any value)
+  std::memset(hp + kNoAllocCounterOff, 0, kNoAllocWorkOff - kNoAllocCounterOff);
   WorkItem* items = reinterpret_cast<WorkItem*>(hp + kNoAllocWorkOff);
   const bool harm = prec == FMM_FP64_HARMONIC;
   const int cfg = pick_config(ctx, nullptr, prec);
@@ -945,12 +948,10 @@ fmm_status fmm_m2l_noalloc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, 
   HIP_TRY(ctx, hipEventRecord(ctx->noalloc_uploaded, s));
   wl.items = reinterpret_cast<const WorkItem*>(ctx->noalloc_dev + kNoAllocWorkOff);
   wl.count = (int)count;
-  // (the first counter is zero between launches, the other is reset by the launch)
-  const bool split = prec == FMM_SPLIT_FP32;
-  wl.counter = reinterpret_cast<unsigned*>(ctx->noalloc_dev + kNoAllocCounterOff) + (streams || split ? 0 : 1);
+  wl.counter = reinterpret_cast<unsigned*>(ctx->noalloc_dev + kNoAllocCounterOff);
   const DevDesc* d_desc = reinterpret_cast<const DevDesc*>(ctx->noalloc_dev);
   if (streams) HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, wl, d_desc, M, L, harm, s));
-  else if (split) HIP_TRY(ctx, launch_m2l_split(ctx->mfma, wl, d_desc, M, L, s));
+  else if (prec == FMM_SPLIT_FP32) HIP_TRY(ctx, launch_m2l_split(ctx->mfma, wl, d_desc, M, L, s));
   else HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, d_desc, M, L, prec, cfg, s));
   return FMM_OK;
 }
