@@ -11,6 +11,7 @@
 
 #include "kernels.h"
 #include "m2l_mfma.h"
+#include "stencil_pairs.h"
 
 using namespace fmm;
 
@@ -33,52 +34,6 @@ thread_local std::string g_create_error;
 const char* kStatusStrings[] = {"FMM_OK", "FMM_EINVAL: invalid argument",
                                 "FMM_ENOMEM: out of memory", "FMM_EHIP: HIP runtime error",
                                 "FMM_EUNSUPPORTED: unsupported request"};
-
-// Shell stencil 5 <= |d|^2 <= 36, dz slowest, then dy, then dx.
-std::vector<int> make_stencil() {
-  std::vector<int> s;
-  for (int dz = -kRad; dz <= kRad; ++dz)
-    for (int dy = -kRad; dy <= kRad; ++dy)
-      for (int dx = -kRad; dx <= kRad; ++dx) {
-        int q = dx * dx + dy * dy + dz * dz;
-        if (q >= 5 && q <= 36) {
-          s.push_back(dx);
-          s.push_back(dy);
-          s.push_back(dz);
-        }
-      }
-  return s;
-}
-
-const std::vector<int>& stencil_host() {
-  static const std::vector<int> s = make_stencil();
-  return s;
-}
-
-// pairs (target cell, offset) whose source lies in each of the 27 blocks
-const std::vector<int64_t>& block_pairs() {
-  static const std::vector<int64_t> bp = [] {
-    std::vector<int64_t> v(27, 0);
-    const auto& s = stencil_host();
-    for (int t = 0; t < kNTarget; ++t) {
-      int jx = t % 8 + 8, jy = (t / 8) % 8 + 8, jz = t / 64 + 8;
-      for (size_t i = 0; i < s.size(); i += 3) {
-        int sx = jx + s[i], sy = jy + s[i + 1], sz = jz + s[i + 2];
-        v[(sx / 8) + 3 * (sy / 8) + 9 * (sz / 8)]++;
-      }
-    }
-    return v;
-  }();
-  return bp;
-}
-
-int64_t pairs_of_mask(uint32_t mask) {
-  const auto& bp = block_pairs();
-  int64_t n = 0;
-  for (int b = 0; b < 27; ++b)
-    if ((mask >> b) & 1u) n += bp[b];
-  return n;
-}
 
 uint64_t fnv1a(const void* data, size_t n, uint64_t h = 1469598103934665603ull) {
   const unsigned char* p = static_cast<const unsigned char*>(data);
@@ -500,7 +455,7 @@ fmm_status fmm_create(fmm_ctx** out, int32_t device) {
   CREATE_TRY(hipGetSymbolAddress(reinterpret_cast<void**>(&c->noalloc_dev), HIP_SYMBOL(scratch)));
   CREATE_TRY(hipHostMalloc(reinterpret_cast<void**>(&c->noalloc_host), kNoAllocBytes, hipHostMallocDefault));
   CREATE_TRY(hipEventCreateWithFlags(&c->noalloc_uploaded, hipEventDisableTiming));
-  sort_by_cost(nullptr, 0, false, nullptr);   // the work-list builder's tables, set up once
+  (void)pairs_of_mask(0);   // the work-list builder's table is made here, not in a compute call
   CREATE_TRY(hipStreamSynchronize(c->internal));
 #undef CREATE_TRY
   *out = ctx.release();

@@ -29,6 +29,7 @@
 #include "kernels.h"
 #include "m2l_mfma.h"
 #include "p2m_common.h"
+#include "stencil_pairs.h"
 
 namespace fmm {
 
@@ -1661,38 +1662,6 @@ void build_pairs(const std::vector<int>& st, std::vector<int4>* pairs, std::vect
   gstart->push_back((int)pairs->size());
 }
 
-int64_t block_pair_count(uint32_t mask, const std::vector<int>& st) {
-  static int64_t per_block[27] = {-1};
-  if (per_block[0] < 0) {
-    int64_t v[27] = {};
-    for (int t = 0; t < kNTarget; ++t) {
-      const int jx = t % 8 + 8, jy = (t / 8) % 8 + 8, jz = t / 64 + 8;
-      for (size_t i = 0; i < st.size(); i += 3)
-        v[(jx + st[i]) / 8 + 3 * ((jy + st[i + 1]) / 8) + 9 * ((jz + st[i + 2]) / 8)]++;
-    }
-    for (int b = 0; b < 27; ++b) per_block[b] = v[b];
-  }
-  int64_t n = 0;
-  for (int b = 0; b < 27; ++b)
-    if ((mask >> b) & 1u) n += per_block[b];
-  return n;
-}
-
-std::vector<int> host_stencil() {
-  std::vector<int> s;
-  for (int dz = -kRad; dz <= kRad; ++dz)
-    for (int dy = -kRad; dy <= kRad; ++dy)
-      for (int dx = -kRad; dx <= kRad; ++dx) {
-        const int q = dx * dx + dy * dy + dz * dz;
-        if (q >= 5 && q <= 36) {
-          s.push_back(dx);
-          s.push_back(dy);
-          s.push_back(dz);
-        }
-      }
-  return s;
-}
-
 // Forward configurations.
 struct Config {
   fmm_precision prec;
@@ -1712,12 +1681,11 @@ constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 }  // namespace
 
 void sort_by_cost(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkItem* out) {
-  static const std::vector<int> st = host_stencil();
   for (int64_t b = 0; b < nsub; ++b) {
     const int p = desc[b].p;
     const int64_t per_pair = harmonic ? (int64_t)(p + 1) * (p + 1) * (p + 1) * (p + 1)
                                       : (int64_t)ncomp(p) * ncomp(p);
-    const int64_t pairs = block_pair_count(desc[b].mask, st);
+    const int64_t pairs = pairs_of_mask(desc[b].mask);
     out[b].sub = (int32_t)b;
     out[b].part = (int32_t)(per_pair * pairs / 4096);   // below 2^18
   }
@@ -2083,7 +2051,7 @@ hipError_t mfma_tables_create(MfmaTables* t, double* const* d_T, const int* d_st
   int dev = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&t->num_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-  const std::vector<int> st = host_stencil();
+  const std::vector<int>& st = stencil_host();
   // forward: LDS offsets of the offsets, blocks each quad touches per target plane
   std::vector<int> off(kNStencil);
   for (int i = 0; i < kNStencil; ++i) off[i] = st[3 * i] + kWin * st[3 * i + 1] + kWin * kWin * st[3 * i + 2];
