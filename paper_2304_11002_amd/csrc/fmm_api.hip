@@ -46,27 +46,36 @@ uint64_t fnv1a(const void* data, size_t n, uint64_t h = 1469598103934665603ull) 
 
 }  // namespace
 
+// Work lists of one form's forward or adjoint calls on a descriptor set, made by
+// the first of them (P2M and evaluation need none): in the set's own allocation if
+// that call is the set's first, else in one of theirs.
+struct CallLists {
+  bool made = false;
+  void* dev = nullptr;            // (own device allocation and pinned host copy, if any)
+  void* pinned = nullptr;
+  WorkList whole;                 // sub-grids, longest first; a counter that the launches leave at zero, and
+                                  // after it one that the per-wave launches reset
+  WorkList cut;                   // their parts (forward) or rounds (adjoint), where planned or asked for
+};
+// the lists a call needs (a bit each)
+constexpr unsigned need_forward(bool harmonic) { return 1u << harmonic; }
+constexpr unsigned need_adjoint(bool harmonic) { return 4u << harmonic; }
+
 // Descriptor set uploaded to the device, plus everything derived from it.
 struct DescEntry {
   std::vector<fmm_subgrid> host;
   uint64_t hash = 0;
   uint64_t id = 0;                // unique per upload (keys this set's graphs)
   uint64_t last_use = 0;
-  void* dev = nullptr;            // one device allocation: descriptors, id lists, work list
+  void* dev = nullptr;            // one device allocation: descriptors, id lists, the first call's work lists
   void* pinned = nullptr;         // pinned host copy of the same bytes
   size_t bytes = 0;
   DevDesc* d_desc = nullptr;
   int* d_ids[kMaxP + 1] = {};     // reference kernels: sub-grids per order
   int count[kMaxP + 1] = {};
-  WorkList work;                  // per-wave kernels: whole[0]'s items, a counter that its launches reset
-  // per form (dense, harmonic): whole sub-grids, longest first, and their parts
-  // (streamed forward, where planned or small enough to be asked for), with a
-  // counter that the launches leave at zero
-  WorkList whole[2];
-  WorkList parts[2];
-  StreamPlan plan[2];
-  WorkList rounds[2];             // adjoint: the sub-grids' rounds, where planned
-  AdjointPlan adjoint[2];
+  CallLists forward[2], adjoint[2];   // per form (dense, harmonic)
+  StreamPlan plan[2];             // made with the lists
+  AdjointPlan adjoint_plan[2];
   bool part_even = true;          // every part_off even: particle blocks 16-byte aligned
   int tuned[4] = {-1, -1, -1, -1};   // autotuned configuration per precision
   // FMM_EXACT_SLICE: the sub-grids' slice planes and exponents (one allocation)
@@ -223,6 +232,11 @@ void free_entry(DescEntry* e) {
   if (e->ready) (void)hipEventSynchronize(e->ready);
   if (e->dev) (void)hipFree(e->dev);
   if (e->pinned) (void)hipHostFree(e->pinned);
+  for (int f = 0; f < 2; ++f)
+    for (CallLists* l : {&e->forward[f], &e->adjoint[f]}) {
+      if (l->dev) (void)hipFree(l->dev);
+      if (l->pinned) (void)hipHostFree(l->pinned);
+    }
   if (e->slice_dev) (void)hipFree(e->slice_dev);
   if (e->ready) (void)hipEventDestroy(e->ready);
   if (e->last_launch) (void)hipEventDestroy(e->last_launch);
@@ -242,9 +256,68 @@ constexpr size_t kMaxGraphs = 16;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Find or upload the descriptor set; builds the id lists and the work list.
+struct ListItems {
+  std::vector<WorkItem> whole, cut;
+  size_t off_cut() const { return align_up(sizeof(WorkItem) * whole.size(), 256); }
+  size_t off_counter() const { return align_up(off_cut() + sizeof(WorkItem) * cut.size(), 256); }
+  size_t bytes() const { return off_counter() + 256; }
+};
+
+// The items of the lists of one need, longest sub-grid first, and the plan they follow.
+ListItems build_lists(const fmm_ctx* ctx, DescEntry* e, unsigned need) {
+  const bool harmonic = (need & (need_forward(true) | need_adjoint(true))) != 0;
+  const int64_t nsub = (int64_t)e->host.size();
+  const int num_cu = ctx->mfma.num_cu;
+  ListItems li;
+  li.whole.resize((size_t)nsub);
+  sort_by_cost(e->host.data(), nsub, harmonic, li.whole.data());
+  if (need & (need_forward(false) | need_forward(true))) {
+    const StreamPlan plan = plan_stream(li.whole.data(), nsub, num_cu);
+    e->plan[harmonic] = plan;
+    if (plan.parts || nsub <= kMaxSplitSubgrids) {
+      li.cut = li.whole;
+      li.cut.resize((size_t)max_parts(nsub));
+      li.cut.resize((size_t)split_items(li.cut.data(), nsub, num_cu));
+    }
+  } else {
+    const AdjointPlan plan = plan_adjoint(li.whole.data(), nsub, num_cu, harmonic);
+    e->adjoint_plan[harmonic] = plan;
+    if (plan.rounds)
+      for (const WorkItem& it : li.whole) {
+        uint32_t sets[kMaxRounds];
+        const int n = adjoint_round_sets(e->host[(size_t)it.sub].p, harmonic, sets);
+        for (int k = 0; k < n; ++k) li.cut.push_back(WorkItem{it.sub, (int32_t)sets[k]});
+      }
+  }
+  whole_items(li.whole.data(), nsub);
+  return li;
+}
+
+CallLists* lists_of(DescEntry* e, unsigned need) {
+  return need == need_forward(false)  ? &e->forward[0]
+         : need == need_forward(true) ? &e->forward[1]
+                                      : &e->adjoint[need == need_adjoint(true)];
+}
+
+// Writes the lists at hp (host) for their copy to dp (device).
+void place_lists(const ListItems& li, CallLists* l, char* hp, char* dp) {
+  std::memcpy(hp, li.whole.data(), sizeof(WorkItem) * li.whole.size());
+  std::memcpy(hp + li.off_cut(), li.cut.data(), sizeof(WorkItem) * li.cut.size());
+  std::memset(hp + li.off_counter(), 0, 256);
+  l->made = true;
+  l->whole.items = reinterpret_cast<const WorkItem*>(dp);
+  l->whole.count = (int)li.whole.size();
+  l->whole.counter = reinterpret_cast<unsigned*>(dp + li.off_counter());
+  l->cut = l->whole;
+  l->cut.items = reinterpret_cast<const WorkItem*>(dp + li.off_cut());
+  l->cut.count = (int)li.cut.size();
+  l->cut.parts = true;
+}
+
+// Find or upload the descriptor set; builds the id lists, and for a new set the
+// work lists of the call's need (0: none).
 fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStream_t stream,
-                    DescEntry** out) {
+                    unsigned need, DescEntry** out) {
   const size_t nbytes = sizeof(fmm_subgrid) * (size_t)nsub;
   const uint64_t h = fnv1a(desc, nbytes, fnv1a(&nsub, sizeof nsub));
   for (auto& e : ctx->descs) {
@@ -281,31 +354,11 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
   e->hash = h;
   e->id = ++ctx->next_id;
   e->last_use = ++ctx->clock;
-  // layout: descriptors | ids per order | work list
+  // layout: descriptors | ids per order | work lists
   std::vector<int> ids[kMaxP + 1];
   for (int64_t b = 0; b < nsub; ++b) {
     ids[desc[b].p].push_back((int)b);
     if (desc[b].part_off & 1) e->part_even = false;
-  }
-  std::vector<WorkItem> items[2], parts[2], rounds[2];   // dense, harmonic
-  StreamPlan plan[2];
-  for (int f = 0; f < 2; ++f) {
-    items[f].resize((size_t)nsub);
-    sort_by_cost(desc, nsub, f == 1, items[f].data());
-    plan[f] = plan_stream(items[f].data(), nsub, ctx->mfma.num_cu);
-    if (plan[f].parts || nsub <= kMaxSplitSubgrids) {
-      parts[f] = items[f];
-      parts[f].resize((size_t)max_parts(nsub));
-      parts[f].resize((size_t)split_items(parts[f].data(), nsub, ctx->mfma.num_cu));
-    }
-    e->adjoint[f] = plan_adjoint(items[f].data(), nsub, ctx->mfma.num_cu, f == 1);
-    if (e->adjoint[f].rounds)
-      for (const WorkItem& it : items[f]) {
-        uint32_t sets[kMaxRounds];
-        const int n = adjoint_round_sets(desc[it.sub].p, f == 1, sets);
-        for (int k = 0; k < n; ++k) rounds[f].push_back(WorkItem{it.sub, (int32_t)sets[k]});
-      }
-    whole_items(items[f].data(), nsub);
   }
   size_t off_desc = 0;
   size_t off = align_up(nbytes, 256);
@@ -314,53 +367,22 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     off_ids[p] = off;
     off = align_up(off + sizeof(int) * ids[p].size(), 256);
   }
-  size_t off_work[2], off_parts[2], off_rounds[2], off_zero[2];
-  for (int f = 0; f < 2; ++f) {
-    off_work[f] = off;
-    off = align_up(off + sizeof(WorkItem) * items[f].size(), 256);
-    off_parts[f] = off;
-    off = align_up(off + sizeof(WorkItem) * parts[f].size(), 256);
-    off_rounds[f] = off;
-    off = align_up(off + sizeof(WorkItem) * rounds[f].size(), 256);
-    off_zero[f] = off;
-    off = align_up(off + 256, 256);
-  }
-  const size_t off_counter = off;
-  off = align_up(off + 256, 256);
-  e->bytes = off;
+  ListItems lists;
+  if (need) lists = build_lists(ctx, e.get(), need);
+  const size_t off_lists = off;
+  e->bytes = off + (need ? lists.bytes() : 0);
   HIP_TRY(ctx, hipMalloc(&e->dev, e->bytes));
   HIP_TRY(ctx, hipHostMalloc(&e->pinned, e->bytes, hipHostMallocDefault));
   char* hp = static_cast<char*>(e->pinned);
-  std::memset(hp, 0, e->bytes);
   std::memcpy(hp + off_desc, desc, nbytes);
   for (int p = 2; p <= kMaxP; ++p) std::memcpy(hp + off_ids[p], ids[p].data(), sizeof(int) * ids[p].size());
-  for (int f = 0; f < 2; ++f) {
-    std::memcpy(hp + off_work[f], items[f].data(), sizeof(WorkItem) * items[f].size());
-    std::memcpy(hp + off_parts[f], parts[f].data(), sizeof(WorkItem) * parts[f].size());
-    std::memcpy(hp + off_rounds[f], rounds[f].data(), sizeof(WorkItem) * rounds[f].size());
-  }
   char* dp = static_cast<char*>(e->dev);
   e->d_desc = reinterpret_cast<DevDesc*>(dp + off_desc);
   for (int p = 2; p <= kMaxP; ++p) {
     e->d_ids[p] = reinterpret_cast<int*>(dp + off_ids[p]);
     e->count[p] = (int)ids[p].size();
   }
-  for (int f = 0; f < 2; ++f) {
-    e->whole[f].items = reinterpret_cast<const WorkItem*>(dp + off_work[f]);
-    e->whole[f].count = (int)items[f].size();
-    e->whole[f].counter = reinterpret_cast<unsigned*>(dp + off_zero[f]);
-    e->parts[f].items = reinterpret_cast<const WorkItem*>(dp + off_parts[f]);
-    e->parts[f].count = (int)parts[f].size();
-    e->parts[f].counter = e->whole[f].counter;
-    e->parts[f].parts = true;
-    e->plan[f] = plan[f];
-    e->rounds[f].items = reinterpret_cast<const WorkItem*>(dp + off_rounds[f]);
-    e->rounds[f].count = (int)rounds[f].size();
-    e->rounds[f].counter = e->whole[f].counter;
-    e->rounds[f].parts = true;
-  }
-  e->work = e->whole[0];
-  e->work.counter = reinterpret_cast<unsigned*>(dp + off_counter);
+  if (need) place_lists(lists, lists_of(e.get(), need), hp + off_lists, dp + off_lists);
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->ready, hipEventDisableTiming));
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->last_launch, hipEventDisableTiming));
   HIP_TRY(ctx, hipMemcpyAsync(e->dev, e->pinned, e->bytes, hipMemcpyHostToDevice, stream));
@@ -368,6 +390,36 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
   HIP_TRY(ctx, hipEventRecord(e->last_launch, stream));
   *out = e.get();
   ctx->descs.push_back(std::move(e));
+  return FMM_OK;
+}
+
+// Makes the lists of a need that the set's first call did not have, copied on the
+// caller's stream. A caller whose stream is being captured gets them at once (the
+// captured work runs later, and other calls may use them before).
+fmm_status ensure_lists(fmm_ctx* ctx, DescEntry* e, unsigned need, hipStream_t stream) {
+  CallLists* l = lists_of(e, need);
+  if (l->made) return FMM_OK;
+  const ListItems li = build_lists(ctx, e, need);
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (stream) HIP_TRY(ctx, hipStreamIsCapturing(stream, &status));
+  const bool capturing = status == hipStreamCaptureStatusActive;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // lets this thread allocate and wait while it captures
+  if (capturing) HIP_TRY(ctx, hipThreadExchangeStreamCaptureMode(&mode));
+  hipError_t err = hipMalloc(&l->dev, li.bytes());
+  if (err == hipSuccess) err = hipHostMalloc(&l->pinned, li.bytes(), hipHostMallocDefault);
+  if (err == hipSuccess) {
+    place_lists(li, l, static_cast<char*>(l->pinned), static_cast<char*>(l->dev));
+    err = hipMemcpyAsync(l->dev, l->pinned, li.bytes(), hipMemcpyHostToDevice, capturing ? ctx->internal : stream);
+  }
+  if (err == hipSuccess)
+    err = capturing ? hipStreamSynchronize(ctx->internal) : hipEventRecord(e->last_launch, stream);
+  if (capturing) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (err != hipSuccess) {
+    if (l->dev) (void)hipFree(l->dev);
+    if (l->pinned) (void)hipHostFree(l->pinned);
+    *l = CallLists{};
+    return hip_err(ctx, err, "work lists");
+  }
   return FMM_OK;
 }
 
@@ -534,7 +586,7 @@ fmm_status fmm_p2m(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, const do
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  CHECK_OK(get_desc(ctx, desc, nsub, s, 0, &e));
   HIP_TRY(ctx, launch_p2m(e->d_desc, nsub, e->d_ids, e->count, pos, mass, ppc, M, e->part_even,
                           ctx->p2m_window != 0, s));
   return mark_used(ctx, e, s);
@@ -554,7 +606,7 @@ fmm_status fmm_p2m_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  CHECK_OK(get_desc(ctx, desc, nsub, s, 0, &e));
   HIP_TRY(ctx, launch_p2m_backward(e->d_desc, nsub, e->d_ids, e->count, pos, ppc, dM, dmass, e->part_even, s));
   return mark_used(ctx, e, s);
 }
@@ -577,7 +629,7 @@ fmm_status fmm_evaluate(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  CHECK_OK(get_desc(ctx, desc, nsub, s, 0, &e));
   HIP_TRY(ctx, launch_evaluate(e->d_desc, nsub, pos, mass, ppc, L, out, s));
   return mark_used(ctx, e, s);
 }
@@ -738,7 +790,8 @@ static fmm_status run_ref(fmm_ctx* ctx, DescEntry* e, bool backward, const doubl
 // graph if enabled.
 static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* L,
                            fmm_precision prec, int cfg, hipStream_t s) {
-  const WorkList& wl = e->work;
+  WorkList wl = e->forward[0].whole;
+  wl.counter += 1;
   if (!ctx->use_graph) {
     HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, e->d_desc, M, L, prec, cfg, s));
     return FMM_OK;
@@ -785,6 +838,7 @@ static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* 
 // FMM_EXACT_SLICE: the slice planes and exponents of the set (allocated on first
 // use, and again if more slices are asked for), then the two kernels
 static fmm_status run_slice(fmm_ctx* ctx, DescEntry* e, const double* M, double* L, hipStream_t s) {
+  CHECK_OK(ensure_lists(ctx, e, need_forward(true), s));
   const int64_t nsub = (int64_t)e->host.size();
   const size_t planes = align_up((size_t)nsub * ctx->slices * kSlicePlane, 256);
   const size_t bytes = planes + sizeof(int32_t) * (size_t)nsub;
@@ -801,7 +855,7 @@ static fmm_status run_slice(fmm_ctx* ctx, DescEntry* e, const double* M, double*
   }
   int8_t* pl = static_cast<int8_t*>(e->slice_dev);
   int32_t* ex = reinterpret_cast<int32_t*>(pl + planes);
-  HIP_TRY(ctx, launch_m2l_slice(ctx->mfma, ctx->slice, e->whole[1], e->d_desc, nsub, M, L, ctx->slices, pl, ex, s));
+  HIP_TRY(ctx, launch_m2l_slice(ctx->mfma, ctx->slice, e->forward[1].whole, e->d_desc, nsub, M, L, ctx->slices, pl, ex, s));
   return FMM_OK;
 }
 
@@ -811,8 +865,10 @@ static bool takes_parts(const fmm_ctx* ctx, int64_t nsub, const StreamPlan& plan
   return plan.parts || (ctx->round_split == 1 && nsub <= kMaxSplitSubgrids);
 }
 
+// (its forward lists made)
 static const WorkList& stream_list(const fmm_ctx* ctx, const DescEntry* e, bool harmonic) {
-  return takes_parts(ctx, (int64_t)e->host.size(), e->plan[harmonic]) ? e->parts[harmonic] : e->whole[harmonic];
+  const CallLists& l = e->forward[harmonic];
+  return takes_parts(ctx, (int64_t)e->host.size(), e->plan[harmonic]) ? l.cut : l.whole;
 }
 
 // The M2L of one call: reference kernel, exact slices, the streamed forward, or
@@ -821,13 +877,14 @@ static fmm_status run_m2l(fmm_ctx* ctx, DescEntry* e, const double* M, double* L
                           int cfg, hipStream_t s) {
   if (ctx->m2l_kernel == 1) return run_ref(ctx, e, false, M, L, s);
   if (prec == FMM_EXACT_SLICE) return run_slice(ctx, e, M, L, s);
+  const bool harm = prec == FMM_FP64_HARMONIC;
+  CHECK_OK(ensure_lists(ctx, e, need_forward(harm), s));
   if (mfma_config_streams(cfg)) {
-    const bool harm = prec == FMM_FP64_HARMONIC;
     HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s));
     return FMM_OK;
   }
   if (prec == FMM_SPLIT_FP32) {
-    HIP_TRY(ctx, launch_m2l_split(ctx->mfma, e->whole[0], e->d_desc, M, L, s));
+    HIP_TRY(ctx, launch_m2l_split(ctx->mfma, e->forward[0].whole, e->d_desc, M, L, s));
     return FMM_OK;
   }
   return run_mfma(ctx, e, M, L, prec, cfg, s);
@@ -856,7 +913,8 @@ fmm_status fmm_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, const do
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
+  CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   CHECK_OK(run_m2l(ctx, e, M, L, prec, pick_config(ctx, e, prec), s));
   return mark_used(ctx, e, s);
 }
@@ -932,14 +990,19 @@ fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, cons
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
+  CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   const int cfg = pick_config(ctx, e, prec);
   const bool aligned = ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(mass)) & 15u) == 0;
   // (moments in the M2L's launch where the plan expects that to be faster)
   const bool harm = prec == FMM_FP64_HARMONIC;
-  if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && mfma_config_streams(cfg) &&
-      e->plan[harm].fuse) {
-    HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, e->whole[harm], e->d_desc, M, L, harm, s, pos, mass, M));
+  bool fuse = ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && mfma_config_streams(cfg);
+  if (fuse) {
+    CHECK_OK(ensure_lists(ctx, e, need_forward(harm), s));
+    fuse = e->plan[harm].fuse;
+  }
+  if (fuse) {
+    HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, e->forward[harm].whole, e->d_desc, M, L, harm, s, pos, mass, M));
   } else {
     HIP_TRY(ctx, launch_p2m(e->d_desc, nsub, e->d_ids, e->count, pos, mass, ppc, M, e->part_even, true, s));
     CHECK_OK(run_m2l(ctx, e, M, L, prec, cfg, s));
@@ -947,8 +1010,10 @@ fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, cons
   return mark_used(ctx, e, s);
 }
 
+// (its adjoint lists made)
 static const WorkList& adjoint_list(const DescEntry* e, bool harmonic) {
-  return e->adjoint[harmonic].rounds ? e->rounds[harmonic] : e->whole[harmonic];
+  const CallLists& l = e->adjoint[harmonic];
+  return e->adjoint_plan[harmonic].rounds ? l.cut : l.whole;
 }
 
 fmm_status fmm_m2l_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, const double* dL,
@@ -965,10 +1030,12 @@ fmm_status fmm_m2l_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_adjoint(ctx->adjoint_form == 1);
+  CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   if (ctx->m2l_kernel == 1) {
     CHECK_OK(run_ref(ctx, e, true, dL, dM, s));
   } else {
+    CHECK_OK(ensure_lists(ctx, e, need_adjoint(ctx->adjoint_form == 1), s));
     HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, adjoint_list(e, ctx->adjoint_form == 1), e->d_desc, dL, dM,
                                           ctx->adjoint_form == 1, s));
   }
@@ -992,11 +1059,13 @@ fmm_status fmm_m2l_p2m_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t n
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_adjoint(ctx->adjoint_form == 1);
+  CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   const bool aligned = ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(dmass)) & 15u) == 0;
   const bool harm = ctx->adjoint_form == 1;
-  if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && e->adjoint[harm].fuse) {
-    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, e->whole[harm], e->d_desc, dL, dM, harm, s, pos, dmass));
+  if (ctx->m2l_kernel != 1) CHECK_OK(ensure_lists(ctx, e, need_adjoint(harm), s));
+  if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && e->adjoint_plan[harm].fuse) {
+    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, e->adjoint[harm].whole, e->d_desc, dL, dM, harm, s, pos, dmass));
   } else {
     if (ctx->m2l_kernel == 1) CHECK_OK(run_ref(ctx, e, true, dL, dM, s));
     else HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, adjoint_list(e, harm), e->d_desc, dL, dM, harm, s));
@@ -1034,13 +1103,18 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, &e));
+  const unsigned need = need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
+  CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   if (prec == FMM_EXACT_SLICE) {
     // one kernel: nothing to time
     e->tuned[prec] = mfma_default_config(prec);
     if (chosen) *chosen = e->tuned[prec];
     return mark_used(ctx, e, s);
   }
+  const bool harm = prec == FMM_FP64_HARMONIC;
+  CHECK_OK(ensure_lists(ctx, e, need_forward(harm), s));
+  WorkList per_wave = e->forward[harm].whole;
+  per_wave.counter += 1;
   hipEvent_t t0, t1;
   HIP_TRY(ctx, hipEventCreate(&t0));
   HIP_TRY(ctx, hipEventCreate(&t1));
@@ -1050,10 +1124,9 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
     if (!mfma_config_supports(cfg, prec) || !mfma_config_distinct(cfg)) continue;
     // one warm-up launch, then the best of three, as fmm_m2l runs the configuration
     auto launch = [&]() {
-      const bool harm = prec == FMM_FP64_HARMONIC;
       return mfma_config_streams(cfg) ? launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s)
-             : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, e->whole[0], e->d_desc, M, L, s)
-                                      : launch_m2l_mfma(ctx->mfma, e->work, e->d_desc, M, L, prec, cfg, s);
+             : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, e->forward[0].whole, e->d_desc, M, L, s)
+                                      : launch_m2l_mfma(ctx->mfma, per_wave, e->d_desc, M, L, prec, cfg, s);
     };
     HIP_TRY(ctx, launch());
     float cfg_ms = 1e30f;

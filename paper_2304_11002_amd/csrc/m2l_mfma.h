@@ -18,7 +18,7 @@ struct WorkItem {
 struct WorkList {
   const WorkItem* items = nullptr;   // device, longest first
   int count = 0;
-  unsigned* counter = nullptr;       // device work counter, reset by every launch that uses it
+  unsigned* counter = nullptr;       // device work counter: zero between launches, but launch_m2l_mfma resets it
   bool parts = false;                // the items are parts (streamed forward) or rounds (adjoint) of sub-grids
 };
 
