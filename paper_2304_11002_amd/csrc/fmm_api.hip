@@ -270,14 +270,15 @@ ListItems build_lists(const fmm_ctx* ctx, DescEntry* e, unsigned need) {
   const int num_cu = ctx->mfma.num_cu;
   ListItems li;
   li.whole.resize((size_t)nsub);
-  sort_by_cost(e->host.data(), nsub, harmonic, li.whole.data());
-  if (need & (need_forward(false) | need_forward(true))) {
+  const bool adjoint = (need & (need_adjoint(false) | need_adjoint(true))) != 0;
+  sort_by_cost(e->host.data(), nsub, harmonic, adjoint, li.whole.data());
+  if (!adjoint) {
     const StreamPlan plan = plan_stream(li.whole.data(), nsub, num_cu);
     e->plan[harmonic] = plan;
     if (plan.parts || nsub <= kMaxSplitSubgrids) {
       li.cut = li.whole;
       li.cut.resize((size_t)max_parts(nsub));
-      li.cut.resize((size_t)split_items(li.cut.data(), nsub, num_cu));
+      li.cut.resize((size_t)split_items(e->host.data(), li.cut.data(), nsub, num_cu));
     }
   } else {
     const AdjointPlan plan = plan_adjoint(li.whole.data(), nsub, num_cu, harmonic);
@@ -952,9 +953,9 @@ fmm_status fmm_m2l_noalloc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, 
   const bool streams = mfma_config_streams(cfg);
   int64_t count = nsub;
   WorkList wl;
-  sort_by_cost(desc, nsub, harm, items);
+  sort_by_cost(desc, nsub, harm, false, items);
   wl.parts = streams && takes_parts(ctx, nsub, plan_stream(items, nsub, ctx->mfma.num_cu));
-  if (wl.parts) count = split_items(items, nsub, ctx->mfma.num_cu);
+  if (wl.parts) count = split_items(desc, items, nsub, ctx->mfma.num_cu);
   else whole_items(items, nsub);
   const size_t used = kNoAllocWorkOff + sizeof(WorkItem) * (size_t)count;
   HIP_TRY(ctx, hipMemcpyAsync(ctx->noalloc_dev, hp, used, hipMemcpyHostToDevice, s));

@@ -23,10 +23,11 @@ struct WorkList {
 };
 
 // Host: the sub-grids in out[0 .. nsub), longest first (equal costs by
-// descriptor index), each item's cost in `part`. The cost is its products:
-// C^2 x present pairs for the dense form, (p+1)^4 x present pairs for the
-// harmonic form, whose p = 4 : p = 3 ratio is 2.44, not 3.06.
-void sort_by_cost(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkItem* out);
+// descriptor index), each item's cost in `part`. The cost is its products, C^2 a
+// pair for the dense form and (p+1)^4 for the harmonic form, whose p = 4 : p = 3
+// ratio is 2.44, not 3.06: of the present pairs and half of the absent ones in
+// the forward, of all pairs in the adjoint.
+void sort_by_cost(const fmm_subgrid* desc, int64_t nsub, bool harmonic, bool adjoint, WorkItem* out);
 // Sorted items (costs in `part`) as whole sub-grids, in place.
 void whole_items(WorkItem* items, int64_t n);
 // How the streamed forward runs sorted items (costs in `part`): as parts or as
@@ -37,16 +38,15 @@ struct StreamPlan {
 };
 StreamPlan plan_stream(const WorkItem* items, int64_t n, int num_cu);
 // Sorted items cut into parts, in place (room for max_parts(n)); returns their
-// number. A sub-grid goes in 4 parts, and in 8 or 32 while a part costs more
-// than the work left from it on, per workgroup slot: a batch that cannot fill
-// the GPU is spread over it, and a large one ends on small parts instead of a
-// last wave that most compute units sit out.
+// number. A sub-grid goes in 4 parts, and in 8 or 32 where a part would take long
+// against the whole batch spread over the GPU: a batch that cannot fill the GPU is
+// spread over it, and a larger one does not wait for its longest sub-grids.
 constexpr int kMaxPartLevel = 2;
 constexpr int kLevelParts[kMaxPartLevel + 1] = {4, 8, 32};
 constexpr int64_t kMaxExtraItems = 8192;
 constexpr int64_t kMaxSplitSubgrids = 256;   // batches that FMM_OPT_ROUND_SPLIT = 1 applies to
 constexpr int64_t max_parts(int64_t n) { return n * kLevelParts[0] + kMaxExtraItems; }
-int64_t split_items(WorkItem* items, int64_t n, int num_cu);
+int64_t split_items(const fmm_subgrid* desc, WorkItem* items, int64_t n, int num_cu);
 
 // The same for the adjoint: by rounds or whole sub-grids, and with the mass
 // gradients in the same launch (whole sub-grids) or in one of their own.

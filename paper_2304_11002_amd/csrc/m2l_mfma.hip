@@ -1680,14 +1680,22 @@ constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 
 }  // namespace
 
-void sort_by_cost(const fmm_subgrid* desc, int64_t nsub, bool harmonic, WorkItem* out) {
+// What a sub-grid takes against one of its order with every block present (256 alike,
+// whole, p = 2 to 4): forward, with a share f of the pairs present, 0.71 to 0.76 at
+// f = 0.34, 0.76 to 0.84 at 0.37 to 0.42, 0.86 to 0.93 at 0.52, 0.94 to 1.05 from
+// 0.68 on, as its windows are staged all the same and a tile's products skip only
+// quads with no present source; the adjoint 1.09 to 1.19 whatever the mask, as nearly
+// every pair of offsets meets some present block.
+void sort_by_cost(const fmm_subgrid* desc, int64_t nsub, bool harmonic, bool adjoint, WorkItem* out) {
+  constexpr int64_t kAll = (int64_t)kNTarget * kNStencil;
   for (int64_t b = 0; b < nsub; ++b) {
     const int p = desc[b].p;
     const int64_t per_pair = harmonic ? (int64_t)(p + 1) * (p + 1) * (p + 1) * (p + 1)
                                       : (int64_t)ncomp(p) * ncomp(p);
     const int64_t pairs = pairs_of_mask(desc[b].mask);
     out[b].sub = (int32_t)b;
-    out[b].part = (int32_t)(per_pair * pairs / 4096);   // below 2^18
+    const int64_t counted = !adjoint ? (kAll + pairs) / 2 : desc[b].mask == kFullMask ? kAll : kAll * 9 / 8;
+    out[b].part = (int32_t)(per_pair * counted / 4096);   // below 2^18
   }
   std::sort(out, out + nsub, [](const WorkItem& a, const WorkItem& b) {
     return a.part != b.part ? a.part > b.part : a.sub < b.sub;
@@ -1699,58 +1707,81 @@ void whole_items(WorkItem* items, int64_t n) {
 }
 
 // Time (in cost units) of the items, longest first, on num_cu compute units that
-// each take the next one when free, with `each` added to every item.
-static int64_t makespan(const WorkItem* items, int64_t n, int num_cu, int64_t total, int64_t each) {
+// each take the next one when free (ahead: when they start the one before it), with
+// `each` added to every item.
+static int64_t makespan(const WorkItem* items, int64_t n, int num_cu, int64_t total, int64_t each, bool ahead = false) {
   constexpr int kMaxUnits = 1024;
   if (n <= num_cu) return items[0].part + each;
   if (items[0].part == items[n - 1].part) return ((n + num_cu - 1) / num_cu) * (items[0].part + each);
   // unlike sub-grids end on short ones: past a few per unit the ends even out
   if (n > 4 * (int64_t)num_cu || num_cu > kMaxUnits) return (total + n * each) / num_cu;
-  int64_t free_at[kMaxUnits] = {};   // a min-heap
+  struct Unit {
+    int64_t at, last;   // when it takes another item; ahead: the one it starts then
+    bool operator>(const Unit& o) const { return at != o.at ? at > o.at : last > o.last; }
+  };
+  Unit units[kMaxUnits] = {};   // a min-heap
   for (int64_t i = 0; i < n; ++i) {
-    std::pop_heap(free_at, free_at + num_cu, std::greater<int64_t>());
-    free_at[num_cu - 1] += items[i].part + each;
-    std::push_heap(free_at, free_at + num_cu, std::greater<int64_t>());
+    std::pop_heap(units, units + num_cu, std::greater<Unit>());
+    Unit& u = units[num_cu - 1];
+    const int64_t cost = items[i].part + each;
+    u.at += ahead ? u.last : cost;
+    u.last = ahead ? cost : 0;
+    std::push_heap(units, units + num_cu, std::greater<Unit>());
   }
-  return *std::max_element(free_at, free_at + num_cu);
+  int64_t end = 0;
+  for (int i = 0; i < num_cu; ++i) end = std::max(end, units[i].at + units[i].last);
+  return end;
+}
+
+// the longest of the items is over 1.5 times the mean
+static bool unlike_items(const WorkItem* items, int64_t n, int64_t total) {
+  return n > 0 && 2 * n * items[0].part > 3 * total;
 }
 
 // In cost units (p = 3, all blocks present: 28,544 harmonic, 44,600 dense; a
 // workgroup takes 0.031 us per unit, so 890 and 1350 us): a batch in parts takes
-// 1.03 of its work spread evenly plus about a fifth of its longest sub-grid (512
-// alike: 2050 us against 1850 whole; 300: 1230 against 1960; 700 mixed: 3300
-// against 3640); moments cost 100 us inside a whole sub-grid's launch and 0.77 us
-// of the whole GPU per sub-grid in a launch of their own.
+// 1.04 of its work spread evenly, with 900 units a sub-grid for the windows that its
+// parts stage besides, plus a fifth of its longest sub-grid, or less where that one is
+// cut finer (512 alike: 2050 us against 1850 whole; 300: 1230 against 1960; 256 of
+// p = 2, uneven, harmonic: 565 against 526; 500 mixed, uneven, dense: 3910 against
+// 4300). Moments cost 140 us inside a whole sub-grid's launch, where a workgroup also
+// takes its next sub-grid when it starts one, and 0.64 us of the whole GPU per sub-grid
+// in a launch of their own (harmonic, in one launch against two: 700 of p = 3 3192 and
+// 3276 us, 2000 8390 and 8850, 1034 5190 and 4880 in parts; 513 mixed, uneven 3750
+// and 3055).
 StreamPlan plan_stream(const WorkItem* items, int64_t n, int num_cu) {
-  constexpr int64_t kMomentsInside = 3300, kMomentsApart = 6300;
+  constexpr int64_t kMomentsInside = 4500, kMomentsApart = 5300, kStaged = 900;
   if (n == 0) return StreamPlan{};
   int64_t total = 0;
   for (int64_t i = 0; i < n; ++i) total += items[i].part;
   const int64_t whole = makespan(items, n, num_cu, total, 0);
-  const int64_t parts = (total * 103 / num_cu + 20 * (int64_t)items[0].part) / 100;
+  const int64_t longest = (unlike_items(items, n, total) ? 8 : 21) * (int64_t)items[0].part;
+  const int64_t parts = ((total + n * kStaged) * 104 / num_cu + longest) / 100;
   StreamPlan p;
   p.parts = parts < whole;
-  p.fuse = n > num_cu && makespan(items, n, num_cu, total, kMomentsInside) <
+  p.fuse = n > num_cu && makespan(items, n, num_cu, total, kMomentsInside, true) <
                              std::min(parts, whole) + n * kMomentsApart / num_cu;
   return p;
 }
 
 // The adjoint's units (p = 3: 28,544 harmonic, 44,600 dense, 1230 and 1660 us of a
-// workgroup). By rounds, a batch takes its work spread evenly (harmonic: 1.04 of
-// it, each round folds dL anew) plus about an eighth of its longest sub-grid:
-// harmonic p = 3, whole against rounds: 1 sub-grid 1160 and 166 us, 256 1379 and
+// workgroup). By rounds, a batch takes its work spread evenly (harmonic: 1.05 of
+// it, as each round folds dL anew; dense 0.97) plus about an eighth of its longest
+// sub-grid (dense: little where that one is far longer than the others): harmonic
+// p = 3, whole against rounds: 1 sub-grid 1160 and 166 us, 256 1379 and
 // 1459, 300 2505 and 1760, 512 2631 and 2776, 600 3795 and 3202, 2048 9853 and
-// 10307; dense, 19 of mixed p 5170 and 326, 900 alike 6655 and 5854. Mass gradients
-// cost 120 us inside a sub-grid's launch, and 1.14 us of the whole GPU per sub-grid
-// in a launch of their own (600 harmonic: 4121 us inside, 3815 apart; 900: 5447 and
-// 5746).
+// 10307; 256 of p = 4, uneven, 3340 and 3760; 900 of mixed p 6030 and 6300; dense, 19
+// of mixed p 5170 and 326, 900 alike 6655 and 5854. Mass gradients cost 130 us inside
+// a sub-grid's launch, and 0.98 us of the whole GPU per sub-grid in a launch of their
+// own (600 harmonic: 4121 us inside, 3815 apart; 900: 5447 and 5746).
 AdjointPlan plan_adjoint(const WorkItem* items, int64_t n, int num_cu, bool harmonic) {
-  constexpr int64_t kGradsInside = 2800, kGradsApart = 6800;
+  constexpr int64_t kGradsInside = 3100, kGradsApart = 5800;
   if (n == 0) return AdjointPlan{};
   int64_t total = 0;
   for (int64_t i = 0; i < n; ++i) total += items[i].part;
   const int64_t whole = makespan(items, n, num_cu, total, 0);
-  const int64_t split = (total * (harmonic ? 104 : 100) / num_cu + 12 * (int64_t)items[0].part) / 100;
+  const int64_t longest = (!unlike_items(items, n, total) ? 13 : harmonic ? 12 : 4) * (int64_t)items[0].part;
+  const int64_t split = (total * (harmonic ? 105 : 97) / num_cu + longest) / 100;
   AdjointPlan p;
   p.rounds = split < whole && n <= kMaxRoundSubgrids;
   p.fuse = n > num_cu && makespan(items, n, num_cu, total, kGradsInside) <
@@ -1763,18 +1794,22 @@ AdjointPlan plan_adjoint(const WorkItem* items, int64_t n, int num_cu, bool harm
 // of its own takes longer than the whole batch on a full GPU. 32 alike: 288 in
 // quarters, 188 in eighths; 43 alike 293 and 302; 100 alike 514 and 559. A batch
 // of unlike sub-grids, whose longest would set the time, gains further up: 64
-// mixed orders 956 and 701, 128 1102 and 958, 200 1390 and 1349. Tiles, which
+// mixed orders 956 and 701, 128 1102 and 958, 200 1390 and 1349; those with absent
+// blocks, whose parts skip more than the whole does, a little less far (200 mixed
+// and uneven, dense, the partly present ones of p = 4 in quarters: 1770 against 1905,
+// 260 2200 against 2435). Tiles, which
 // stage more window and use the matrix cores less well, only where eighths cannot
 // reach every compute unit: 8 alike 266 in quarters, 158 in eighths, 118 in tiles;
 // 24 alike 279, 180, 269.
-int64_t split_items(WorkItem* items, int64_t n, int num_cu) {
+int64_t split_items(const fmm_subgrid* desc, WorkItem* items, int64_t n, int num_cu) {
   int64_t total = 0, extra = 0;
   for (int64_t i = 0; i < n; ++i) total += items[i].part;
-  const bool unlike = n > 0 && 2 * n * items[0].part > 3 * total;   // the longest is over 1.5 times the mean
+  const bool unlike = unlike_items(items, n, total);
   for (int64_t i = 0; i < n; ++i) {
     const int64_t c = (int64_t)items[i].part * num_cu;
     int level = 0;
-    if ((unlike ? c * 2 : c * 6 / 10) > 4 * total) level = 1;
+    const int64_t tenths = !unlike ? 6 : desc[items[i].sub].mask == kFullMask ? 20 : 16;
+    if (c * tenths / 10 > 4 * total) level = 1;
     if (c * 6 / 10 > 8 * total) level = 2;
     if (extra + kLevelParts[level] - kLevelParts[0] > kMaxExtraItems) level = 0;
     extra += kLevelParts[level] - kLevelParts[0];
