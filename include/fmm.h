@@ -40,10 +40,12 @@
  *     the null stream). The host waits, and memory is allocated, only in
  *     these cases:
  *       * the first call with a descriptor set the context does not hold
- *         allocates device and pinned host memory for its copy (hipMalloc,
- *         hipHostMalloc), and the first M2L and the first M2L adjoint of each
- *         form on it for their work lists (if that call is under stream
- *         capture, the host also waits for their upload);
+ *         allocates device and pinned host memory for its copy and work
+ *         lists (hipMalloc, hipHostMalloc);
+ *       * the work lists of the M2L and of its adjoint, per form, are made by
+ *         the first call that uses them: with more than 1024 sub-grids, and
+ *         unless it is the set's first call, that call allocates them too; if
+ *         it is under stream capture, the host waits for their upload;
  *       * when the context already holds 8 sets, that call first evicts the
  *         least recently used one: the host waits for that set's last launch
  *         and frees its memory and the graphs captured for it (graphs of the

@@ -47,8 +47,8 @@ uint64_t fnv1a(const void* data, size_t n, uint64_t h = 1469598103934665603ull) 
 }  // namespace
 
 // Work lists of one form's forward or adjoint calls on a descriptor set, made by
-// the first of them (P2M and evaluation need none): in the set's own allocation if
-// that call is the set's first, else in one of theirs.
+// the first of them (P2M and evaluation need none): in the set's allocation, or for
+// large sets, unless that call is the set's first, in one of their own.
 struct CallLists {
   bool made = false;
   void* dev = nullptr;            // (own device allocation and pinned host copy, if any)
@@ -57,9 +57,11 @@ struct CallLists {
                                   // after it one that the per-wave launches reset
   WorkList cut;                   // their parts (forward) or rounds (adjoint), where planned or asked for
 };
-// the lists a call needs (a bit each)
-constexpr unsigned need_forward(bool harmonic) { return 1u << harmonic; }
-constexpr unsigned need_adjoint(bool harmonic) { return 4u << harmonic; }
+// the lists a call needs
+constexpr int need_forward(bool harmonic) { return harmonic ? 1 : 0; }
+constexpr int need_adjoint(bool harmonic) { return harmonic ? 3 : 2; }
+constexpr int kNeedNone = -1;
+constexpr int64_t kRoomSubgrids = 1024;   // sets of up to so many keep room for all lists (0.5 MB)
 
 // Descriptor set uploaded to the device, plus everything derived from it.
 struct DescEntry {
@@ -73,7 +75,8 @@ struct DescEntry {
   DevDesc* d_desc = nullptr;
   int* d_ids[kMaxP + 1] = {};     // reference kernels: sub-grids per order
   int count[kMaxP + 1] = {};
-  CallLists forward[2], adjoint[2];   // per form (dense, harmonic)
+  CallLists lists[4];             // by need
+  size_t room[4] = {};            // their places in the allocation, if kept there
   StreamPlan plan[2];             // made with the lists
   AdjointPlan adjoint_plan[2];
   bool part_even = true;          // every part_off even: particle blocks 16-byte aligned
@@ -232,11 +235,10 @@ void free_entry(DescEntry* e) {
   if (e->ready) (void)hipEventSynchronize(e->ready);
   if (e->dev) (void)hipFree(e->dev);
   if (e->pinned) (void)hipHostFree(e->pinned);
-  for (int f = 0; f < 2; ++f)
-    for (CallLists* l : {&e->forward[f], &e->adjoint[f]}) {
-      if (l->dev) (void)hipFree(l->dev);
-      if (l->pinned) (void)hipHostFree(l->pinned);
-    }
+  for (CallLists& l : e->lists) {
+    if (l.dev) (void)hipFree(l.dev);
+    if (l.pinned) (void)hipHostFree(l.pinned);
+  }
   if (e->slice_dev) (void)hipFree(e->slice_dev);
   if (e->ready) (void)hipEventDestroy(e->ready);
   if (e->last_launch) (void)hipEventDestroy(e->last_launch);
@@ -256,21 +258,34 @@ constexpr size_t kMaxGraphs = 16;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Sizes of a set's allocations: sets that replace each other mostly have the same
+// (a new size costs hipHostMalloc 100 to 150 us, one just freed 15).
+size_t alloc_size(size_t x) {
+  size_t n = 64 << 10;
+  while (n < x) n *= 2;
+  return n;
+}
+
 struct ListItems {
   std::vector<WorkItem> whole, cut;
   size_t off_cut() const { return align_up(sizeof(WorkItem) * whole.size(), 256); }
   size_t off_counter() const { return align_up(off_cut() + sizeof(WorkItem) * cut.size(), 256); }
   size_t bytes() const { return off_counter() + 256; }
 };
+// at most, for nsub sub-grids
+size_t list_room(int64_t nsub, int need) {
+  const int64_t cut = need >= need_adjoint(false) ? nsub * kMaxRounds
+                                                  : std::min(nsub * kLevelParts[kMaxPartLevel], max_parts(nsub));
+  return align_up(sizeof(WorkItem) * (size_t)nsub, 256) + align_up(sizeof(WorkItem) * (size_t)cut, 256) + 256;
+}
 
 // The items of the lists of one need, longest sub-grid first, and the plan they follow.
-ListItems build_lists(const fmm_ctx* ctx, DescEntry* e, unsigned need) {
-  const bool harmonic = (need & (need_forward(true) | need_adjoint(true))) != 0;
+ListItems build_lists(const fmm_ctx* ctx, DescEntry* e, int need) {
+  const bool adjoint = need >= need_adjoint(false), harmonic = need == need_forward(true) || need == need_adjoint(true);
   const int64_t nsub = (int64_t)e->host.size();
   const int num_cu = ctx->mfma.num_cu;
   ListItems li;
   li.whole.resize((size_t)nsub);
-  const bool adjoint = (need & (need_adjoint(false) | need_adjoint(true))) != 0;
   sort_by_cost(e->host.data(), nsub, harmonic, adjoint, li.whole.data());
   if (!adjoint) {
     const StreamPlan plan = plan_stream(li.whole.data(), nsub, num_cu);
@@ -294,12 +309,6 @@ ListItems build_lists(const fmm_ctx* ctx, DescEntry* e, unsigned need) {
   return li;
 }
 
-CallLists* lists_of(DescEntry* e, unsigned need) {
-  return need == need_forward(false)  ? &e->forward[0]
-         : need == need_forward(true) ? &e->forward[1]
-                                      : &e->adjoint[need == need_adjoint(true)];
-}
-
 // Writes the lists at hp (host) for their copy to dp (device).
 void place_lists(const ListItems& li, CallLists* l, char* hp, char* dp) {
   std::memcpy(hp, li.whole.data(), sizeof(WorkItem) * li.whole.size());
@@ -316,9 +325,9 @@ void place_lists(const ListItems& li, CallLists* l, char* hp, char* dp) {
 }
 
 // Find or upload the descriptor set; builds the id lists, and for a new set the
-// work lists of the call's need (0: none).
+// work lists of the call's need.
 fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStream_t stream,
-                    unsigned need, DescEntry** out) {
+                    int need, DescEntry** out) {
   const size_t nbytes = sizeof(fmm_subgrid) * (size_t)nsub;
   const uint64_t h = fnv1a(desc, nbytes, fnv1a(&nsub, sizeof nsub));
   for (auto& e : ctx->descs) {
@@ -355,7 +364,7 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
   e->hash = h;
   e->id = ++ctx->next_id;
   e->last_use = ++ctx->clock;
-  // layout: descriptors | ids per order | work lists
+  // layout: descriptors | ids per order | the call's work lists | room for the others
   std::vector<int> ids[kMaxP + 1];
   for (int64_t b = 0; b < nsub; ++b) {
     ids[desc[b].p].push_back((int)b);
@@ -369,9 +378,18 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     off = align_up(off + sizeof(int) * ids[p].size(), 256);
   }
   ListItems lists;
-  if (need) lists = build_lists(ctx, e.get(), need);
-  const size_t off_lists = off;
-  e->bytes = off + (need ? lists.bytes() : 0);
+  if (need != kNeedNone) {
+    lists = build_lists(ctx, e.get(), need);
+    e->room[need] = off;
+    off = align_up(off + lists.bytes(), 256);
+  }
+  const size_t upload = off;
+  for (int k = 0; k < 4 && nsub <= kRoomSubgrids; ++k)
+    if (k != need) {
+      e->room[k] = off;
+      off += list_room(nsub, k);
+    }
+  e->bytes = alloc_size(off);
   HIP_TRY(ctx, hipMalloc(&e->dev, e->bytes));
   HIP_TRY(ctx, hipHostMalloc(&e->pinned, e->bytes, hipHostMallocDefault));
   char* hp = static_cast<char*>(e->pinned);
@@ -383,10 +401,10 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
     e->d_ids[p] = reinterpret_cast<int*>(dp + off_ids[p]);
     e->count[p] = (int)ids[p].size();
   }
-  if (need) place_lists(lists, lists_of(e.get(), need), hp + off_lists, dp + off_lists);
+  if (need != kNeedNone) place_lists(lists, &e->lists[need], hp + e->room[need], dp + e->room[need]);
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->ready, hipEventDisableTiming));
   HIP_TRY(ctx, hipEventCreateWithFlags(&e->last_launch, hipEventDisableTiming));
-  HIP_TRY(ctx, hipMemcpyAsync(e->dev, e->pinned, e->bytes, hipMemcpyHostToDevice, stream));
+  HIP_TRY(ctx, hipMemcpyAsync(e->dev, e->pinned, upload, hipMemcpyHostToDevice, stream));
   HIP_TRY(ctx, hipEventRecord(e->ready, stream));
   HIP_TRY(ctx, hipEventRecord(e->last_launch, stream));
   *out = e.get();
@@ -397,8 +415,8 @@ fmm_status get_desc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, hipStre
 // Makes the lists of a need that the set's first call did not have, copied on the
 // caller's stream. A caller whose stream is being captured gets them at once (the
 // captured work runs later, and other calls may use them before).
-fmm_status ensure_lists(fmm_ctx* ctx, DescEntry* e, unsigned need, hipStream_t stream) {
-  CallLists* l = lists_of(e, need);
+fmm_status ensure_lists(fmm_ctx* ctx, DescEntry* e, int need, hipStream_t stream) {
+  CallLists* l = &e->lists[need];
   if (l->made) return FMM_OK;
   const ListItems li = build_lists(ctx, e, need);
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -406,11 +424,17 @@ fmm_status ensure_lists(fmm_ctx* ctx, DescEntry* e, unsigned need, hipStream_t s
   const bool capturing = status == hipStreamCaptureStatusActive;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // lets this thread allocate and wait while it captures
   if (capturing) HIP_TRY(ctx, hipThreadExchangeStreamCaptureMode(&mode));
-  hipError_t err = hipMalloc(&l->dev, li.bytes());
-  if (err == hipSuccess) err = hipHostMalloc(&l->pinned, li.bytes(), hipHostMallocDefault);
+  hipError_t err = hipSuccess;
+  char *hp = static_cast<char*>(e->pinned) + e->room[need], *dp = static_cast<char*>(e->dev) + e->room[need];
+  if (!e->room[need]) {
+    err = hipMalloc(&l->dev, alloc_size(li.bytes()));
+    if (err == hipSuccess) err = hipHostMalloc(&l->pinned, alloc_size(li.bytes()), hipHostMallocDefault);
+    hp = static_cast<char*>(l->pinned);
+    dp = static_cast<char*>(l->dev);
+  }
   if (err == hipSuccess) {
-    place_lists(li, l, static_cast<char*>(l->pinned), static_cast<char*>(l->dev));
-    err = hipMemcpyAsync(l->dev, l->pinned, li.bytes(), hipMemcpyHostToDevice, capturing ? ctx->internal : stream);
+    place_lists(li, l, hp, dp);
+    err = hipMemcpyAsync(dp, hp, li.bytes(), hipMemcpyHostToDevice, capturing ? ctx->internal : stream);
   }
   if (err == hipSuccess)
     err = capturing ? hipStreamSynchronize(ctx->internal) : hipEventRecord(e->last_launch, stream);
@@ -587,7 +611,7 @@ fmm_status fmm_p2m(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, const do
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, 0, &e));
+  CHECK_OK(get_desc(ctx, desc, nsub, s, kNeedNone, &e));
   HIP_TRY(ctx, launch_p2m(e->d_desc, nsub, e->d_ids, e->count, pos, mass, ppc, M, e->part_even,
                           ctx->p2m_window != 0, s));
   return mark_used(ctx, e, s);
@@ -607,7 +631,7 @@ fmm_status fmm_p2m_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, 0, &e));
+  CHECK_OK(get_desc(ctx, desc, nsub, s, kNeedNone, &e));
   HIP_TRY(ctx, launch_p2m_backward(e->d_desc, nsub, e->d_ids, e->count, pos, ppc, dM, dmass, e->part_even, s));
   return mark_used(ctx, e, s);
 }
@@ -630,7 +654,7 @@ fmm_status fmm_evaluate(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  CHECK_OK(get_desc(ctx, desc, nsub, s, 0, &e));
+  CHECK_OK(get_desc(ctx, desc, nsub, s, kNeedNone, &e));
   HIP_TRY(ctx, launch_evaluate(e->d_desc, nsub, pos, mass, ppc, L, out, s));
   return mark_used(ctx, e, s);
 }
@@ -791,7 +815,7 @@ static fmm_status run_ref(fmm_ctx* ctx, DescEntry* e, bool backward, const doubl
 // graph if enabled.
 static fmm_status run_mfma(fmm_ctx* ctx, DescEntry* e, const double* M, double* L,
                            fmm_precision prec, int cfg, hipStream_t s) {
-  WorkList wl = e->forward[0].whole;
+  WorkList wl = e->lists[need_forward(false)].whole;
   wl.counter += 1;
   if (!ctx->use_graph) {
     HIP_TRY(ctx, launch_m2l_mfma(ctx->mfma, wl, e->d_desc, M, L, prec, cfg, s));
@@ -856,7 +880,7 @@ static fmm_status run_slice(fmm_ctx* ctx, DescEntry* e, const double* M, double*
   }
   int8_t* pl = static_cast<int8_t*>(e->slice_dev);
   int32_t* ex = reinterpret_cast<int32_t*>(pl + planes);
-  HIP_TRY(ctx, launch_m2l_slice(ctx->mfma, ctx->slice, e->forward[1].whole, e->d_desc, nsub, M, L, ctx->slices, pl, ex, s));
+  HIP_TRY(ctx, launch_m2l_slice(ctx->mfma, ctx->slice, e->lists[need_forward(true)].whole, e->d_desc, nsub, M, L, ctx->slices, pl, ex, s));
   return FMM_OK;
 }
 
@@ -868,7 +892,7 @@ static bool takes_parts(const fmm_ctx* ctx, int64_t nsub, const StreamPlan& plan
 
 // (its forward lists made)
 static const WorkList& stream_list(const fmm_ctx* ctx, const DescEntry* e, bool harmonic) {
-  const CallLists& l = e->forward[harmonic];
+  const CallLists& l = e->lists[need_forward(harmonic)];
   return takes_parts(ctx, (int64_t)e->host.size(), e->plan[harmonic]) ? l.cut : l.whole;
 }
 
@@ -885,7 +909,7 @@ static fmm_status run_m2l(fmm_ctx* ctx, DescEntry* e, const double* M, double* L
     return FMM_OK;
   }
   if (prec == FMM_SPLIT_FP32) {
-    HIP_TRY(ctx, launch_m2l_split(ctx->mfma, e->forward[0].whole, e->d_desc, M, L, s));
+    HIP_TRY(ctx, launch_m2l_split(ctx->mfma, e->lists[need_forward(false)].whole, e->d_desc, M, L, s));
     return FMM_OK;
   }
   return run_mfma(ctx, e, M, L, prec, cfg, s);
@@ -914,7 +938,7 @@ fmm_status fmm_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, const do
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
+  const int need = ctx->m2l_kernel == 1 ? kNeedNone : need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
   CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   CHECK_OK(run_m2l(ctx, e, M, L, prec, pick_config(ctx, e, prec), s));
   return mark_used(ctx, e, s);
@@ -991,7 +1015,7 @@ fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, cons
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
+  const int need = ctx->m2l_kernel == 1 ? kNeedNone : need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
   CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   const int cfg = pick_config(ctx, e, prec);
   const bool aligned = ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(mass)) & 15u) == 0;
@@ -1003,7 +1027,7 @@ fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, cons
     fuse = e->plan[harm].fuse;
   }
   if (fuse) {
-    HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, e->forward[harm].whole, e->d_desc, M, L, harm, s, pos, mass, M));
+    HIP_TRY(ctx, launch_m2l_stream(ctx->mfma, e->lists[need_forward(harm)].whole, e->d_desc, M, L, harm, s, pos, mass, M));
   } else {
     HIP_TRY(ctx, launch_p2m(e->d_desc, nsub, e->d_ids, e->count, pos, mass, ppc, M, e->part_even, true, s));
     CHECK_OK(run_m2l(ctx, e, M, L, prec, cfg, s));
@@ -1013,7 +1037,7 @@ fmm_status fmm_p2m_m2l(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, cons
 
 // (its adjoint lists made)
 static const WorkList& adjoint_list(const DescEntry* e, bool harmonic) {
-  const CallLists& l = e->adjoint[harmonic];
+  const CallLists& l = e->lists[need_adjoint(harmonic)];
   return e->adjoint_plan[harmonic].rounds ? l.cut : l.whole;
 }
 
@@ -1031,7 +1055,7 @@ fmm_status fmm_m2l_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_adjoint(ctx->adjoint_form == 1);
+  const int need = ctx->m2l_kernel == 1 ? kNeedNone : need_adjoint(ctx->adjoint_form == 1);
   CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   if (ctx->m2l_kernel == 1) {
     CHECK_OK(run_ref(ctx, e, true, dL, dM, s));
@@ -1060,13 +1084,13 @@ fmm_status fmm_m2l_p2m_backward(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t n
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  const unsigned need = ctx->m2l_kernel == 1 ? 0 : need_adjoint(ctx->adjoint_form == 1);
+  const int need = ctx->m2l_kernel == 1 ? kNeedNone : need_adjoint(ctx->adjoint_form == 1);
   CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   const bool aligned = ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(dmass)) & 15u) == 0;
   const bool harm = ctx->adjoint_form == 1;
   if (ctx->m2l_kernel != 1) CHECK_OK(ensure_lists(ctx, e, need_adjoint(harm), s));
   if (ctx->m2l_kernel != 1 && ppc == 8 && e->part_even && aligned && e->adjoint_plan[harm].fuse) {
-    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, e->adjoint[harm].whole, e->d_desc, dL, dM, harm, s, pos, dmass));
+    HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, e->lists[need_adjoint(harm)].whole, e->d_desc, dL, dM, harm, s, pos, dmass));
   } else {
     if (ctx->m2l_kernel == 1) CHECK_OK(run_ref(ctx, e, true, dL, dM, s));
     else HIP_TRY(ctx, launch_m2l_mfma_backward(ctx->mfma, adjoint_list(e, harm), e->d_desc, dL, dM, harm, s));
@@ -1104,7 +1128,7 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
   DeviceGuard guard(ctx->device);
   HIP_TRY(ctx, guard.err);
   DescEntry* e = nullptr;
-  const unsigned need = need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
+  const int need = need_forward(prec == FMM_FP64_HARMONIC || prec == FMM_EXACT_SLICE);
   CHECK_OK(get_desc(ctx, desc, nsub, s, need, &e));
   if (prec == FMM_EXACT_SLICE) {
     // one kernel: nothing to time
@@ -1114,7 +1138,7 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
   }
   const bool harm = prec == FMM_FP64_HARMONIC;
   CHECK_OK(ensure_lists(ctx, e, need_forward(harm), s));
-  WorkList per_wave = e->forward[harm].whole;
+  WorkList per_wave = e->lists[need_forward(harm)].whole;
   per_wave.counter += 1;
   hipEvent_t t0, t1;
   HIP_TRY(ctx, hipEventCreate(&t0));
@@ -1126,7 +1150,7 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
     // one warm-up launch, then the best of three, as fmm_m2l runs the configuration
     auto launch = [&]() {
       return mfma_config_streams(cfg) ? launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s)
-             : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, e->forward[0].whole, e->d_desc, M, L, s)
+             : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, e->lists[need_forward(false)].whole, e->d_desc, M, L, s)
                                       : launch_m2l_mfma(ctx->mfma, per_wave, e->d_desc, M, L, prec, cfg, s);
     };
     HIP_TRY(ctx, launch());

@@ -24,7 +24,9 @@ def _batch(torch, seed, n):
     rng = np.random.default_rng([71, seed, n])
     desc, m_el, l_el = fmm.make_descriptors(rng.integers(2, 5, n), rng.integers(0, 3, n),
                                             [synth.random_mask(rng) for _ in range(n)])
-    return desc, torch.from_numpy(rng.standard_normal(m_el)).to("cuda"), l_el
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return desc, torch.randn(m_el, dtype=torch.float64, device="cuda", generator=g), l_el
 
 
 def _uploaded(torch, path, call):
@@ -63,12 +65,12 @@ def test_calls_without_lists_upload_descriptors_only(torch, tmp_path):
 
 
 @pytest.mark.parametrize("mode", ["thread_local", "global"])
-@pytest.mark.parametrize("n", [3, 150, 600])
+@pytest.mark.parametrize("n", [3, 150, 600, 1100])       # (above 1024 the lists are allocated then)
 def test_first_m2l_and_adjoint_of_a_set_under_capture(torch, n, mode):
     # the set is known from another call; its lists are made during the capture
     ensure_library()
     desc, M, l_el = _batch(torch, 1, n)
-    dL = torch.from_numpy(np.random.default_rng(73).standard_normal(l_el)).to("cuda")
+    dL = torch.randn(l_el, dtype=torch.float64, device="cuda")
     for prec, form in ((fmm.FMM_FP64, 0), (fmm.FMM_FP64_HARMONIC, 1)):
         with fmm.Context(0) as ref:
             ref.set_option(fmm.FMM_OPT_ADJOINT_FORM, form)
