@@ -141,8 +141,8 @@ typedef struct {
 #define FMM_OPT_ROUND_SPLIT 6  /* FMM_FP64 and FMM_FP64_HARMONIC M2L (tile configurations 0, 1, 7, 9, 10):
                                   0 one workgroup per sub-grid; 1 batches of at most 256 sub-grids in
                                   parts of a sub-grid's targets, spread over the workgroups; -1 (default)
-                                  whole sub-grids or parts, whichever is expected to be faster for the
-                                  batch. For batches that cannot fill the GPU, whose longest sub-grid
+                                  whole sub-grids or parts, whichever fmm_autotune found to be faster for
+                                  the set or else is expected to be. For batches that cannot fill the GPU, whose longest sub-grid
                                   (p = 4) would set the time, or whose last wave of sub-grids is short.
                                   The results are the same bits. */
 
@@ -340,6 +340,9 @@ fmm_status fmm_stencil_tables(fmm_ctx* ctx, int32_t p, double* out, void* stream
  * for FMM_FP64 those with per-wave table loads) on these descriptors and
  * buffers (M read, L overwritten) and keep the fastest for later calls with the
  * same descriptor set and precision; `chosen` (may be NULL) receives its index.
+ * The streamed kernel is timed over whole sub-grids and, for batches of at most
+ * 256 sub-grids or that are planned so, over parts of them; the faster is what
+ * FMM_OPT_ROUND_SPLIT = -1 runs on the set from then on.
  * Synchronises the stream. FMM_OPT_TILE_CONFIG >= 0 overrides the choice. */
 fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub,
                         const double* M, double* L, fmm_precision prec,

@@ -81,6 +81,7 @@ struct DescEntry {
   AdjointPlan adjoint_plan[2];
   bool part_even = true;          // every part_off even: particle blocks 16-byte aligned
   int tuned[4] = {-1, -1, -1, -1};   // autotuned configuration per precision
+  int tuned_parts[4] = {-1, -1, -1, -1};   // and whether it runs parts of sub-grids (-1: as planned)
   // FMM_EXACT_SLICE: the sub-grids' slice planes and exponents (one allocation)
   void* slice_dev = nullptr;
   size_t slice_bytes = 0;
@@ -116,7 +117,7 @@ struct fmm_ctx {
   int tile_config = -1;
   int adjoint_form = 0;     // FMM_OPT_ADJOINT_FORM
   int p2m_window = 0;       // FMM_OPT_P2M_WINDOW
-  int round_split = -1;     // FMM_OPT_ROUND_SPLIT: -1 as planned, 0 whole sub-grids, 1 parts (small batches)
+  int round_split = -1;     // FMM_OPT_ROUND_SPLIT: -1 as tuned or planned, 0 whole sub-grids, 1 parts (small batches)
   int slices = 7;           // FMM_OPT_SLICES
   // fmm_m2l_noalloc: this device's address of the static array, a pinned host
   // copy of it, and the event after its upload
@@ -884,16 +885,19 @@ static fmm_status run_slice(fmm_ctx* ctx, DescEntry* e, const double* M, double*
   return FMM_OK;
 }
 
-// FMM_OPT_ROUND_SPLIT: whole sub-grids, parts of them (small batches), or as planned
-static bool takes_parts(const fmm_ctx* ctx, int64_t nsub, const StreamPlan& plan) {
+// FMM_OPT_ROUND_SPLIT: whole sub-grids, parts of them (small batches), or as the
+// autotuner found (tuned) or the plan expects
+static bool takes_parts(const fmm_ctx* ctx, int64_t nsub, const StreamPlan& plan, int tuned) {
   if (ctx->round_split == 0) return false;
-  return plan.parts || (ctx->round_split == 1 && nsub <= kMaxSplitSubgrids);
+  if (ctx->round_split == 1 && nsub <= kMaxSplitSubgrids) return true;
+  return tuned < 0 ? plan.parts : tuned == 1;
 }
 
 // (its forward lists made)
 static const WorkList& stream_list(const fmm_ctx* ctx, const DescEntry* e, bool harmonic) {
   const CallLists& l = e->lists[need_forward(harmonic)];
-  return takes_parts(ctx, (int64_t)e->host.size(), e->plan[harmonic]) ? l.cut : l.whole;
+  const int tuned = e->tuned_parts[harmonic ? FMM_FP64_HARMONIC : FMM_FP64];
+  return takes_parts(ctx, (int64_t)e->host.size(), e->plan[harmonic], tuned) ? l.cut : l.whole;
 }
 
 // The M2L of one call: reference kernel, exact slices, the streamed forward, or
@@ -978,7 +982,7 @@ fmm_status fmm_m2l_noalloc(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, 
   int64_t count = nsub;
   WorkList wl;
   sort_by_cost(desc, nsub, harm, false, items);
-  wl.parts = streams && takes_parts(ctx, nsub, plan_stream(items, nsub, ctx->mfma.num_cu));
+  wl.parts = streams && takes_parts(ctx, nsub, plan_stream(items, nsub, ctx->mfma.num_cu), -1);
   if (wl.parts) count = split_items(desc, items, nsub, ctx->mfma.num_cu);
   else whole_items(items, nsub);
   const size_t used = kNoAllocWorkOff + sizeof(WorkItem) * (size_t)count;
@@ -1143,35 +1147,44 @@ fmm_status fmm_autotune(fmm_ctx* ctx, const fmm_subgrid* desc, int64_t nsub, con
   hipEvent_t t0, t1;
   HIP_TRY(ctx, hipEventCreate(&t0));
   HIP_TRY(ctx, hipEventCreate(&t1));
-  int best = -1;
-  float best_ms = 0.f;
+  int best = -1, best_parts = -1;   // the faster list of the streamed configurations (one kernel)
+  float best_ms = 0.f, stream_ms = 0.f;
   for (int cfg = 0; cfg < mfma_num_configs(); ++cfg) {
     if (!mfma_config_supports(cfg, prec) || !mfma_config_distinct(cfg)) continue;
-    // one warm-up launch, then the best of three, as fmm_m2l runs the configuration
-    auto launch = [&]() {
-      return mfma_config_streams(cfg) ? launch_m2l_stream(ctx->mfma, stream_list(ctx, e, harm), e->d_desc, M, L, harm, s)
-             : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, e->lists[need_forward(false)].whole, e->d_desc, M, L, s)
-                                      : launch_m2l_mfma(ctx->mfma, per_wave, e->d_desc, M, L, prec, cfg, s);
-    };
-    HIP_TRY(ctx, launch());
-    float cfg_ms = 1e30f;
-    for (int r = 0; r < 3; ++r) {
-      HIP_TRY(ctx, hipEventRecord(t0, s));
+    const bool streams = mfma_config_streams(cfg);
+    const CallLists& l = e->lists[need_forward(harm)];
+    for (int parts = 0; parts < (streams && l.cut.count > 0 ? 2 : 1); ++parts) {
+      // one warm-up launch, then the best of three
+      auto launch = [&]() {
+        return streams ? launch_m2l_stream(ctx->mfma, parts ? l.cut : l.whole, e->d_desc, M, L, harm, s)
+               : prec == FMM_SPLIT_FP32 ? launch_m2l_split(ctx->mfma, l.whole, e->d_desc, M, L, s)
+                                        : launch_m2l_mfma(ctx->mfma, per_wave, e->d_desc, M, L, prec, cfg, s);
+      };
       HIP_TRY(ctx, launch());
-      HIP_TRY(ctx, hipEventRecord(t1, s));
-      HIP_TRY(ctx, hipEventSynchronize(t1));
-      float ms = 0.f;
-      HIP_TRY(ctx, hipEventElapsedTime(&ms, t0, t1));
-      cfg_ms = std::min(cfg_ms, ms);
-    }
-    if (best < 0 || cfg_ms < best_ms) {
-      best = cfg;
-      best_ms = cfg_ms;
+      float ms = 1e30f;
+      for (int r = 0; r < 3; ++r) {
+        HIP_TRY(ctx, hipEventRecord(t0, s));
+        HIP_TRY(ctx, launch());
+        HIP_TRY(ctx, hipEventRecord(t1, s));
+        HIP_TRY(ctx, hipEventSynchronize(t1));
+        float one = 0.f;
+        HIP_TRY(ctx, hipEventElapsedTime(&one, t0, t1));
+        ms = std::min(ms, one);
+      }
+      if (best < 0 || ms < best_ms) {
+        best = cfg;
+        best_ms = ms;
+      }
+      if (streams && (parts == 0 || ms < stream_ms)) {
+        best_parts = parts;
+        stream_ms = ms;
+      }
     }
   }
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
   e->tuned[prec] = best;
+  e->tuned_parts[prec] = best_parts;
   if (chosen) *chosen = best;
   return mark_used(ctx, e, s);
 }
