@@ -226,7 +226,7 @@ def bench_tree(torch, fmm, ctx, K, W):
            "upward_ms": up, "m2l_ms": m2l, "downward_ms": down, "evaluate_ms": ev,
            "m2l_pairs": pairs, "m2l_pairs_per_s": pairs / (m2l * 1e-3), "m2l_form": "harmonic",
            "m2l_dense_ms": m2l_dense, "m2l_dense_tflops": fl_dense / (m2l_dense * 1e-3) / 1e12,
-           "roofline_m2l": {"bound": "mfma", "kernel": "m2l_level_kernel<3, true, 2> (levels 128, 64) + m2l_level_kernel<3, true, 1> (levels 32..4), v_mfma_f64_4x4x4, harmonic form; time of the fmm_tree_m2l call",
+           "roofline_m2l": {"bound": "mfma", "kernel": "m2l_level_kernel<3, true, true> (levels 128, 64) + m2l_level_kernel<3, true, false> (levels 32..4), v_mfma_f64_16x16x4, harmonic form; time of the fmm_tree_m2l call",
                             "achieved": fl / (m2l * 1e-3) / 1e12, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                             "frac": fl / (m2l * 1e-3) / 1e12 / FP64_PEAK_TFLOPS, "traffic": None,
                             "executed_flops": fl, "flops_per_slot": harmonic_flops_per_pair(p),
@@ -236,6 +236,63 @@ def bench_tree(torch, fmm, ctx, K, W):
     log("tree 128^3: solve %.3f ms (upward %.3f, M2L %.3f, downward %.3f, evaluate %.3f), M2L %.1f TFLOP/s executed;"
         " dense-form M2L %.3f ms" % (ms, up, m2l, down, ev, fl / (m2l * 1e-3) / 1e12, m2l_dense))
     del pos, mass, M, L, E
+    return res
+
+
+def bench_small(torch, fmm, ctx, K, W):
+    """Batches too small to fill the GPU: the step of one sub-grid, and the M2L of 128
+    drawn like the uneven workload, as the library plans them (parts of sub-grids), over
+    whole sub-grids, and the latter batch as the autotuner leaves it."""
+    def times(step, split):
+        ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, split)
+        try:
+            return timed(torch, step, K, W, marks=1)[1][:, 0]
+        finally:
+            ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, -1)
+
+    w1 = synth.config(1)
+    d1, m1, l1 = fmm.make_descriptors(w1.p, w1.log2_inv_h, w1.mask)
+    p1, ms1 = synth.subgrid_particles(w1.seed)
+    pos1 = torch.from_numpy(p1).to("cuda")
+    mass1 = torch.from_numpy(ms1).to("cuda")
+    M1 = torch.empty(m1, dtype=torch.float64, device="cuda")
+    L1 = torch.empty(l1, dtype=torch.float64, device="cuda")
+
+    def step_one(ev, i):
+        if ev: ev[0].record()
+        ctx.p2m_m2l(d1, pos1, mass1, 8, M1, L1, fmm.FMM_FP64_HARMONIC)
+        if ev: ev[1].record()
+
+    one, one_whole = times(step_one, -1), times(step_one, 0)
+    res = {"single_subgrid": {"workload": "single_subgrid_p3", "pairs": fmm.pair_count(d1),
+                              "step_ms_median": float(np.median(one)), "step_ms_min": float(one.min()),
+                              "whole_subgrid_step_ms_median": float(np.median(one_whole)),
+                              "whole_subgrid_step_ms_min": float(one_whole.min())}}
+    log("single sub-grid step %.3f ms (median), %.3f ms over the whole sub-grid"
+        % (np.median(one), np.median(one_whole)))
+
+    w128 = synth.config(3, nsub=128)
+    d128, m128, l128 = fmm.make_descriptors(w128.p, w128.log2_inv_h, w128.mask)
+    p128, ms128 = upload_batch(torch, w128)
+    M128 = torch.empty(m128, dtype=torch.float64, device="cuda")
+    L128 = torch.empty(l128, dtype=torch.float64, device="cuda")
+    ctx.p2m(d128, p128, ms128, 8, M128)
+
+    def step_small(ev, i):
+        if ev: ev[0].record()
+        ctx.m2l(d128, M128, L128, fmm.FMM_FP64_HARMONIC)
+        if ev: ev[1].record()
+
+    planned, whole = times(step_small, -1), times(step_small, 0)
+    chosen = ctx.autotune(d128, M128, torch.empty_like(L128), fmm.FMM_FP64_HARMONIC)
+    tuned = times(step_small, -1)
+    res["small_uneven_batch"] = {"workload": "uneven_128_mixed_p (p 1:2:1, random masks, three spacings)",
+                                 "pairs": fmm.pair_count(d128), "form": "harmonic",
+                                 "m2l_ms": float(np.median(planned)),
+                                 "whole_subgrids_m2l_ms": float(np.median(whole)),
+                                 "autotuned_m2l_ms": float(np.median(tuned)), "autotune_choice": chosen}
+    log("uneven 128: M2L %.3f ms as planned, %.3f ms over whole sub-grids, %.3f ms autotuned"
+        % (np.median(planned), np.median(whole), np.median(tuned)))
     return res
 
 
@@ -562,7 +619,7 @@ def main():
                                                            seg_h[:, 0].mean())}), flush=True)
         ctx.close()
         return
-    ctx.p2m_m2l(desc, pos, mass, 8, M, L, fmm.FMM_FP64_HARMONIC)   # graph capture, untimed
+    ctx.p2m_m2l(desc, pos, mass, 8, M, L, fmm.FMM_FP64_HARMONIC)   # first call, untimed
 
     def step(ev, i):
         if ev: ev[0].record()
@@ -578,7 +635,7 @@ def main():
 
     # the same step as two launches: P2M, then the M2L-only kernel (same bits)
     Lu = torch.empty_like(L)
-    ctx.m2l(desc, M, Lu, fmm.FMM_FP64_HARMONIC)                # graph capture, untimed
+    ctx.m2l(desc, M, Lu, fmm.FMM_FP64_HARMONIC)                # first call, untimed
 
     def step_two(ev, i):
         if ev: ev[0].record()
@@ -718,70 +775,7 @@ def main():
         out["tree"] = bench_tree(torch, fmm, ctx, K, W)
         torch.cuda.empty_cache()
 
-        # ---------------- one sub-grid: the latency of the step (too small to fill the GPU)
-        w1 = synth.config(1)
-        d1, m1, l1 = fmm.make_descriptors(w1.p, w1.log2_inv_h, w1.mask)
-        p1, ms1 = synth.subgrid_particles(w1.seed)
-        pos1 = torch.from_numpy(p1).to("cuda")
-        mass1 = torch.from_numpy(ms1).to("cuda")
-        M1 = torch.empty(m1, dtype=torch.float64, device="cuda")
-        L1 = torch.empty(l1, dtype=torch.float64, device="cuda")
-
-        def step_one(ev, i):
-            if ev: ev[0].record()
-            ctx.p2m_m2l(d1, pos1, mass1, 8, M1, L1, fmm.FMM_FP64_HARMONIC)
-            if ev: ev[1].record()
-
-        _, seg1 = timed(torch, step_one, K, W, marks=1)
-        # the same with parts of the sub-grid asked for
-        ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, 1)
-        try:
-            _, seg1s = timed(torch, step_one, K, W, marks=1)
-        finally:
-            ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, -1)
-        out["single_subgrid"] = {"workload": "single_subgrid_p3", "pairs": fmm.pair_count(d1),
-                                 "step_ms_median": float(np.median(seg1[:, 0])),
-                                 "step_ms_min": float(seg1[:, 0].min()),
-                                 "round_split_step_ms_median": float(np.median(seg1s[:, 0])),
-                                 "round_split_step_ms_min": float(seg1s[:, 0].min())}
-        log("single sub-grid step %.3f ms (median), %.3f ms in parts of its targets"
-            % (np.median(seg1[:, 0]), np.median(seg1s[:, 0])))
-        del pos1, mass1, M1, L1
-
-        # ---------------- a small uneven batch (128 sub-grids drawn like the uneven
-        # workload): M2L with one workgroup per sub-grid and in parts
-        w128 = synth.config(3, nsub=128)
-        d128, m128, l128 = fmm.make_descriptors(w128.p, w128.log2_inv_h, w128.mask)
-        p128, ms128 = upload_batch(torch, w128)
-        M128 = torch.empty(m128, dtype=torch.float64, device="cuda")
-        L128 = torch.empty(l128, dtype=torch.float64, device="cuda")
-        ctx.p2m(d128, p128, ms128, 8, M128)
-
-        def step_small(ev, i):
-            if ev: ev[0].record()
-            ctx.m2l(d128, M128, L128, fmm.FMM_FP64_HARMONIC)
-            if ev: ev[1].record()
-
-        _, seg_sw = timed(torch, step_small, K, W, marks=1)
-        ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, 1)
-        try:
-            _, seg_ss = timed(torch, step_small, K, W, marks=1)
-        finally:
-            ctx.set_option(fmm.FMM_OPT_ROUND_SPLIT, -1)
-        # and as the autotuner leaves it (parts, as planned at this size)
-        Lt128 = torch.empty_like(L128)
-        tuned128 = ctx.autotune(d128, M128, Lt128, fmm.FMM_FP64_HARMONIC)
-        del Lt128
-        _, seg_st = timed(torch, step_small, K, W, marks=1)
-        out["small_uneven_batch"] = {"workload": "uneven_128_mixed_p (p 1:2:1, random masks, three spacings)",
-                                     "pairs": fmm.pair_count(d128),
-                                     "form": "harmonic", "m2l_ms": float(np.median(seg_sw[:, 0])),
-                                     "round_split_m2l_ms": float(np.median(seg_ss[:, 0])),
-                                     "autotuned_m2l_ms": float(np.median(seg_st[:, 0])),
-                                     "autotune_choice": tuned128}
-        log("uneven 128: M2L %.3f ms, %.3f ms in parts of its targets, %.3f ms autotuned"
-            % (np.median(seg_sw[:, 0]), np.median(seg_ss[:, 0]), np.median(seg_st[:, 0])))
-        del p128, ms128, M128, L128
+        out.update(bench_small(torch, fmm, ctx, K, W))
 
         # ---------------- CPU baseline (the oracle on the host cores)
         out["cpu_baseline"] = cpu_baseline(w.nsub, args.cpu_seconds)

@@ -104,9 +104,9 @@ struct HOut {
 };
 
 struct MfmaTables {
-  // forward, per order p: [rounds][quad][comp of pair][n-group][kk*4 + j] float64
+  // per-wave forward, per order p: [rounds][quad][comp of pair][n-group][kk*4 + j] float64
   double* fwd[kMaxP + 1] = {};
-  // forward with LDS-staged tables, per order p: [rounds][quad][n-group][kk*4 + j][comp of pair]
+  // streamed forward, per order p: [rounds][quad][n-group][kk*4 + j][comp of pair]
   double* fwdl[kMaxP + 1] = {};
   // split precision, per order p: [rounds][quad][n-group][kk*4 + j][comp of pair][hi, lo] float32
   float* fwds[kMaxP + 1] = {};
@@ -193,7 +193,7 @@ hipError_t launch_m2l_split(const MfmaTables& t, const WorkList& w, const DevDes
 bool mfma_config_streams(int cfg);
 // false: the same kernel as another configuration
 bool mfma_config_distinct(int cfg);
-// The other FMM_FP64 and the split-precision configurations, over whole sub-grids.
+// The other FMM_FP64 configurations (tables loaded per wave), over whole sub-grids.
 hipError_t launch_m2l_mfma(const MfmaTables& t, const WorkList& w, const DevDesc* d_desc,
                            const double* M, double* L, fmm_precision prec, int cfg, hipStream_t s);
 // The streamed forward, dense or harmonic form, over a list of parts

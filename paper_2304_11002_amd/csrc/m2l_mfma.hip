@@ -1,24 +1,25 @@
-// Matrix-core M2L on gfx950: v_mfma_f64_4x4x4_4b (four independent 4x4x4
-// products per instruction), persistent workgroups over a longest-first list
-// of sub-grids.
+// Matrix-core M2L on gfx950: v_mfma_f64_16x16x4 and v_mfma_f64_4x4x4_4b (four
+// independent 4x4x4 products per instruction), workgroups over a longest-first list
+// of sub-grids or of parts of them.
 //
-// Forward (one workgroup owns one sub-grid's 512 targets for the whole sum):
+// Forward (every target's whole sum belongs to one work item):
 //   L[t][n] = h^(-1-|n|) sum_d sum_k [h^-|k| M_k(t + d)] T_d[k][n]
 // is a sum over (d, k) of rank-1 updates of the [512 x C] output. The
 // reduction is taken four stencil offsets at a time for one moment
 // component: one instruction multiplies a [16 cells x 4 offsets] slice of the
-// shifted source window (A) by [4 offsets x 4 components] of the tables (B),
-// for four groups of 4 cells at once. C = 20 splits into five column groups
-// of 4, so no column padding is computed at p = 3.
+// shifted source window (A) by [4 offsets x 16 (or 4) columns] of the tables (B).
+// The columns past the last sixteen go in groups of four, so no column padding is
+// computed at p = 3.
 //
-// Data movement: the 20^3 reachable window of two moment components at a
-// time ("round") is staged in LDS as double2 (128,000 bytes), zero on absent
-// blocks and pre-scaled by h^-|k| (exact powers of two); every cell of it is
-// then reused by all 892 offsets. Table operands stream from L2 (the packed
-// tables are laid out in consumption order). The only HBM traffic is the
-// window (read once) and L.
+// Data movement: the window of two moment components at a time ("round") that the
+// item's targets reach is staged in LDS as double2 (128,000 bytes for a whole
+// sub-grid), zero on absent blocks and pre-scaled by h^-|k| (exact powers of two);
+// every cell of it is then reused by all 892 offsets. Table operands stream from L2
+// (the packed tables are laid out in consumption order). The only HBM traffic is the
+// window and L.
 //
-// Operand lane layouts of v_mfma_f64_4x4x4_4b (checked on gfx950):
+// Operand lane layouts of v_mfma_f64_4x4x4_4b (checked on gfx950; 16x16x4 takes the
+// same A, its D layout is with the streamed forward below):
 //   A: lane l -> block (l%16)/4, row l%4, k l/16   (so: cell l%16 of a 16-cell tile)
 //   B: lane l -> block (l%16)/4, col l%4, k l/16
 //   D: lane l -> block (l%16)/4, col l%4, row l/16 (so: cell 4*((l%16)/4) + l/16)
@@ -80,7 +81,7 @@ __device__ __forceinline__ v4d mfma16(double a, double b, v4d c) {
 __global__ void reset_counter_kernel(unsigned* counter) { *counter = 0u; }
 
 // ---------------------------------------------------------------------------
-// forward
+// forward, table operands loaded per wave (FMM_FP64 configurations 2 to 5)
 // ---------------------------------------------------------------------------
 
 template <int P, int WAVES, bool PF>
@@ -275,9 +276,10 @@ __global__ void __launch_bounds__(WAVES * 64) m2l_fwd_kernel(
 // 2000 -> 1230 us, where whole ones take two waves); two workgroups share a
 // compute unit, but their staging still costs (a window of 14 planes for 2 target
 // planes, and one workgroup's loads in flight hold up the other's table
-// operands), so large batches go in whole sub-grids (4096 at p = 3, harmonic:
-// 14.26 ms, 67 TFLOP/s executed, in parts 14.5, and 15.2 with the four-block
-// instruction and tables staged through LDS). plan_stream and split_items choose.
+// operands), so large batches go in whole sub-grids (2000 at p = 3, harmonic: 7.29
+// ms, in parts 7.53, and 7.69 with the four-block instruction and tables staged
+// through LDS; 4096: 14.6 ms, 65.6 TFLOP/s executed). plan_stream and split_items
+// choose.
 //
 // Columns. Sixteen output columns at a time go through v_mfma_f64_16x16x4
 // ([16 cells x 4 offsets] x [4 offsets x 16 columns]), which sums the offsets in
@@ -1468,7 +1470,7 @@ __global__ void __launch_bounds__(kBwdThreads) m2l_bwd_kernel(
 // ---------------------------------------------------------------------------
 
 // forward: [r][q][c][g][kk*4 + j] = T_{4q+kk}[2r+c][4g+j]
-// LDS-staged forward: [r][q][g][kk*4 + j][c], same values
+// streamed forward: [r][q][g][kk*4 + j][c], same values
 __global__ void pack_fwd_kernel(const double* __restrict__ T, int p, double* __restrict__ out,
                                 double* __restrict__ outl) {
   const int C = ncomp(p), NG = (C + 3) / 4, ROUNDS = (C + 1) / 2;
