@@ -262,6 +262,8 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // Sizes of a set's allocations: sets that replace each other mostly have the same
 // (a new size costs hipHostMalloc 100 to 150 us, one just freed 15).
 size_t alloc_size(size_t x) {
+  constexpr size_t kStep = 1 << 20;
+  if (x > kStep) return align_up(x, kStep);
   size_t n = 64 << 10;
   while (n < x) n *= 2;
   return n;
